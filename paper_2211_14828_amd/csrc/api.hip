@@ -290,7 +290,8 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
       }
     } else {
       P.maxSJ = std::max(P.maxSJ, g.S * g.J);
-      GramArgs ga = gram_plan(P.gelem, g.A, g.I, g.B, (int)g.S, cu_count());
+      // a sampled mode takes no sketch with the whole unfolding (run_mode_heavy)
+      GramArgs ga = gram_plan(P.gelem, g.A, g.I, g.B, g.sampled ? 0 : (int)g.S, cu_count(), (int)g.S);
       P.partial_bytes = std::max(P.partial_bytes, gram_partial_bytes(ga, P.gelem));
     }
   }
@@ -581,7 +582,7 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
       ProfScope ps("omega", st);
       HIPCHK(launch_omega(P.gelem, P.seed, n, S * g.J, L.omegaT, st));
     }
-    GramArgs ga = gram_plan(P.gelem, g.A, g.I, g.B, Sf, cu_count());
+    GramArgs ga = gram_plan(P.gelem, g.A, g.I, g.B, Sf, cu_count(), (int)S);
     ga.X = xsrc;
     ga.omegaT = L.omegaT;
     ga.partial = L.partial;

@@ -1,460 +1,529 @@
-// Sketch and Gram products of one mode, in a single pass over the tensor.
+// Sketch and Gram products of one mode, in a single pass over the tensor
+// (float64, float32 and bfloat16 operands; the mixed forms' large modes have a
+// pipelined kernel of their own, gram_pipe.hip).
 //
 // For the mode-n view [A, I, B] of the row-major tensor (Table 1:
 // X_(n)[i, a*B + b] = X[a, i, b], never materialised) this computes
-//   C = X_(n) X_(n)^T            (I x I, lower-triangle tiles)     (Remark 1)
-//   W = X_(n) Omega^(n)          (I x S, read through Omega^T)     (Alg. 1, step 2)
-// as one extended product [X_(n); Omega^T] x X_(n)^T: the output tiles are the
-// lower triangle of C plus one tile column per 128 sketch columns.  Each
-// workgroup owns one 128 x 128 output tile and one contiguous slice of the
-// contraction index (split-K); slices are reduced in a fixed order in float64
-// by a second kernel, so results are deterministic.
+//   C = X_(n) X_(n)^T            (I x I, lower triangle)           (Remark 1)
+//   W = X_(n) Omega^(n)          (I x S, as Omega^T X_(n)^T)       (Alg. 1, step 2)
+// The output is cut into 32 x 32 blocks, and only the wanted ones are formed
+// and stored: the lower triangle of C and S rows of W^T.  A workgroup of four
+// waves owns one tile and a slice of the contraction (split-K); each wave forms
+// up to 2 x 2 blocks.  Tiles:
+//   C     128 rows x 128 columns, lower triangle (a diagonal tile stages its
+//         rows once; its upper-right wave has nothing to do);
+//   W     64 sketch rows x 256 columns;
+//   thin  I <= 64 and S <= 64: the mode's 64 rows and the sketch's 64 rows
+//         staged together, each wave 32 of them by the mode's 64 columns, so X
+//         is read once (the modes of a 64^5 tensor are bound by that read).
+// The slices are summed in a fixed order in float64 by a second kernel, so
+// results are deterministic.
 //
-// The contraction index runs over K tiles that never cross an a-slab: for
-// B > 1 a tile is (a, b0 .. b0+BK) (rows of X[a] are contiguous in b, masked
-// at the slab end); for B == 1 (last mode) a tile is a0 .. a0+BK and the
-// operand is transposed while it is staged into LDS.
+// Float32 operands are split exactly into three bfloat16 parts while they are
+// staged, x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m (24
+// significand bits in three parts of 8; the parts of a finite x are exact),
+// and every product is formed from the six part products above 2^-24,
+// hh + hm + mh + mm + hl + lh, on 32x32x16 bfloat16 MFMA with float32
+// accumulation.  The terms left out (ml, lm, ll) are below 2^-25 of a product
+// and of either sign.  hh and the five smaller products have an accumulator
+// each, so a sum is rounded once per 16 K values against 16 times with the
+// 32x32x2 float32 MFMA: for 32 rows of Gaussian values over 16384 columns the
+// diagonal's error against float64 is 6.2e-7 (1.9e-6 with the float32 MFMA,
+// 3.1e-6 with one accumulator for all six), over 256 columns 8.4e-8 (1.9e-7).
+// The float32 MFMA has a sixteenth of the bfloat16 rate; six products leave
+// 2.7 times its rate.
 //
-// Workgroups are dispatched round-robin over the 8 XCDs.  When the split count
-// is a multiple of 8, all tiles of one split are mapped to the same XCD so the
-// slab of X that they share is fetched from HBM once into that XCD's L2.
+// K tiles are 128 bytes of a row.  For B of at least a tile, a tile is
+// (a, b0 .. b0 + KT), rows contiguous in b, read as 16-byte pieces (which need
+// no alignment beyond the element's).  For smaller B (the last mode, and the
+// mode before a thin last one) a tile is KT / B whole values of a; the lanes
+// then run over the mode's rows and each thread gathers its K values, so the
+// staged layout needs no transposition.  A slab's last tile overlaps the one
+// before it, with the values they share zeroed, so no load is masked.
 //
-// Thin modes (float32, I <= 64 and S <= 64, e.g. the 64-row modes of a 64^5
-// tensor) use one 128 x 64 output tile instead of two 128 x 128 ones: the
-// staged operand holds the mode's rows (0..63) and the sketch rows (64..127),
-// the other operand is its first 64 rows, so the tile is [C; W^T] and a wave
-// computes 64 x 32 of it.  Two thirds of its products are wanted, against a
-// sixth for the square tiles.
+// Workgroups are dispatched round-robin over the 8 XCDs.  Those of one XCD take
+// consecutive (split, tile) pairs, so the tiles of a split, which share a slab
+// of X, run on one XCD (or two) and the slab is fetched from HBM once into its
+// L2, for any number of splits.
+// Measured per mode, against 128 x 128 tiles on the MFMA of the operand's own
+// type: float32 1000^3, S = 60, 12.5 ms (20.2; bound by its loads and by the
+// staging between two barriers a K tile, the matrix cores a third busy), 400^3,
+// S = 30, 0.41 ms (1.12); float32 64^5, S = 22, 1.55 ms (2.75; 2.8 TB/s of X);
+// float64 200^3, S = 15, 0.11 ms (0.22).
 #include "rbki_kernels.h"
-#include "rbki_mma.h"
 #include "rbki_philox.h"
 
 namespace rbki {
 
 namespace {
 
+constexpr int BLK = 32;                  // output blocks
+constexpr int GROUP = 64;                // staged rows come in groups of 64
+constexpr int GROUPS_TILE = 5;           // the most groups of a tile (W: 1 + 4)
+constexpr int GROUPS_THIN = 2;
+
+template <int E> struct Op;
+template <> struct Op<E_F64> {
+  typedef double T;
+  typedef double Out;
+  typedef f64x4_t Acc;
+  // NACC: accumulators of one row of two blocks (float32: also those of the
+  // part products below hh)
+  static constexpr int KT = 16, EPC = 2, NACC = 8, GROUP_BYTES = GROUP * 128;
+};
+template <> struct Op<E_F32> {
+  typedef float T;
+  typedef float Out;
+  typedef f32x16_t Acc;
+  static constexpr int KT = 32, EPC = 4, NACC = 4, GROUP_BYTES = GROUP * 192;   // three bfloat16 planes
+};
+template <> struct Op<E_BF16> {
+  typedef bf16_t T;
+  typedef float Out;
+  typedef f32x16_t Acc;
+  static constexpr int KT = 64, EPC = 8, NACC = 2, GROUP_BYTES = GROUP * 128;
+};
+
+typedef __attribute__((ext_vector_type(2))) float f32pair_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16pair_t;
+typedef uint32_t u32x4u_t __attribute__((ext_vector_type(4), aligned(2)));
+
+// The bfloat16 parts of two floats, packed (low half first).
+__device__ inline uint32_t pack_bf16(float x0, float x1) {
+  const f32pair_t v = {x0, x1};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16pair_t));
+}
+__device__ inline void split3(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = pack_bf16(x0, x1);
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xFFFF0000u);
+  m = pack_bf16(r0, r1);
+  l = pack_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xFFFF0000u));
+}
+
+// Where the K values of a tile lie: element offsets from a row's start, and
+// the values [lo, hi) of the tile that count (the others are zeroed).
+struct KTile {
+  int64_t x, o;      // in X (a I B + b0) and in a row of Omega^T (a B + b0)
+  int lo, hi;
+};
+
+// One thread's share of a staged group: 32 bytes of K values, as words.
+struct Piece {
+  uint32_t u[8];
+};
+
+// Rows by 16-byte pieces: piece j of a thread is row (tid / 8) + 32 j, K
+// values (tid % 8) EPC ...  p[j] points at the first of them for K offset 0.
 template <int E>
-struct Stage {
-  typedef typename Mma<E>::T T;
-  static constexpr int BK = Mma<E>::BK;
-  static constexpr int EPC = 16 / (int)sizeof(T);     // elements per 16-byte chunk
-  uint4 chunk[4];
-  unsigned valid;                                     // VEC form: bit j = chunk j in range
-};
+__device__ inline void load_rows(Piece& r, const typename Op<E>::T* const (&p)[2], int64_t off) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const u32x4u_t v = *(const u32x4u_t*)(p[j] + off);
+    r.u[4 * j] = v.x; r.u[4 * j + 1] = v.y; r.u[4 * j + 2] = v.z; r.u[4 * j + 3] = v.w;
+  }
+}
 
-// Load one operand tile (128 rows x BK k) of the mode view into registers.
-// omega_rows: rows are sketch columns s (rows of Omega^T, length J).
-//
-// VEC (rows and row strides a multiple of 16 bytes, so a 16-byte chunk is
-// either wholly inside the tile or wholly outside): every lane issues its
-// loads unconditionally from a clamped, always valid address and records
-// which chunks are real; the mask is applied when the chunks are written to
-// LDS.  No load sits under divergent control flow, so all of them stay in
-// flight together while the previous K tile is multiplied.  The other form
-// reads element by element with per-element bounds.
-template <int E, bool VEC>
-__device__ inline void load_operand(Stage<E>& st, const GramArgs& g, const void* base, bool omega_rows,
-                                    int64_t row0, int64_t nrows, int64_t a, int64_t b0, int64_t kvalid) {
-  typedef typename Mma<E>::T T;
-  constexpr int EPC = Stage<E>::EPC;
-  constexpr int BK = Stage<E>::BK;
-  const T* X = (const T*)base;
+// Rows across the lanes: thread (row tid % 64, wave w) takes K values
+// w KT / 4 ... of its row at byte offset rb; koff: the values' offsets (the
+// same for the whole wave), those from nk on do not exist.
+template <int E>
+__device__ inline void load_gather(Piece& r, const typename Op<E>::T* X, uint32_t rb, const int64_t* koff, int64_t off,
+                                   int nk) {
+  typedef typename Op<E>::T T;
+  constexpr int KW = Op<E>::KT / 4;
+  const int k0 = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * KW;
+#pragma unroll
+  for (int k = 0; k < KW; ++k) {
+    T v = 0;
+    if (k0 + k < nk) v = *(const T*)((const char*)(X + (off + koff[k])) + rb);
+    if constexpr (E == E_F64) {
+      const uint64_t w = __builtin_bit_cast(uint64_t, v);
+      r.u[2 * k] = (uint32_t)w;
+      r.u[2 * k + 1] = (uint32_t)(w >> 32);
+    } else if constexpr (E == E_F32) {
+      r.u[k] = __float_as_uint(v);
+    } else {
+      r.u[k / 2] = k & 1 ? r.u[k / 2] | (uint32_t)v << 16 : (uint32_t)v;
+    }
+  }
+}
+
+// Zero the values of a piece outside [lo, hi); k(e): the K value of element e.
+template <int E, class K>
+__device__ inline void clip(Piece& r, int lo, int hi, K k) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if constexpr (E == E_BF16) {
+      const int k0 = k(2 * i), k1 = k(2 * i + 1);
+      r.u[i] &= (k0 >= lo && k0 < hi ? 0x0000FFFFu : 0u) | (k1 >= lo && k1 < hi ? 0xFFFF0000u : 0u);
+    } else {
+      const int ki = k(E == E_F64 ? i / 2 : i);
+      if (ki < lo || ki >= hi) r.u[i] = 0;
+    }
+  }
+}
+
+// LDS: a row holds its K values in 16-byte chunks, the chunk index XOR-swizzled
+// with the row so that the 32 (or 16) rows of one operand read and the 64 banks
+// meet without conflicts.  Float32: three planes of 64-byte rows.
+// (A multiple of 16 rows more moves the place by whole rows.)
+template <int E> constexpr int LDS_ROW_BYTES = E == E_F32 ? 64 : 128;
+template <int E>
+__device__ inline int lds_at(int row, int q) {
+  if constexpr (E == E_F32) return row * 64 + ((q ^ (row >> 2)) & 3) * 16;
+  else return row * 128 + ((q ^ (row >> 1)) & 7) * 16;
+}
+
+template <int E, bool GATHER>
+__device__ inline void store_piece(Piece r, char* lds, int plane, int grow, const KTile& t) {
+  typedef Op<E> O;
   const int tid = threadIdx.x;
-  if (VEC) st.valid = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = tid + 256 * j;
-    if (g.B > 1 || omega_rows) {
-      // chunk c: row c / (BK/EPC), k offset (c % (BK/EPC)) * EPC
-      const int row = c / (BK / EPC);
-      const int kk = (c % (BK / EPC)) * EPC;
-      const int64_t r = row0 + row;
-      if (VEC) {
-        const bool ok = r < nrows && kk < kvalid;
-        const int64_t rc = r < nrows ? r : nrows - 1;
-        const int kc = kk < kvalid ? kk : 0;
-        const int64_t off = omega_rows ? rc * g.J + (g.B > 1 ? a * g.B + b0 : b0) + kc
-                                       : (a * g.I + rc) * g.B + b0 + kc;
-        st.chunk[j] = *(const uint4*)(X + off);
-        st.valid |= ok ? 1u << j : 0u;
-      } else {
-        union { uint4 v; T e[EPC]; } u;
-        u.v = make_uint4(0, 0, 0, 0);
-        if (r < nrows) {
-          const int64_t off = omega_rows ? r * g.J + (g.B > 1 ? a * g.B + b0 : b0) + kk
-                                         : (a * g.I + r) * g.B + b0 + kk;
-#pragma unroll
-          for (int e = 0; e < EPC; ++e)
-            if (kk + e < kvalid) u.e[e] = X[off + e];
-        }
-        st.chunk[j] = u.v;
-      }
-    } else {
-      // B == 1, rows of X_(n) are the contiguous index: chunk c covers EPC
-      // consecutive rows at one k.
-      const int per_k = TILE / EPC;
-      const int kk = c / per_k;
-      const int row = (c % per_k) * EPC;
-      const int64_t r = row0 + row;
-      if (VEC) {
-        const bool ok = kk < kvalid && r < nrows;
-        const int64_t rc = r < nrows ? r : nrows - EPC;
-        const int kc = kk < kvalid ? kk : 0;
-        st.chunk[j] = *(const uint4*)(X + (b0 + kc) * g.I + rc);   // b0 is a0 here
-        st.valid |= ok ? 1u << j : 0u;
-      } else {
-        union { uint4 v; T e[EPC]; } u;
-        u.v = make_uint4(0, 0, 0, 0);
-        if (kk < kvalid) {
-          const int64_t off = (b0 + kk) * g.I + r;
-#pragma unroll
-          for (int e = 0; e < EPC; ++e)
-            if (r + e < nrows) u.e[e] = X[off + e];
-        }
-        st.chunk[j] = u.v;
-      }
-    }
-  }
-}
-
-template <int E, bool VEC>
-__device__ inline void store_operand(const Stage<E>& st, const GramArgs& g, bool omega_rows, char* lds) {
-  typedef typename Mma<E>::T T;
-  constexpr int EPC = Stage<E>::EPC;
-  constexpr int BK = Stage<E>::BK;
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = tid + 256 * j;
-    uint4 v = st.chunk[j];
-    if (VEC && !((st.valid >> j) & 1u)) v = make_uint4(0, 0, 0, 0);
-    if (g.B > 1 || omega_rows) {
-      const int row = c / (BK / EPC);
-      const int kk = (c % (BK / EPC)) * EPC;
-      *(uint4*)(lds + row * LDS_ROW + kk * (int)sizeof(T)) = v;
-    } else {
-      const int per_k = TILE / EPC;
-      const int kk = c / per_k;
-      const int row = (c % per_k) * EPC;
-      union { uint4 v; T e[EPC]; } u;
-      u.v = v;
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) *(T*)(lds + (row + e) * LDS_ROW + kk * (int)sizeof(T)) = u.e[e];
-    }
-  }
-}
-
-__device__ inline void decode_tile(const GramArgs& g, int tile, int& ti, int& tj, bool& is_w) {
-  if (tile < g.ntri) {
-    // tile = ti*(ti+1)/2 + tj, tj <= ti
-    int t = (int)((sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
-    while ((t + 1) * (t + 2) / 2 <= tile) ++t;
-    while (t * (t + 1) / 2 > tile) --t;
-    ti = t;
-    tj = tile - t * (t + 1) / 2;
-    is_w = false;
-  } else {
-    int w = tile - g.ntri;
-    ti = w / g.nw;
-    tj = w % g.nw;
-    is_w = true;
-  }
-}
-
-// Thin tile staging (float32): chunk j < 2 of a thread is one of 512 chunks
-// of the mode's 64 rows, j >= 2 one of the sketch's 64 rows.
-struct ThinStage {
-  uint4 chunk[4];
-  unsigned valid;
-};
-
-template <bool VEC>
-__device__ inline void load_thin(ThinStage& st, const GramArgs& g, int64_t a, int64_t b0, int64_t kvalid) {
-  const float* X = (const float*)g.X;
-  const float* O = (const float*)g.omegaT;
-  const int tid = threadIdx.x;
-  st.valid = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = tid + 256 * (j & 1);
-    if (j < 2 && g.B == 1) {
-      // the last mode: rows of X_(n) are the contiguous index; chunk c covers
-      // 4 consecutive rows at one k
-      const int kk = c >> 4, row = (c & 15) * 4;
-      const bool ok = kk < kvalid && row < g.I;
-      if (VEC) {
-        const int64_t rc = row < g.I ? row : g.I - 4;
-        const int kc = kk < kvalid ? kk : 0;
-        st.chunk[j] = *(const uint4*)(X + (b0 + kc) * g.I + rc);
-      } else {
-        union { uint4 v; float e[4]; } u;
-        u.v = make_uint4(0, 0, 0, 0);
-        if (kk < kvalid) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (row + e < g.I) u.e[e] = X[(b0 + kk) * g.I + row + e];
-        }
-        st.chunk[j] = u.v;
-      }
-      st.valid |= ok ? 1u << j : 0u;
-    } else {
-      // row c / 8, k offset (c % 8) * 4; the mode's rows or the sketch's
-      const int row = c >> 3, kk = (c & 7) * 4;
-      const bool om = j >= 2;
-      const int64_t nrows = om ? g.S : g.I;
-      const bool ok = row < nrows && kk < kvalid;
-      const int64_t kbase = g.B > 1 ? a * g.B + b0 : b0;
-      if (VEC) {
-        const int64_t rc = row < nrows ? row : nrows - 1;
-        const int kc = kk < kvalid ? kk : 0;
-        st.chunk[j] = om ? *(const uint4*)(O + rc * g.J + kbase + kc)
-                         : *(const uint4*)(X + (a * g.I + rc) * g.B + b0 + kc);
-      } else {
-        union { uint4 v; float e[4]; } u;
-        u.v = make_uint4(0, 0, 0, 0);
-        if (row < nrows) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (kk + e < kvalid)
-              u.e[e] = om ? O[(int64_t)row * g.J + kbase + kk + e] : X[(a * g.I + row) * g.B + b0 + kk + e];
-        }
-        st.chunk[j] = u.v;
-      }
-      st.valid |= ok ? 1u << j : 0u;
-    }
-  }
-}
-
-__device__ inline void store_thin(const ThinStage& st, const GramArgs& g, char* lds) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = tid + 256 * (j & 1);
-    const uint4 v = ((st.valid >> j) & 1u) ? st.chunk[j] : make_uint4(0, 0, 0, 0);
-    if (j < 2 && g.B == 1) {
-      const int kk = c >> 4, row = (c & 15) * 4;
-      union { uint4 v; float e[4]; } u;
-      u.v = v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) *(float*)(lds + (row + e) * LDS_ROW + kk * 4) = u.e[e];
-    } else {
-      const int row = (c >> 3) + (j >= 2 ? 64 : 0), kk = (c & 7) * 4;
-      *(uint4*)(lds + row * LDS_ROW + kk * 4) = v;
-    }
-  }
-}
-
-// One K tile of the thin product for a wave's 64 x 32 block: rows wr + 32 m
-// + (lane % 32) of the staged operand, columns wc + (lane % 32) of its first
-// 64 rows (the 32x32 layout of rbki_mma.h, blocks m = 0, 1).
-__device__ inline void thin_step(f32x16_t (&c)[2], const char* lds, int lane, int wr, int wc) {
-  const int half = lane >> 5, r = lane & 31;
-  float a[2][16], b[16];
-#pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const float4* pa = (const float4*)(lds + (wr + m * 32 + r) * LDS_ROW + half * 64);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 v = pa[q];
-      a[m][4 * q] = v.x; a[m][4 * q + 1] = v.y; a[m][4 * q + 2] = v.z; a[m][4 * q + 3] = v.w;
-    }
-  }
-  const float4* pb = (const float4*)(lds + (wc + r) * LDS_ROW + half * 64);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4 v = pb[q];
-    b[4 * q] = v.x; b[4 * q + 1] = v.y; b[4 * q + 2] = v.z; b[4 * q + 3] = v.w;
-  }
-#pragma unroll
-  for (int t = 0; t < 16; ++t)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) c[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m][t], b[t], c[m], 0, 0, 0);
-}
-
-template <bool VEC>
-__device__ inline void thin_tile(const GramArgs& g, int split, char (&lds)[2][2][TILE * LDS_ROW]) {
-  constexpr int BK = Mma<E_F32>::BK;
-  const int64_t kt0 = (int64_t)split * g.nkt / g.splits;
-  const int64_t kt1 = (int64_t)(split + 1) * g.nkt / g.splits;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wr = (wave >> 1) * 64, wc = (wave & 1) * 32;
-  f32x16_t acc[2];
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[m][v] = 0.f;
-  ThinStage st;
-  auto load = [&](int64_t kt) {
-    int64_t a, b0, kv;
-    if (g.B > 1) {
-      a = kt / g.nbt;
-      b0 = (kt - a * g.nbt) * BK;
-      kv = g.B - b0 < BK ? g.B - b0 : BK;
-    } else {
-      a = 0;
-      b0 = kt * BK;
-      kv = g.A - b0 < BK ? g.A - b0 : BK;
-    }
-    load_thin<VEC>(st, g, a, b0, kv);
-  };
-  if (kt0 < kt1) {
-    load(kt0);
-    store_thin(st, g, lds[0][0]);
-    __syncthreads();
-    for (int64_t kt = kt0; kt < kt1; ++kt) {
-      const int buf = (int)((kt - kt0) & 1);
-      const bool more = kt + 1 < kt1;
-      if (more) load(kt + 1);
-      thin_step(acc, lds[buf][0], lane, wr, wc);
-      if (more) store_thin(st, g, lds[buf ^ 1][0]);
-      __syncthreads();
-    }
-  }
-  // rows 0..63: C (row i, column j); rows 64..127: W^T (row 64 + s, column i)
-  float* out = (float*)g.partial + (int64_t)split * (TILE * TILE);
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = wr + m * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      out[row * TILE + wc + (lane & 31)] = acc[m][v];
-    }
-}
-
-template <int E, bool VEC>
-__global__ void __launch_bounds__(256, E == E_F64 ? 1 : 2) gram_sketch_kernel(GramArgs g) {
-  typedef Mma<E> M;
-  typedef typename M::Out Out;
-  constexpr int BK = M::BK;
-  __shared__ __attribute__((aligned(16))) char lds[2][2][TILE * LDS_ROW];
-
+  if (t.lo > 0 || t.hi < O::KT)
+    clip<E>(r, t.lo, t.hi, [&](int e) {
+      return GATHER ? (tid >> 6) * (O::KT / 4) + e : (tid & 7) * O::EPC + e % O::EPC;
+    });
   if constexpr (E == E_F32) {
-    if (g.thin) {
-      // one tile: the split is the workgroup (the XCD map gives the same)
-      thin_tile<VEC>(g, (int)blockIdx.x, lds);
-      return;
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      split3(__uint_as_float(r.u[2 * i]), __uint_as_float(r.u[2 * i + 1]), h[i], m[i], l[i]);
+    if constexpr (GATHER) {
+      char* d = lds + lds_at<E>(grow + (tid & 63), tid >> 6);
+      *(uint4*)d = make_uint4(h[0], h[1], h[2], h[3]);
+      *(uint4*)(d + plane) = make_uint4(m[0], m[1], m[2], m[3]);
+      *(uint4*)(d + 2 * plane) = make_uint4(l[0], l[1], l[2], l[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        char* d = lds + lds_at<E>(grow + (tid >> 3) + 32 * j, (tid & 7) >> 1) + (tid & 1) * 8;
+        *(uint2*)d = make_uint2(h[2 * j], h[2 * j + 1]);
+        *(uint2*)(d + plane) = make_uint2(m[2 * j], m[2 * j + 1]);
+        *(uint2*)(d + 2 * plane) = make_uint2(l[2 * j], l[2 * j + 1]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = GATHER ? (tid & 63) : (tid >> 3) + 32 * j;
+      const int q = GATHER ? 2 * (tid >> 6) + j : (tid & 7);
+      *(uint4*)(lds + lds_at<E>(grow + row, q)) = make_uint4(r.u[4 * j], r.u[4 * j + 1], r.u[4 * j + 2], r.u[4 * j + 3]);
     }
   }
-  // workgroup -> (split, tile)
-  const int w = blockIdx.x;
-  int split, tile;
-  if (g.xcd_map) {
-    const int xcd = w & 7, slot = w >> 3;
-    split = xcd + 8 * (slot / g.ntiles);
-    tile = slot % g.ntiles;
+}
+
+// One K tile of a wave's MB x 2 blocks: rows ra + .., columns rb + .. of the
+// staged rows; bit 2 m + n of mask: 32 x 32 block (m, n) is wanted.
+template <int E, int MB>
+__device__ inline void tile_step(typename Op<E>::Acc (&c)[Op<E>::NACC * MB], const char* lds, int plane, int lane, int ra,
+                                 int rb, int mask) {
+  constexpr int RB = LDS_ROW_BYTES<E>;
+  const char* la = lds + ra * RB;
+  const char* lb = lds + rb * RB;
+  if constexpr (E == E_F64) {
+    const int g = lane >> 4, r = lane & 15;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      // lane group g takes K values 4 g + 2 t, 4 g + 2 t + 1
+      const int at = lds_at<E>(r, 2 * g + t);
+      double2 a[2 * MB], b[4];
+#pragma unroll
+      for (int m = 0; m < 2 * MB; ++m) a[m] = *(const double2*)(la + at + 16 * m * RB);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) b[n] = *(const double2*)(lb + at + 16 * n * RB);
+#pragma unroll
+      for (int m = 0; m < 2 * MB; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          if ((mask >> (2 * (m >> 1) + (n >> 1))) & 1) {
+            c[4 * m + n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m].x, b[n].x, c[4 * m + n], 0, 0, 0);
+            c[4 * m + n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m].y, b[n].y, c[4 * m + n], 0, 0, 0);
+          }
+        }
+    }
   } else {
-    split = w / g.ntiles;
-    tile = w % g.ntiles;
+    constexpr int NP = E == E_F32 ? 3 : 1, NT = E == E_F32 ? 2 : 4;
+    const int half = lane >> 5, r = lane & 31;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int at = lds_at<E>(r, 2 * t + half);
+      bf16x8_t a[MB][NP], b[2][NP];
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m) a[m][p] = *(const bf16x8_t*)(la + at + p * plane + 32 * m * RB);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) b[n][p] = *(const bf16x8_t*)(lb + at + p * plane + 32 * n * RB);
+      }
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+          if ((mask >> (2 * m + n)) & 1) {
+            f32x16_t& big = c[2 * m + n];
+            if constexpr (E == E_F32) {
+              f32x16_t& low = c[2 * MB + 2 * m + n];
+              low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m][2], b[n][0], low, 0, 0, 0);
+              low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m][0], b[n][2], low, 0, 0, 0);
+              low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m][1], b[n][1], low, 0, 0, 0);
+              low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m][1], b[n][0], low, 0, 0, 0);
+              low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m][0], b[n][1], low, 0, 0, 0);
+            }
+            big = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m][0], b[n][0], big, 0, 0, 0);
+          }
+    }
   }
-  int ti, tj;
-  bool is_w;
-  decode_tile(g, tile, ti, tj, is_w);
-  const bool diag = !is_w && ti == tj;
-  const int64_t r0 = (int64_t)ti * TILE, c0 = (int64_t)tj * TILE;
+}
+
+// (ti, tj <= ti) of lower-triangle position t = ti (ti + 1) / 2 + tj.
+__device__ inline void tri_at(int t, int& ti, int& tj) {
+  int i = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while ((i + 1) * (i + 2) / 2 <= t) ++i;
+  while (i * (i + 1) / 2 > t) --i;
+  ti = i;
+  tj = t - i * (i + 1) / 2;
+}
+
+template <int E, bool GATHER, int NG>
+__global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kernel(GramArgs g) {
+  typedef Op<E> O;
+  typedef typename O::T T;
+  typedef typename O::Out Out;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int plane = NG * GROUP * 64;           // float32: bytes of one part's rows
+  constexpr int MB = NG == GROUPS_THIN ? 1 : 2;    // block rows of a wave
+  constexpr int NACC = O::NACC * MB;
+  const T* X = (const T*)g.X;
+  const T* Om = (const T*)g.omegaT;
+
+  // workgroup -> (split, tile): the workgroups of one XCD (ids equal modulo 8)
+  // take consecutive (split, tile) pairs
+  const int per = (g.ntiles * g.splits) >> 3, spare = (g.ntiles * g.splits) & 7, xcd = blockIdx.x & 7;
+  const int id = xcd * per + (xcd < spare ? xcd : spare) + (int)(blockIdx.x >> 3);
+  const int split = id / g.ntiles, tile = id % g.ntiles;
+
+  // the tile's groups: first row and rows that exist (<= 0: not staged), and
+  // whether they are sketch rows
+  int grow[NG], gn[NG];
+  bool gom[NG];
+  // this wave's role: staged rows of its operands, first row and column of its
+  // output (row in the sketch for a W block), wanted blocks
+  const int lane = threadIdx.x & 63;
+  const int wave = (int)__builtin_amdgcn_readfirstlane((threadIdx.x >> 6) + split) & 3;
+  int ra, rb, row0, col0, nrow, mask = 0;
+  bool is_w, diag = false;
+  const int I = (int)g.I, S = g.S;
+  if constexpr (NG == GROUPS_THIN) {
+    grow[0] = 0; gn[0] = I; gom[0] = false;
+    grow[1] = 0; gn[1] = S; gom[1] = true;
+    is_w = wave >= 2;
+    ra = 32 * wave;
+    rb = 0;
+    row0 = 32 * (wave & 1);
+    col0 = 0;
+    diag = !is_w;
+    nrow = is_w ? S : I;
+  } else {
+    is_w = tile >= g.ntri;
+    if (!is_w) {
+      int ti, tj;
+      tri_at(tile, ti, tj);
+      diag = ti == tj;
+#pragma unroll
+      for (int i = 0; i < NG; ++i) {
+        grow[i] = (i < 2 ? ti : tj) * 128 + (i & 1) * 64;
+        gn[i] = i < 2 ? I - grow[i] : (i < 4 && !diag) ? 64 : 0;
+        gom[i] = false;
+      }
+      ra = (wave >> 1) * 64;
+      rb = (diag ? 0 : 128) + (wave & 1) * 64;
+      row0 = ti * 128 + (wave >> 1) * 64;
+      col0 = tj * 128 + (wave & 1) * 64;
+      nrow = I;
+    } else {
+      const int w = tile - g.ntri, sg = w / g.nw, cg = w % g.nw;
+#pragma unroll
+      for (int i = 0; i < NG; ++i) {
+        grow[i] = i == 0 ? sg * 64 : cg * 256 + (i - 1) * 64;
+        gn[i] = (i == 0 ? S : I) - grow[i];
+        gom[i] = i == 0;
+      }
+      ra = 0;
+      rb = 64 + 64 * wave;
+      row0 = sg * 64;
+      col0 = cg * 256 + 64 * wave;
+      nrow = S;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const int r = row0 + 32 * m, c = col0 + 32 * n;
+      if (r < nrow && c < I && (is_w || r >= c)) mask |= 1 << (2 * m + n);
+    }
+
+  // row pointers at K offset 0 (rows past the end repeat the last one: their
+  // products are not wanted)
+  const T* p[NG][2];
+  uint32_t rbyte[NG];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const int last = gn[i] < GROUP ? gn[i] - 1 : GROUP - 1;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = (int)(threadIdx.x >> 3) + 32 * j;
+      p[i][j] = (gom[i] ? Om : X) + (grow[i] + (r < last ? r : last)) * (gom[i] ? g.J : g.B) + (threadIdx.x & 7) * O::EPC;
+    }
+    const int r = (int)(threadIdx.x & 63);
+    rbyte[i] = (uint32_t)(grow[i] + (r < last ? r : last)) * (uint32_t)g.B * (uint32_t)sizeof(T);
+  }
+  // GATHER: K value k of a tile is (a0 + k / B, k % B); nk of them
+  int64_t koff[GATHER ? O::KT / 4 : 1];
+  const int nk = GATHER ? (int)(g.nbt * g.B) : O::KT;
+  if constexpr (GATHER) {
+    const int k0 = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (O::KT / 4);
+#pragma unroll
+    for (int k = 0; k < O::KT / 4; ++k) koff[k] = (int64_t)((k0 + k) / (int)g.B) * g.I * g.B + (k0 + k) % (int)g.B;
+  }
 
   const int64_t kt0 = (int64_t)split * g.nkt / g.splits;
   const int64_t kt1 = (int64_t)(split + 1) * g.nkt / g.splits;
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;
-
-  typename M::Frag f;
-  M::zero(f);
-
-  Stage<E> sa, sb;
-  auto kt_coords = [&](int64_t kt, int64_t& a, int64_t& b0, int64_t& kvalid) {
-    if (g.B > 1) {
-      a = kt / g.nbt;
-      b0 = (kt - a * g.nbt) * BK;
-      kvalid = g.B - b0 < BK ? g.B - b0 : BK;
-    } else {
-      a = 0;
-      b0 = kt * BK;
-      kvalid = g.A - b0 < BK ? g.A - b0 : BK;
-    }
-  };
-  auto load = [&](int64_t kt) {
-    int64_t a, b0, kv;
-    kt_coords(kt, a, b0, kv);
-    load_operand<E, VEC>(sa, g, g.X, false, r0, g.I, a, b0, kv);
-    if (is_w) load_operand<E, VEC>(sb, g, g.omegaT, true, c0, g.S, a, b0, kv);
-    else if (!diag) load_operand<E, VEC>(sb, g, g.X, false, c0, g.I, a, b0, kv);
-  };
-  auto store = [&](int buf) {
-    store_operand<E, VEC>(sa, g, false, lds[buf][0]);
-    if (is_w) store_operand<E, VEC>(sb, g, true, lds[buf][1]);
-    else if (!diag) store_operand<E, VEC>(sb, g, false, lds[buf][1]);
-  };
-
-  if (kt0 < kt1) {
-    load(kt0);
-    store(0);
-    __syncthreads();
-    for (int64_t kt = kt0; kt < kt1; ++kt) {
-      const int buf = (int)((kt - kt0) & 1);
-      const bool more = kt + 1 < kt1;
-      if (more) load(kt + 1);
-      M::step(f, lds[buf][0], diag ? lds[buf][0] : lds[buf][1], lane, wr, wc);
-      if (more) store(buf ^ 1);
-      __syncthreads();
-    }
-  }
-
-  Out* out = (Out*)g.partial + ((int64_t)split * g.ntiles + tile) * (TILE * TILE);
+  Piece st[NG];
+  auto load = [&](int64_t x, int64_t o) {
 #pragma unroll
-  for (int j = 0; j < M::NACC; ++j) {
-    int row, col;
-    M::coord(j, lane, row, col);
-    out[(wr + row) * TILE + wc + col] = M::get(f, j);
+    for (int i = 0; i < NG; ++i) {
+      if (gn[i] <= 0) continue;
+      if (GATHER && !gom[i]) load_gather<E>(st[i], X, rbyte[i], koff, x, nk);
+      else load_rows<E>(st[i], p[i], gom[i] ? o : x);
+    }
+  };
+  // K tile kt: slab a from b0 on (GATHER: g.nbt values of a from a on).  The
+  // last tile of a slab (of the mode) is moved back to end with it, its values
+  // that the tile before holds zeroed.  GATHER: the up to B - 1 sketch values
+  // past nk are read (at the very end of Omega^T from the workspace behind it)
+  // and zeroed.
+  int64_t a, b0 = 0;
+  if (GATHER) {
+    a = kt0 * g.nbt;
+  } else {
+    a = kt0 / g.nbt;
+    b0 = (kt0 - a * g.nbt) * O::KT;
   }
+  auto tile_now = [&]() {
+    KTile k;
+    const int64_t at = GATHER ? a : b0, end = GATHER ? g.A - g.nbt : g.B - O::KT;
+    const int64_t from = at < end ? at : end;
+    k.lo = (int)(at - from) * (GATHER ? (int)g.B : 1);
+    k.hi = nk;
+    k.x = GATHER ? from * g.I * g.B : a * g.I * g.B + from;
+    k.o = GATHER ? from * g.B : a * g.B + from;
+    return k;
+  };
+  auto advance = [&]() {
+    if (GATHER) {
+      a += g.nbt;
+    } else {
+      b0 += O::KT;
+      if (b0 >= g.B) {
+        b0 = 0;
+        ++a;
+      }
+    }
+  };
+
+  typename O::Acc acc[NACC];
+#pragma unroll
+  for (int i = 0; i < NACC; ++i)
+#pragma unroll
+    for (int v = 0; v < (E == E_F64 ? 4 : 16); ++v) acc[i][v] = 0;
+
+  KTile now = {};
+  if (kt0 < kt1) {
+    now = tile_now();
+    load(now.x, now.o);
+  }
+  for (int64_t kt = kt0; kt < kt1; ++kt) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      if (gn[i] <= 0) continue;
+      if (GATHER && !gom[i]) store_piece<E, true>(st[i], lds, plane, i * GROUP, now);
+      else store_piece<E, false>(st[i], lds, plane, i * GROUP, now);
+    }
+    __syncthreads();
+    if (kt + 1 < kt1) {
+      advance();
+      now = tile_now();
+      load(now.x, now.o);
+    }
+    if (mask) tile_step<E, MB>(acc, lds, plane, lane, ra, rb, mask);
+    __syncthreads();
+  }
+
+  // the wanted blocks, [block][32][32]: C's lower triangle of blocks, then W^T
+  const int nb = (I + BLK - 1) / BLK;
+  Out* part = (Out*)g.partial + (int64_t)split * g.blocks * (BLK * BLK);
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      if (!((mask >> (2 * m + n)) & 1)) continue;
+      const int bi = row0 / BLK + m, bj = col0 / BLK + n;
+      Out* out = part + (int64_t)(is_w ? nb * (nb + 1) / 2 + bi * nb + bj : bi * (bi + 1) / 2 + bj) * (BLK * BLK);
+      if constexpr (E == E_F64) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            out[((i >> 1) * 16 + 4 * v + (lane >> 4)) * BLK + (i & 1) * 16 + (lane & 15)] =
+                acc[4 * (2 * m + (i >> 1)) + 2 * n + (i & 1)][v];
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          out[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * BLK + (lane & 31)] =
+              E == E_F32 ? acc[2 * m + n][v] + acc[(2 * MB + 2 * m + n) % NACC][v] : acc[2 * m + n][v];
+      }
+    }
 }
 
 // Sum the split-K partials in a fixed order: C (I x I, both triangles) and
-// W^T (S x I), float64.
+// W^T (S x I), float64.  64 consecutive values of a block per workgroup, the
+// splits dealt to 16 groups of lanes whose sums are added in order, so that a
+// few thousand outputs (a thin mode with hundreds of splits) still fill the
+// chip.
+constexpr int RED_GROUPS = 16;
 template <class Out>
-__global__ void gram_reduce_kernel(GramArgs g, double* C, double* Wt) {
-  const int64_t nC = g.I * g.I;
-  const int64_t total = nC + (int64_t)g.S * g.I;
-  const int64_t stride = (int64_t)TILE * TILE * g.ntiles;
-  const Out* P = (const Out*)g.partial;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    int64_t tile, idx;
-    if (e < nC) {
-      int64_t i = e / g.I, j = e - i * g.I;
-      int64_t ti = i / TILE, tj = j / TILE;
-      if (ti >= tj) {
-        tile = ti * (ti + 1) / 2 + tj;
-        idx = (i - ti * TILE) * TILE + (j - tj * TILE);
-      } else {
-        tile = tj * (tj + 1) / 2 + ti;
-        idx = (j - tj * TILE) * TILE + (i - ti * TILE);
-      }
-    } else if (g.thin) {
-      int64_t f = e - nC;
-      int64_t s = f / g.I, i = f - s * g.I;
-      tile = 0;
-      idx = (64 + s) * TILE + i;
-    } else {
-      int64_t f = e - nC;
-      int64_t s = f / g.I, i = f - s * g.I;
-      int64_t ti = i / TILE, sj = s / TILE;
-      tile = g.ntri + ti * g.nw + sj;
-      idx = (i - ti * TILE) * TILE + (s - sj * TILE);
-    }
-    double acc = 0.0;
-    for (int sp = 0; sp < g.splits; ++sp) acc += (double)P[sp * stride + tile * (TILE * TILE) + idx];
-    if (e < nC) C[e] = acc;
-    else Wt[e - nC] = acc;
+__global__ void __launch_bounds__(64 * RED_GROUPS) gram_reduce_kernel(GramArgs g, double* C, double* Wt) {
+  __shared__ double sums[RED_GROUPS][64];
+  const int l = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + l;
+  const Out* P = (const Out*)g.partial + e;
+  const int64_t stride = (int64_t)g.blocks * (BLK * BLK);
+  double acc = 0.0;
+#pragma unroll 4
+  for (int sp = grp; sp < g.splits; sp += RED_GROUPS) acc += (double)P[sp * stride];
+  sums[grp][l] = acc;
+  __syncthreads();
+  if (grp) return;
+#pragma unroll
+  for (int i = 1; i < RED_GROUPS; ++i) acc += sums[i][l];
+  const int blk = (int)(e / (BLK * BLK)), at = (int)(e % (BLK * BLK));
+  const int nb = (int)ceil_div(g.I, BLK), ntri = nb * (nb + 1) / 2;
+  int bi, bj;
+  if (blk < ntri) tri_at(blk, bi, bj);
+  else {
+    bi = (blk - ntri) / nb;
+    bj = (blk - ntri) % nb;
+  }
+  const int64_t i = bi * BLK + at / BLK, j = bj * BLK + at % BLK;
+  if (blk >= ntri) {
+    if (i < g.S && j < g.I) Wt[i * g.I + j] = acc;
+  } else if (i < g.I && j <= i) {
+    C[i * g.I + j] = acc;
+    C[j * g.I + i] = acc;
   }
 }
 
 // Omega^T (S x J) in the element type of the product.
-template <class T>
-__device__ inline T from_double(double v);
-template <> __device__ inline double from_double<double>(double v) { return v; }
-template <> __device__ inline float from_double<float>(double v) { return (float)v; }
-
 template <int E>
 __global__ void omega_kernel(uint64_t seed, uint32_t mode, int64_t total, void* out) {
   const int64_t npairs = (total + 1) / 2;
@@ -503,85 +572,95 @@ __global__ void philox_kernel(const uint32_t* ctr, int64_t count, uint64_t seed,
 
 // ------------------------------------------------------------------ planning
 
-int gram_bk(int elem) {
-  switch (elem) {
-    case E_F64: return Mma<E_F64>::BK;
-    case E_F32: return Mma<E_F32>::BK;
-    default: return Mma<E_BF16>::BK;       // the 128-tile kernel has no fp8 form
-  }
-}
-
 int elem_size(int elem) { return elem == E_F64 ? 8 : elem == E_F32 ? 4 : elem == E_BF16 ? 2 : 1; }
 
-GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count) {
+static int gram_kt(int elem) { return elem == E_F64 ? Op<E_F64>::KT : elem == E_F32 ? Op<E_F32>::KT : Op<E_BF16>::KT; }
+
+// The most bytes that the partials may take: two slices per compute unit of
+// 128 x 128 tiles of the rows and the sketch, each of at least 8 K tiles.
+static size_t partial_limit(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count) {
+  const int64_t nt = ceil_div(I, 128);
+  const bool thin = elem == E_F32 && I <= 64 && S >= 1 && S <= 64;
+  const int64_t tiles = thin ? 1 : nt * (nt + 1) / 2 + nt * ceil_div(S, 128);
+  const int kt = gram_kt(elem);
+  const int64_t nkt = B > 1 ? A * ceil_div(B, kt) : ceil_div(A, kt);
+  int64_t splits = std::min(std::max<int64_t>(ceil_div(2 * (int64_t)cu_count, tiles), 1), std::max<int64_t>(nkt / 8, 1));
+  if (splits >= 8) splits = (splits + 7) / 8 * 8;
+  splits = std::min(splits, std::max<int64_t>(nkt, 1));
+  return (size_t)(splits * tiles) * 128 * 128 * (elem == E_F64 ? 8 : 4);
+}
+
+GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch) {
   GramArgs g = {};
   g.A = A;
   g.I = I;
   g.B = B;
   g.J = A * B;
   g.S = S;
-  g.nt = (int)ceil_div(I, TILE);
-  g.ntri = g.nt * (g.nt + 1) / 2;
-  g.nw = S > 0 ? (int)ceil_div(S, TILE) : 0;
-  g.ntiles = g.ntri + g.nt * g.nw;
-  g.thin = (elem == E_F32 && I <= 64 && S >= 1 && S <= 64) ? 1 : 0;
-  if (g.thin) {
-    g.nw = 0;
-    g.ntiles = 1;
+  g.thin = I <= GROUP && S <= GROUP;
+  g.nt = (int)ceil_div(I, 128);
+  g.ntri = g.thin ? 1 : g.nt * (g.nt + 1) / 2;
+  g.nw = (int)ceil_div(I, 256);
+  g.ntiles = g.thin ? 1 : g.ntri + (int)ceil_div(S, GROUP) * g.nw;
+  const int nb = (int)ceil_div(I, BLK);
+  g.blocks = nb * (nb + 1) / 2 + (int)ceil_div(S, BLK) * nb;
+  const int kt = gram_kt(elem);
+  g.gather = B < kt;
+  g.nbt = g.gather ? std::min(kt / B, A) : ceil_div(B, kt);
+  g.nkt = g.gather ? ceil_div(A, g.nbt) : A * g.nbt;
+  // Splits: a compute unit's share of the workgroups, two at a time (one alone
+  // leaves the matrix cores idle between its loads and its products: taken as
+  // 1.6 of the time of each of two), times a workgroup's K tiles plus about 6
+  // of prologue and epilogue, plus the partials' traffic in K tiles (about
+  // 7.5 MB pass in the 1.5 us of one).  The thin form, bound by its loads, is
+  // four workgroups to a compute unit.
+  const double per = (double)g.blocks * BLK * BLK * (elem == E_F64 ? 16 : 8);
+  const size_t limit = partial_limit(elem, A, I, B, S_scratch < 0 ? S : S_scratch, cu_count);
+  double best = -1.0;
+  g.splits = 1;
+  for (int64_t s = 1; s <= std::min<int64_t>(g.nkt, 8 * (int64_t)cu_count); ++s) {
+    if (s > 1 && (size_t)s * g.blocks * BLK * BLK * (elem == E_F64 ? 8 : 4) > limit) break;
+    const int64_t n = ceil_div(g.ntiles * s, cu_count);
+    const double share = g.thin ? 4.0 * (double)ceil_div(n, 4) : (double)n + (n & 1 ? 0.6 : 0.0);
+    const double cost = share * ((double)ceil_div(g.nkt, s) + 6.0) + per * s / 7.5e6;
+    if (best < 0 || cost < best) {
+      best = cost;
+      g.splits = (int)s;
+    }
   }
-  const int bk = gram_bk(elem);
-  if (B > 1) {
-    g.nbt = ceil_div(B, bk);
-    g.nkt = A * g.nbt;
-  } else {
-    g.nbt = 0;
-    g.nkt = ceil_div(A, bk);
-  }
-  // split-K: aim for >= 2 workgroups per CU, keep >= 8 K tiles per split
-  const int64_t want = ceil_div(2 * (int64_t)cu_count, g.ntiles);
-  int64_t splits = want < 1 ? 1 : want;
-  const int64_t max_by_k = g.nkt / 8 > 0 ? g.nkt / 8 : 1;
-  if (splits > max_by_k) splits = max_by_k;
-  if (splits >= 8) splits = (splits + 7) / 8 * 8;
-  if (splits > g.nkt) splits = g.nkt > 0 ? g.nkt : 1;
-  g.splits = (int)splits;
-  g.xcd_map = (g.splits % 8 == 0) ? 1 : 0;
-  const int es = elem_size(elem);
-  g.vec_ok = ((B > 1 ? B : I) * es) % 16 == 0 && (g.J * es) % 16 == 0 ? 1 : 0;
   return g;
 }
 
 size_t gram_partial_bytes(const GramArgs& g, int elem) {
-  return (size_t)g.splits * g.ntiles * TILE * TILE * (elem == E_F64 ? 8 : 4);
+  return (size_t)g.splits * g.blocks * BLK * BLK * (elem == E_F64 ? 8 : 4);
 }
 
-// Vector loads need every row start 16-byte aligned: sizes (vec_ok) and base pointers.
-static bool gram_vec(const GramArgs& g) {
-  return g.vec_ok && ((uintptr_t)g.X % 16) == 0 && ((uintptr_t)g.omegaT % 16) == 0;
-}
-
-template <int E>
-static void launch_sketch(const GramArgs& g, unsigned grid, hipStream_t s) {
-  if (gram_vec(g)) hipLaunchKernelGGL((gram_sketch_kernel<E, true>), dim3(grid), dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gram_sketch_kernel<E, false>), dim3(grid), dim3(256), 0, s, g);
-}
-
-hipError_t launch_gram_main(int elem, const GramArgs& g, hipStream_t s) {
-  const unsigned grid = (unsigned)(g.ntiles * g.splits);
-  switch (elem) {
-    case E_F64: launch_sketch<E_F64>(g, grid, s); break;
-    case E_F32: launch_sketch<E_F32>(g, grid, s); break;
-    case E_BF16: launch_sketch<E_BF16>(g, grid, s); break;
-    default: return hipErrorInvalidValue;
-  }
+template <int E, bool GATHER, int NG>
+static hipError_t launch_tiles(const GramArgs& g, hipStream_t s) {
+  hipLaunchKernelGGL((gram_tile_kernel<E, GATHER, NG>), dim3((unsigned)(g.ntiles * g.splits)), dim3(256),
+                     NG * Op<E>::GROUP_BYTES, s, g);
   return hipGetLastError();
 }
 
+template <int E>
+static hipError_t launch_gram(const GramArgs& g, hipStream_t s) {
+  if (g.thin) return g.gather ? launch_tiles<E, true, GROUPS_THIN>(g, s) : launch_tiles<E, false, GROUPS_THIN>(g, s);
+  return g.gather ? launch_tiles<E, true, GROUPS_TILE>(g, s) : launch_tiles<E, false, GROUPS_TILE>(g, s);
+}
+
+hipError_t launch_gram_main(int elem, const GramArgs& g, hipStream_t s) {
+  switch (elem) {
+    case E_F64: return launch_gram<E_F64>(g, s);
+    case E_F32: return launch_gram<E_F32>(g, s);
+    case E_BF16: return launch_gram<E_BF16>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_gram_reduce(int elem, const GramArgs& g, double* C, double* Wt, hipStream_t s) {
-  const int64_t total = g.I * g.I + (int64_t)g.S * g.I;
-  unsigned rgrid = (unsigned)std::min<int64_t>(ceil_div(total, 256), 4096);
-  if (elem == E_F64) hipLaunchKernelGGL(gram_reduce_kernel<double>, dim3(rgrid), dim3(256), 0, s, g, C, Wt);
-  else hipLaunchKernelGGL(gram_reduce_kernel<float>, dim3(rgrid), dim3(256), 0, s, g, C, Wt);
+  const dim3 grid((unsigned)(g.blocks * (BLK * BLK / 64)));
+  if (elem == E_F64) hipLaunchKernelGGL(gram_reduce_kernel<double>, grid, dim3(64 * RED_GROUPS), 0, s, g, C, Wt);
+  else hipLaunchKernelGGL(gram_reduce_kernel<float>, grid, dim3(64 * RED_GROUPS), 0, s, g, C, Wt);
   return hipGetLastError();
 }
 

@@ -15,10 +15,11 @@ struct GramArgs {
   int S;
   int nt, ntri, nw, ntiles;
   int64_t nkt, nbt;
-  int splits, xcd_map, vec_ok;
+  int splits, xcd_map;
+  int blocks, gather;         // gram.hip: stored 32 x 32 blocks per split, K tiles of nbt values of a
   int xbase, xleft, grid;    // pipelined XCD map: whole splits per XCD, spare slots per XCD, workgroups
-  int thin;                 // float32, I <= 64, S <= 64: one 128 x 64 tile [C; W^T] (gram.hip)
-  void* partial;            // [splits][ntiles][128*128] float (double for fp64)
+  int thin;                 // I <= 64, S <= 64: one tile of the mode's and the sketch's rows (gram.hip)
+  void* partial;            // [splits][blocks][32*32] float (double for fp64), gram.hip
   int64_t part_stride;      // elements per split (pipelined bf16 form)
   int64_t wpart_off;        // pipelined form: offset of the sketch partials within a split
   // fp8 block-exponent geometry (blocks of 32 per dimension)
@@ -28,8 +29,8 @@ struct GramArgs {
 };
 
 int elem_size(int elem);
-int gram_bk(int elem);
-GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count);
+// S_scratch (default S): the sketch width whose partials bound this plan's.
+GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch = -1);
 size_t gram_partial_bytes(const GramArgs& g, int elem);
 hipError_t launch_gram_main(int elem, const GramArgs& g, hipStream_t s);
 hipError_t launch_gram_reduce(int elem, const GramArgs& g, double* C, double* Wt, hipStream_t s);
