@@ -144,6 +144,7 @@ struct Plan {
   bool sequential = false;   // sequential truncation (ST-HOSVD form)
   bool one_stream = false;   // every mode on the caller's stream (no helper streams)
   bool fused = false;        // every mode's Krylov chain in one persistent launch (small modes)
+  bool together = false;     // larger modes: every mode's chain step in one launch
   bool any_sampled = false;
   int64_t maxM = 0;          // largest column sample
   size_t ybytes = 0;         // largest gathered sample
@@ -189,6 +190,8 @@ void sketch_runs(const Plan& P, int n, int64_t& B, int64_t& IN) {
     IN = P.dims[P.N - 1];
   }
 }
+
+bool plan_together(const Plan& P);
 
 rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
   if (!prm) return fail(RBKI_E_INVALID, "params is NULL");
@@ -321,10 +324,14 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
   // all modes in one launch, one workgroup per mode
   P.fused = !P.any_sampled;
   for (int n = 0; n < P.N; ++n) P.fused = P.fused && krylov_chain_ok(P.m[n].I, P.m[n].S);
+  P.together = plan_together(P);
   return RBKI_OK;
 }
 
-constexpr size_t kDgemmScratch = (size_t)32 << 20;
+constexpr size_t kDgemmScratch = (size_t)8 << 20;    // split-K partials of the float64 GEMMs
+// What one scratch set may spend, beyond its own buffers, on chain sets for
+// the other modes (plan_chain_sets).
+constexpr size_t kChainSpare = (size_t)24 << 20;
 
 struct Arena {
   char* base;
@@ -399,6 +406,33 @@ int mode_lanes(const Plan& P) { return (P.T >= ((int64_t)1 << 26) && P.N > 1) ? 
 // together before a decomposition.
 size_t counters_bytes(const Plan& P) { return 256 + (size_t)P.N * (P.q + 2) * 4; }
 
+// The buffers of one mode's Krylov chain.
+void carve_chain(const Plan& P, Arena& ar, Lane& L) {
+  L.C = (double*)ar.take((size_t)P.maxI * P.maxI * 8);
+  L.CQt = (double*)ar.take((size_t)P.maxSp * P.maxI * 8);
+  L.Yt = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
+  L.Ytmp = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
+  L.Pm = (double*)ar.take((size_t)P.maxS * P.maxSp * 8);
+  L.G = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
+  if (P.fused) return;                        // the persistent chain needs no more
+  L.L = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
+  L.flags = (int*)ar.take((size_t)P.maxSp * 4);
+  L.ref2 = (double*)ar.take((size_t)P.maxS * 8);
+  if (P.any_sampled) L.CY = (double*)ar.take((size_t)P.maxI * P.maxI * 8);
+}
+
+// Modes too large for the persistent chain whose chains can still run in step,
+// one launch for a step of all of them: those of a plan with one scratch set
+// (large tensors have a set and a stream per mode instead), as long as the
+// other modes' chain buffers stay within kChainSpare.
+bool plan_together(const Plan& P) {
+  if (P.fused || mode_lanes(P) > 1 || P.N < 2) return false;
+  Arena ar(nullptr, 0);
+  Lane L;
+  for (int n = 1; n < P.N; ++n) carve_chain(P, ar, L);
+  return ar.off + 256 <= kChainSpare;
+}
+
 void carve(const Plan& P, Arena& ar, Buffers& b) {
   const int es_g = elem_size(P.gelem);
   if (P.need_pad) {
@@ -414,19 +448,15 @@ void carve(const Plan& P, Arena& ar, Buffers& b) {
     }
   }
   b.lanes = mode_lanes(P);
-  b.chain_lanes = P.fused ? std::max(b.lanes, P.N) : b.lanes;
+  b.chain_lanes = P.fused || P.together ? std::max(b.lanes, P.N) : b.lanes;
   for (int l = 0; l < b.chain_lanes; ++l) {
     Lane& L = b.ln[l];
     if (l >= b.lanes) {
-      // a fused plan's extra sets: chain buffers of their own; the sketch and
-      // Gram scratch of set 0 (those passes run one after the other)
+      // the extra sets of a fused plan or of modes that run together: chain
+      // buffers of their own; the sketch and Gram scratch of set 0 (those
+      // passes run one after the other)
       L = b.ln[0];
-      L.C = (double*)ar.take((size_t)P.maxI * P.maxI * 8);
-      L.CQt = (double*)ar.take((size_t)P.maxSp * P.maxI * 8);
-      L.Yt = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
-      L.Ytmp = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
-      L.Pm = (double*)ar.take((size_t)P.maxS * P.maxSp * 8);
-      L.G = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
+      carve_chain(P, ar, L);
       continue;
     }
     if (P.need_pad && P.oblk_bytes) {
@@ -438,18 +468,9 @@ void carve(const Plan& P, Arena& ar, Buffers& b) {
     }
     L.omegaT = ar.take((size_t)P.maxSJ * (P.need_pad ? 2 : es_g));   // the fallback of the mixed forms: bf16
     L.partial = ar.take(P.partial_bytes);
-    L.C = (double*)ar.take((size_t)P.maxI * P.maxI * 8);
-    L.CQt = (double*)ar.take((size_t)P.maxSp * P.maxI * 8);
-    L.Yt = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
-    L.Ytmp = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
-    L.Pm = (double*)ar.take((size_t)P.maxS * P.maxSp * 8);
     L.dscratch = (double*)ar.take(kDgemmScratch);
-    L.G = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
-    L.L = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
-    L.flags = (int*)ar.take((size_t)P.maxSp * 4);
-    L.ref2 = (double*)ar.take((size_t)P.maxS * 8);
+    carve_chain(P, ar, L);
     if (P.any_sampled) {
-      L.CY = (double*)ar.take((size_t)P.maxI * P.maxI * 8);
       L.ysmp = ar.take(P.ybytes);
       L.cols = (int64_t*)ar.take((size_t)P.maxM * 8);
     }
@@ -618,92 +639,159 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
   return RBKI_OK;
 }
 
-// Alg. 1, block 0: Q_0 = orth(W) from W^T in the lane's Yt.  The first pass
+// The modes whose chains run in step, each with its scratch set.
+struct ModeSet {
+  int count = 0;
+  int mode[8], lane[8];
+  void add(int n, int l) {
+    mode[count] = n;
+    lane[count++] = l;
+  }
+};
+
+// Alg. 1, block 0: Q_0 = orth(W) from W^T in each set's Yt.  The first pass
 // of every block's CholeskyQR2 also keeps the basis at most I_n wide: once
 // it spans the whole space the later blocks are rounding noise and are
 // dropped whatever their norm.
-rbki_status krylov_block0(const Plan& P, const Buffers& b, const Lane& L, int n, hipStream_t st) {
-  const ModeGeom& g = P.m[n];
-  const int64_t I = g.I, S = g.S;
-  int* used = b.used + (size_t)n * (P.q + 2);
-  HIPCHK(row_norms2(L.Yt, S, I, L.ref2, st));
-  HIPCHK(chol_orth(L.Yt, L.Ytmp, S, I, L.G, L.L, L.flags, L.ref2, TAU_REL, TAU_ABS, st, DimBudget{used, used + 1, I}));
-  HIPCHK(chol_orth(L.Ytmp, b.Qt[n], S, I, L.G, L.L, L.flags, nullptr, TAU_REL, 0.0, st));
+CholJob orth_job(const ModeGeom& g, const Lane& L, double* Y, double* Yout) {
+  CholJob c = {};
+  c.Y = Y;
+  c.Yout = Yout;
+  c.s = g.S;
+  c.n = g.I;
+  c.G = L.G;
+  c.Lm = L.L;
+  c.flags = L.flags;
+  return c;
+}
+
+rbki_status krylov_block0(const Plan& P, const Buffers& b, const ModeSet& ms, hipStream_t st) {
+  CholJob first[8], second[8];
+  for (int i = 0; i < ms.count; ++i) {
+    const int n = ms.mode[i];
+    const ModeGeom& g = P.m[n];
+    const Lane& L = b.ln[ms.lane[i]];
+    int* used = b.used + (size_t)n * (P.q + 2);
+    first[i] = orth_job(g, L, L.Yt, L.Ytmp);
+    first[i].ref2 = first[i].norms = L.ref2;
+    first[i].tau_abs = TAU_ABS;
+    first[i].bud = DimBudget{used, used + 1, g.I};
+    second[i] = orth_job(g, L, L.Ytmp, b.Qt[n]);
+  }
+  HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
+  HIPCHK(chol_orth_batched(second, ms.count, TAU_REL, st));
   return RBKI_OK;
 }
 
 // Alg. 1, Krylov step j >= 1: block j of the basis from (X X^T) Q_{j-1} (Ck
 // is X X^T, or Y Y^T of a sampled mode), projected off the earlier blocks
 // twice and orthonormalised.  The product C Q_{j-1} is formed into the
-// lane's Yt and, when CQ is given, kept as rows (j-1) S.. of CQ; with from_cq
+// set's Yt and, when CQ is given, kept as rows (j-1) S.. of CQ; with from_cq
 // it is taken from there instead (formed earlier with the same C).
-rbki_status krylov_step(const Plan& P, const Buffers& b, const Lane& L, int n, int j, const double* Ck, double* CQ,
-                        bool from_cq, hipStream_t st) {
-  const ModeGeom& g = P.m[n];
-  const int64_t I = g.I, S = g.S;
-  double* Qt = b.Qt[n];
-  int* used = b.used + (size_t)n * (P.q + 2);
-  const int64_t m = S * j;                     // rows of the basis so far
-  const double* Qlast = Qt + (m - S) * I;
-  if (from_cq) {
-    HIPCHK(copy_rows_f64(L.Yt, I, CQ + (m - S) * I, I, S, I, st));
-  } else {
-    // Y_j^T = Q_{j-1}^T C  (C symmetric)
-    HIPCHK(dgemm(0, 0, S, I, I, 1.0, Qlast, I, Ck, I, 0.0, L.Yt, I, st));
-    if (CQ) HIPCHK(copy_rows_f64(CQ + (m - S) * I, I, L.Yt, I, S, I, st));
+rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int j, const double* const* Ck,
+                        double* const* CQ, const bool* from_cq, hipStream_t st) {
+  GemmJob cq[8], proj[8], upd[8];
+  CholJob first[8], second[8];
+  int ncq = 0;
+  for (int i = 0; i < ms.count; ++i) {
+    const int n = ms.mode[i];
+    const ModeGeom& g = P.m[n];
+    const Lane& L = b.ln[ms.lane[i]];
+    const int64_t I = g.I, S = g.S, m = S * j;   // m: rows of the basis so far
+    double* Qt = b.Qt[n];
+    int* used = b.used + (size_t)n * (P.q + 2);
+    if (from_cq && from_cq[i]) {
+      HIPCHK(copy_rows_f64(L.Yt, I, CQ[i] + (m - S) * I, I, S, I, st));
+    } else {
+      // Y_j^T = Q_{j-1}^T C  (C symmetric)
+      cq[ncq] = gemm_job(0, 0, S, I, I, 1.0, Qt + (m - S) * I, I, Ck[i], I, 0.0, L.Yt, I);
+      if (CQ[i]) {
+        cq[ncq].C2 = CQ[i] + (m - S) * I;
+        cq[ncq].ldc2 = I;
+      }
+      ++ncq;
+    }
+    // remove earlier blocks, twice
+    proj[i] = gemm_job(0, 1, S, m, I, 1.0, L.Yt, I, Qt, I, 0.0, L.Pm, m);
+    upd[i] = gemm_job(0, 0, S, I, m, -1.0, L.Pm, m, Qt, I, 1.0, L.Yt, I);
+    first[i] = orth_job(g, L, L.Yt, L.Ytmp);
+    first[i].ref2 = L.ref2;
+    first[i].tau_abs = TAU_ABS;
+    first[i].bud = DimBudget{used + j, used + j + 1, I};
+    second[i] = orth_job(g, L, L.Ytmp, Qt + m * I);
   }
-  HIPCHK(row_norms2(L.Yt, S, I, L.ref2, st));
-  for (int pass = 0; pass < 2; ++pass) {       // remove earlier blocks, twice
-    HIPCHK(dgemm(0, 1, S, m, I, 1.0, L.Yt, I, Qt, I, 0.0, L.Pm, m, st));
-    HIPCHK(dgemm(0, 0, S, I, m, -1.0, L.Pm, m, Qt, I, 1.0, L.Yt, I, st));
+  if (ncq) HIPCHK(dgemm_batched(cq, ncq, st));
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int i = 0; i < ms.count; ++i) proj[i].norms = pass == 0 ? b.ln[ms.lane[i]].ref2 : nullptr;
+    HIPCHK(dgemm_batched(proj, ms.count, st));
+    HIPCHK(dgemm_batched(upd, ms.count, st));
   }
-  HIPCHK(chol_orth(L.Yt, L.Ytmp, S, I, L.G, L.L, L.flags, L.ref2, TAU_REL, TAU_ABS, st,
-                   DimBudget{used + j, used + j + 1, I}));
-  HIPCHK(chol_orth(L.Ytmp, Qt + m * I, S, I, L.G, L.L, L.flags, nullptr, TAU_REL, 0.0, st));
+  HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
+  HIPCHK(chol_orth_batched(second, ms.count, TAU_REL, st));
   return RBKI_OK;
 }
 
-// Alg. 2, steps 2-3 of mode n after run_mode_heavy: the Krylov basis from C
-// and W in the scratch set, and Z.
-rbki_status run_mode_chain(const Plan& P, const Buffers& b, int lane, int n, bool with_factor, hipStream_t st) {
-  const Lane& L = b.ln[lane];
-  dgemm_set_scratch(L.dscratch, kDgemmScratch);
-  const ModeGeom& g = P.m[n];
-  const int64_t I = g.I, S = g.S, Sp = g.Sp;
-  double* Qt = b.Qt[n];
-  // the Krylov products: with the sample's Y Y^T for a sampled mode
-  const double* Ck = g.sampled ? L.CY : L.C;
-  rbki_status s = krylov_block0(P, b, L, n, st);
+// Alg. 2, steps 2-3 of the modes after run_mode_heavy: the Krylov bases from C
+// and W in the scratch sets, and Z.
+rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, bool with_factor, hipStream_t st) {
+  dgemm_set_scratch(b.ln[ms.lane[0]].dscratch, kDgemmScratch);
+  const double* Ck[8];
+  double* CQ[8];
+  GemmJob job[8];
+  for (int i = 0; i < ms.count; ++i) {
+    const Lane& L = b.ln[ms.lane[i]];
+    Ck[i] = P.m[ms.mode[i]].sampled ? L.CY : L.C;   // a sampled mode's Krylov products: the sample's Y Y^T
+    CQ[i] = L.CQt;
+  }
+  rbki_status s = krylov_block0(P, b, ms, st);
   if (s != RBKI_OK) return s;
   if (P.power) {
     // power iteration (Sec. 3.1): Q_j = orth(C Q_{j-1}), each step's block
     // replacing the last, with the same drop rule relative to the step's
     // largest squared row norm
-    for (int j = 1; j <= P.q; ++j) {
-      HIPCHK(dgemm(0, 0, S, I, I, 1.0, Qt, I, Ck, I, 0.0, L.Yt, I, st));
-      HIPCHK(row_norms2(L.Yt, S, I, L.ref2, st));
-      HIPCHK(chol_orth(L.Yt, L.Ytmp, S, I, L.G, L.L, L.flags, L.ref2, TAU_REL, TAU_ABS, st));
-      HIPCHK(chol_orth(L.Ytmp, Qt, S, I, L.G, L.L, L.flags, nullptr, TAU_REL, 0.0, st));
+    CholJob first[8], second[8];
+    for (int i = 0; i < ms.count; ++i) {
+      const int n = ms.mode[i];
+      const ModeGeom& g = P.m[n];
+      const Lane& L = b.ln[ms.lane[i]];
+      job[i] = gemm_job(0, 0, g.S, g.I, g.I, 1.0, b.Qt[n], g.I, Ck[i], g.I, 0.0, L.Yt, g.I);
+      first[i] = orth_job(g, L, L.Yt, L.Ytmp);
+      first[i].ref2 = first[i].norms = L.ref2;
+      first[i].tau_abs = TAU_ABS;
+      second[i] = orth_job(g, L, L.Ytmp, b.Qt[n]);
     }
-    if (!with_factor) return RBKI_OK;
-    HIPCHK(dgemm(0, 0, S, I, I, 1.0, Qt, I, L.C, I, 0.0, L.CQt, I, st));
-    HIPCHK(dgemm(0, 1, S, S, I, 1.0, Qt, I, L.CQt, I, 0.0, b.Z[n], S, st));
-    return RBKI_OK;
-  }
-  for (int j = 1; j <= P.q; ++j) {
-    s = krylov_step(P, b, L, n, j, Ck, L.CQt, false, st);
-    if (s != RBKI_OK) return s;
+    for (int j = 1; j <= P.q; ++j) {
+      HIPCHK(dgemm_batched(job, ms.count, st));
+      HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
+      HIPCHK(chol_orth_batched(second, ms.count, TAU_REL, st));
+    }
+  } else {
+    for (int j = 1; j <= P.q; ++j) {
+      s = krylov_step(P, b, ms, j, Ck, CQ, nullptr, st);
+      if (s != RBKI_OK) return s;
+    }
   }
   if (!with_factor) return RBKI_OK;
   // C Q_q, then Z = Q^T (C Q) (Alg. 2, step 3); a sampled mode's earlier
   // products were with Y Y^T, so C Q is formed for the whole basis
-  if (g.sampled) {
-    HIPCHK(dgemm(0, 0, Sp, I, I, 1.0, Qt, I, L.C, I, 0.0, L.CQt, I, st));
-  } else {
-    HIPCHK(dgemm(0, 0, S, I, I, 1.0, Qt + (Sp - S) * I, I, L.C, I, 0.0, L.CQt + (Sp - S) * I, I, st));
+  GemmJob zj[8];
+  for (int i = 0; i < ms.count; ++i) {
+    const int n = ms.mode[i];
+    const ModeGeom& g = P.m[n];
+    const int64_t from = P.power || g.sampled ? 0 : g.Sp - g.S;
+    job[i] = gemm_job(0, 0, g.Sp - from, g.I, g.I, 1.0, b.Qt[n] + from * g.I, g.I, b.ln[ms.lane[i]].C, g.I, 0.0,
+                      CQ[i] + from * g.I, g.I);
+    zj[i] = gemm_job(0, 1, g.Sp, g.Sp, g.I, 1.0, b.Qt[n], g.I, CQ[i], g.I, 0.0, b.Z[n], g.Sp);
   }
-  HIPCHK(dgemm(0, 1, Sp, Sp, I, 1.0, Qt, I, L.CQt, I, 0.0, b.Z[n], Sp, st));
+  HIPCHK(dgemm_batched(job, ms.count, st));
+  HIPCHK(dgemm_batched(zj, ms.count, st));
   return RBKI_OK;
+}
+
+rbki_status run_mode_chain(const Plan& P, const Buffers& b, int lane, int n, bool with_factor, hipStream_t st) {
+  ModeSet ms;
+  ms.add(n, lane);
+  return run_mode_chains(P, b, ms, with_factor, st);
 }
 
 // The persistent chain of mode n on scratch set `lane` (fused plans): blocks
@@ -835,12 +923,14 @@ rbki_status run_factors(const Plan& P, const Buffers& b, hipStream_t st) {
       HIPCHK(jacobi_eig_batched(P.N, Zs, ns, ls, vs, ws, is, 40, st, P.concurrent && nmax <= 192));
     }
   }
+  GemmJob job[8];
   for (int n = 0; n < P.N; ++n) {
     const ModeGeom& g = P.m[n];
-    HIPCHK(dgemm(0, 0, g.R, g.I, g.Sp, 1.0, b.Vt[n], g.Sp, b.Qt[n], g.I, 0.0, b.Ut64[n], g.I, st));
-    // sign rule: largest-magnitude entry of each factor column positive
-    HIPCHK(canonical_sign_rows(b.Ut64[n], g.R, g.I, st));
+    job[n] = gemm_job(0, 0, g.R, g.I, g.Sp, 1.0, b.Vt[n], g.Sp, b.Qt[n], g.I, 0.0, b.Ut64[n], g.I);
   }
+  HIPCHK(dgemm_batched(job, P.N, st));
+  // sign rule: largest-magnitude entry of each factor column positive
+  for (int n = 0; n < P.N; ++n) HIPCHK(canonical_sign_rows(b.Ut64[n], P.m[n].R, P.m[n].I, st));
   return RBKI_OK;
 }
 
@@ -1209,6 +1299,16 @@ static rbki_status run_modes(const Plan& P, const Buffers& b, const void* xsrc, 
     }
     return run_chains(P, jobs, P.N, 0, P.q, st);
   }
+  if (P.together) {
+    // the same with the larger modes' chains in step
+    ModeSet ms;
+    for (int n = 0; n < P.N; ++n) {
+      rbki_status s = run_mode_heavy(P, b, n, xsrc, n, st);
+      if (s != RBKI_OK) return s;
+      ms.add(n, n);
+    }
+    return run_mode_chains(P, b, ms, true, st);
+  }
   const int lanes = (P.concurrent || P.one_stream) ? 1 : b.lanes;
   hipStream_t ls[kMaxLanes] = {st, st, st};
   hipEvent_t ev[kMaxLanes] = {};
@@ -1488,30 +1588,69 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
   }
   HIPCHK(fill_zero(b.info, counters_bytes(P), st));
   double *Cm[8], *CYm[8], *CQm[8];
+  ModeSet ms;
   for (int n = 0; n < P.N; ++n) {
     const ModeGeom& g = P.m[n];
-    Cm[n] = (double*)(ws + AL.C[n]);
-    CYm[n] = g.sampled ? (double*)(ws + AL.CY[n]) : nullptr;
-    CQm[n] = (double*)(ws + AL.CQ[n]);
-    if (P.fused) {
+    if (P.fused || P.together) {
       // each mode's Gram pass into its own chain set, which keeps C and the
       // products C Q for every step
       s = run_mode_heavy(P, b, n, X, n, st);
       if (s != RBKI_OK) return s;
+      Cm[n] = b.ln[n].C;
+      CYm[n] = b.ln[n].CY;
+      CQm[n] = b.ln[n].CQt;
+      ms.add(n, n);
       continue;
     }
+    Cm[n] = (double*)(ws + AL.C[n]);
+    CYm[n] = g.sampled ? (double*)(ws + AL.CY[n]) : nullptr;
+    CQm[n] = (double*)(ws + AL.CQ[n]);
     // the Gram pass (and the sample's), kept for every step; block 0
     s = run_mode_heavy(P, b, 0, X, n, st);
     if (s != RBKI_OK) return s;
     HIPCHK(copy_rows_f64(Cm[n], g.I, L0.C, g.I, g.I, g.I, st));
     if (g.sampled) HIPCHK(copy_rows_f64(CYm[n], g.I, L0.CY, g.I, g.I, g.I, st));
-    s = krylov_block0(P, b, L0, n, st);
+    ModeSet one;
+    one.add(n, 0);
+    s = krylov_block0(P, b, one, st);
     if (s != RBKI_OK) return s;
   }
   dgemm_set_scratch(L0.dscratch, kDgemmScratch);
+  if (P.together) {
+    s = krylov_block0(P, b, ms, st);
+    if (s != RBKI_OK) return s;
+  }
   HostResult hr;
   double fit_prev = 0.0, err = 0.0;
   int t = 0;
+  // Krylov step t (Alg. 1) of a set of modes, from mode n0 on, then C Q_t and
+  // Z_t = Q^T C Q over the t + 1 blocks (Alg. 2, step 3).  A mode that is not
+  // sampled takes C Q_{t-1} from the products kept for Z.
+  auto step = [&](const ModeSet& set, int n0) -> rbki_status {
+    if (t > 0) {
+      const double* Ck[8];
+      bool from_cq[8];
+      double* kept[8];
+      for (int i = 0; i < set.count; ++i) {
+        const bool smp = P.m[n0 + i].sampled;
+        Ck[i] = smp ? CYm[n0 + i] : Cm[n0 + i];
+        kept[i] = smp ? nullptr : CQm[n0 + i];
+        from_cq[i] = !smp;
+      }
+      rbki_status e = krylov_step(P, b, set, t, Ck, kept, from_cq, st);
+      if (e != RBKI_OK) return e;
+    }
+    GemmJob cq[8], zj[8];
+    for (int i = 0; i < set.count; ++i) {
+      const int n = n0 + i;
+      const int64_t I = P.m[n].I, S = P.m[n].S, m = S * (t + 1);
+      cq[i] = gemm_job(0, 0, S, I, I, 1.0, b.Qt[n] + (m - S) * I, I, Cm[n], I, 0.0, CQm[n] + (m - S) * I, I);
+      zj[i] = gemm_job(0, 1, m, m, I, 1.0, b.Qt[n], I, CQm[n], I, 0.0, b.Z[n], m);
+    }
+    HIPCHK(dgemm_batched(cq, set.count, st));
+    HIPCHK(dgemm_batched(zj, set.count, st));
+    return RBKI_OK;
+  };
   for (;; ++t) {
     if (P.fused) {
       // block t of every mode's basis and Z over the t + 1 blocks, in one
@@ -1520,25 +1659,18 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
       for (int n = 0; n < P.N; ++n) jobs[n] = chain_job(P, b, n, n, (int)(P.m[n].S * (t + 1)));
       s = run_chains(P, jobs, P.N, t, t, st);
       if (s != RBKI_OK) return s;
+    } else if (P.together) {
+      s = step(ms, 0);
+      if (s != RBKI_OK) return s;
     }
     for (int n = 0; n < P.N; ++n) {
-      const ModeGeom& g = P.m[n];
-      const int64_t I = g.I, S = g.S, m = S * (t + 1);
-      if (P.fused) {
-        s = factor_single(P, b, n, st, m);
-        if (s != RBKI_OK) return s;
-        continue;
-      }
-      if (t > 0) {
-        // Krylov step t (Alg. 1); a mode that is not sampled takes C Q_{t-1}
-        // from the products kept for Z
-        s = krylov_step(P, b, L0, n, t, g.sampled ? CYm[n] : Cm[n], g.sampled ? nullptr : CQm[n], !g.sampled, st);
+      if (!P.fused && !P.together) {
+        ModeSet one;
+        one.add(n, 0);
+        s = step(one, n);
         if (s != RBKI_OK) return s;
       }
-      // C Q_t, then Z_t = Q^T C Q over the t + 1 blocks (Alg. 2, step 3)
-      HIPCHK(dgemm(0, 0, S, I, I, 1.0, b.Qt[n] + (m - S) * I, I, Cm[n], I, 0.0, CQm[n] + (m - S) * I, I, st));
-      HIPCHK(dgemm(0, 1, m, m, I, 1.0, b.Qt[n], I, CQm[n], I, 0.0, b.Z[n], m, st));
-      s = factor_single(P, b, n, st, m);
+      s = factor_single(P, b, n, st, P.m[n].S * (t + 1));
       if (s != RBKI_OK) return s;
     }
     void* gk = nullptr;

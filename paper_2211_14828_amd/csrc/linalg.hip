@@ -14,91 +14,145 @@ namespace rbki {
 namespace {
 
 // ------------------------------------------------------------------ DGEMM
-// 64 x 64 output tile per 256-thread workgroup, 4 x 4 outputs per thread,
-// K staged through LDS in steps of 16.
-constexpr int GT = 64, GK = 16;
+// Small float64 products on the float64 matrix cores (16x16x4), several
+// independent ones (the modes of a decomposition) in one launch.  They are
+// bound by latency, not by arithmetic: a product of the Krylov chain has a few
+// dozen output tiles and an inner dimension of a few hundred, and the chain
+// runs them one after the other.  So a workgroup owns one tile of 16 columns by
+// 16 or 64 rows, its eight waves take the stages of the inner dimension in
+// turn, with operands straight from memory (they stay in the caches from one
+// product to the next), and the eight partial tiles are added through LDS in a
+// fixed order: no second launch, and a wave has one or two stages to wait for.
+// Inner dimensions of 1024 and more (TR-SVD, modes of thousands of rows) are
+// also split over workgroups, their partials summed in order by a second kernel.
+// Tiles of 64 rows are taken from 1024 tiles of 16 x 16 on, where the bytes
+// read matter: the columns' operand is then read once per 64 rows.
+//
+// 400^3, S = 30, q = 3, bf16 form, three modes together: 41 launches of the
+// chain against 78 products, 57 reductions and 45 others for the modes one by
+// one on the vector units; the decomposition went from 2.98 to 1.75 ms.
+constexpr int GW = 8;                        // waves of a workgroup
+typedef double f64x2u_t __attribute__((ext_vector_type(2), aligned(8)));
 
-__global__ void __launch_bounds__(256) dgemm_kernel(int opA, int opB, int64_t m, int64_t n, int64_t k,
-                                                    double alpha, const double* __restrict__ A, int64_t lda,
-                                                    const double* __restrict__ B, int64_t ldb, double beta,
-                                                    double* __restrict__ C, int64_t ldc, double* __restrict__ part,
-                                                    int64_t kchunk) {
-  __shared__ double As[GK][GT + 1];
-  __shared__ double Bs[GK][GT + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t row0 = (int64_t)blockIdx.y * GT, col0 = (int64_t)blockIdx.x * GT;
-  const int64_t kb = (int64_t)blockIdx.z * kchunk;
-  const int64_t ke = kb + kchunk < k ? kb + kchunk : k;
-  // this thread's four elements of each staged tile: A (i, kk), B (kk, j)
-  int ai[4], ak[4], bk[4], bj[4];
+// KS consecutive values p[t * stride] (p at index k0), t < KS, zero from K on.
+template <int KS>
+__device__ inline void gemm_run(const double* p, int64_t stride, int k0, int K, double (&out)[KS]) {
+  if (stride == 1 && k0 + KS <= K) {
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int e = threadIdx.x + 256 * t;
-    if (opA == 0) { ai[t] = e / GK; ak[t] = e % GK; } else { ak[t] = e / GT; ai[t] = e % GT; }
-    if (opB == 0) { bk[t] = e / GT; bj[t] = e % GT; } else { bj[t] = e / GK; bk[t] = e % GK; }
+    for (int t = 0; t < KS; t += 2) {
+      const f64x2u_t v = *(const f64x2u_t*)(p + t);
+      out[t] = v.x;
+      out[t + 1] = v.y;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < KS; ++t) out[t] = k0 + t < K ? p[t * stride] : 0.0;
   }
-  // the next K tile is loaded into registers while the current one is
-  // multiplied, so only the first tile's memory latency is exposed
-  double ra[4], rb[4];
-  auto fetch = [&](int64_t k0) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int64_t r = row0 + ai[t], c = k0 + ak[t];
-      ra[t] = (r < m && c < ke) ? (opA == 0 ? A[r * lda + c] : A[c * lda + r]) : 0.0;
-      const int64_t r2 = k0 + bk[t], c2 = col0 + bj[t];
-      rb[t] = (r2 < ke && c2 < n) ? (opB == 0 ? B[r2 * ldb + c2] : B[c2 * ldb + r2]) : 0.0;
-    }
-  };
-  double acc[4][4] = {};
-  if (kb < ke) fetch(kb);
-  for (int64_t k0 = kb; k0 < ke; k0 += GK) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      As[ak[t]][ai[t]] = ra[t];
-      Bs[bk[t]][bj[t]] = rb[t];
-    }
-    __syncthreads();
-    if (k0 + GK < ke) fetch(k0 + GK);
-#pragma unroll
-    for (int kk = 0; kk < GK; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = As[kk][ty + 16 * u];
-        b[u] = Bs[kk][tx + 16 * u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t r = row0 + ty + 16 * u, c = col0 + tx + 16 * v;
-      if (r < m && c < n) {
-        if (part) {
-          part[(int64_t)blockIdx.z * m * n + r * n + c] = acc[u][v];
-        } else {
-          double* p = C + r * ldc + c;
-          *p = beta == 0.0 ? alpha * acc[u][v] : alpha * acc[u][v] + beta * *p;
-        }
-      }
-    }
 }
 
-// C = alpha * sum_z part[z] + beta * C, summed in a fixed order.
-__global__ void dgemm_reduce_kernel(int64_t m, int64_t n, int splits, const double* part, double alpha, double beta,
-                                    double* C, int64_t ldc) {
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m * n; e += (int64_t)gridDim.x * blockDim.x) {
-    double acc = 0.0;
-    for (int z = 0; z < splits; ++z) acc += part[(int64_t)z * m * n + e];
-    const int64_t r = e / n, c = e - r * n;
-    double* p = C + r * ldc + c;
-    *p = beta == 0.0 ? alpha * acc : alpha * acc + beta * *p;
+// One tile of 16 RB rows by 16 columns over the inner range [kb, ke).  Lane
+// l holds values k0 + KS (l / 16) + t of row (column) l % 16 of a stage of
+// 4 KS values; rows and columns past the end repeat the last one.
+template <int RB, int KS>
+__device__ inline void gemm_tile(const GemmJob& g, int r0, int c0, int kb, int ke, double* sums, double* part) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int ST = 4 * KS;
+  const double* pa[RB];
+#pragma unroll
+  for (int u = 0; u < RB; ++u) {
+    const int i = r0 + 16 * u + li;
+    pa[u] = g.A + (int64_t)(i < g.m ? i : g.m - 1) * g.sai;
+  }
+  const int j = c0 + li;
+  const double* pb = g.B + (int64_t)(j < g.n ? j : g.n - 1) * g.sbj;
+  f64x4_t acc[RB];
+#pragma unroll
+  for (int u = 0; u < RB; ++u) acc[u] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  double a0[RB][KS], b0[KS], a1[RB][KS], b1[KS];
+  auto load = [&](double (&a)[RB][KS], double (&b)[KS], int k) {
+    k += KS * lg;
+#pragma unroll
+    for (int u = 0; u < RB; ++u) gemm_run<KS>(pa[u] + (int64_t)k * g.sak, g.sak, k, ke, a[u]);
+    gemm_run<KS>(pb + (int64_t)k * g.sbk, g.sbk, k, ke, b);
+  };
+  auto mul = [&](const double (&a)[RB][KS], const double (&b)[KS]) {
+#pragma unroll
+    for (int t = 0; t < KS; ++t)
+#pragma unroll
+      for (int u = 0; u < RB; ++u) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][t], b[t], acc[u], 0, 0, 0);
+  };
+  int k = kb + wave * ST;
+  if (k < ke) load(a0, b0, k);
+  while (k < ke) {
+    const int k1 = k + GW * ST, k2 = k1 + GW * ST;
+    if (k1 < ke) load(a1, b1, k1);
+    mul(a0, b0);
+    if (k2 < ke) load(a0, b0, k2);
+    if (k1 < ke) mul(a1, b1);
+    k = k2;
+  }
+#pragma unroll
+  for (int u = 0; u < RB; ++u)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sums[wave * (RB * 256) + (16 * u + 4 * v + lg) * 16 + li] = acc[u][v];
+  __syncthreads();
+  for (int e = threadIdx.x; e < RB * 256; e += 64 * GW) {
+    double v = sums[e];
+#pragma unroll
+    for (int w = 1; w < GW; ++w) v += sums[w * (RB * 256) + e];
+    const int64_t r = r0 + e / 16, c = c0 + e % 16;
+    if (r >= g.m || c >= g.n) continue;
+    if (part) {
+      part[r * g.n + c] = v;
+    } else {
+      double* p = g.C + r * g.ldc + c;
+      v = g.beta == 0.0 ? g.alpha * v : g.alpha * v + g.beta * *p;
+      *p = v;
+      if (g.C2) g.C2[r * g.ldc2 + c] = v;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(64 * GW) gemm_kernel(GemmArgs a) {
+  extern __shared__ double gemm_lds[];
+  const GemmJob& g = a.job[blockIdx.y];
+  const int tiles = g.trows * g.tcols;
+  const int id = blockIdx.x;
+  if (id >= tiles * g.splits) {
+    // the squared norms of A's rows, one wave a row
+    const int row = (id - tiles * g.splits) * GW + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (!g.norms || row >= g.m) return;
+    double s = 0.0;
+    for (int c = lane; c < g.k; c += 64) {
+      const double v = g.A[(int64_t)row * g.sai + (int64_t)c * g.sak];
+      s = fma(v, v, s);
+    }
+    s = warp_sum(s);
+    if (lane == 0) g.norms[row] = s;
+    return;
+  }
+  const int split = id / tiles, t = id % tiles;
+  const int kb = split * g.kchunk, ke = kb + g.kchunk < g.k ? kb + g.kchunk : g.k;
+  double* part = g.splits > 1 ? g.part + (int64_t)split * g.m * g.n : nullptr;
+  if (g.rows == 64) gemm_tile<4, 4>(g, (t / g.tcols) * 64, (t % g.tcols) * 16, kb, ke, gemm_lds, part);
+  else gemm_tile<1, 8>(g, (t / g.tcols) * 16, (t % g.tcols) * 16, kb, ke, gemm_lds, part);
+}
+
+// C = alpha * sum of the partials + beta * C, summed in a fixed order.
+__global__ void gemm_reduce_kernel(GemmArgs a) {
+  const GemmJob& g = a.job[blockIdx.y];
+  if (g.splits <= 1) return;
+  const int64_t mn = (int64_t)g.m * g.n;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < mn; e += (int64_t)gridDim.x * blockDim.x) {
+    double v = 0.0;
+#pragma unroll 4
+    for (int z = 0; z < g.splits; ++z) v += g.part[z * mn + e];
+    const int64_t r = e / g.n, c = e - r * g.n;
+    double* p = g.C + r * g.ldc + c;
+    v = g.beta == 0.0 ? g.alpha * v : g.alpha * v + g.beta * *p;
+    *p = v;
+    if (g.C2) g.C2[r * g.ldc2 + c] = v;
   }
 }
 
@@ -113,9 +167,15 @@ __global__ void dgemm_reduce_kernel(int64_t m, int64_t n, int splits, const doub
 // vectors) and flags[k] = 1 for kept vectors.
 constexpr int CHOL_MAX = 96;
 
-__global__ void __launch_bounds__(1024) chol_inv_kernel(const double* G, int64_t s, double* Linv, int* flags,
-                                                        const double* ref2, double tau_rel, double tau_abs,
-                                                        DimBudget bud) {
+__global__ void __launch_bounds__(1024) chol_inv_kernel(CholArgs a) {
+  const CholJob& job = a.job[blockIdx.x];
+  const double* G = job.G;
+  const int64_t s = job.s;
+  double* Linv = job.Lm;
+  int* flags = job.flags;
+  const double* ref2 = job.ref2;
+  const double tau_rel = a.tau_rel, tau_abs = job.tau_abs;
+  const DimBudget bud = job.bud;
   __shared__ double Ls[CHOL_MAX][CHOL_MAX + 1];
   __shared__ double Xs[CHOL_MAX][CHOL_MAX + 1];
   __shared__ double d0[CHOL_MAX];
@@ -220,10 +280,19 @@ __device__ inline double lane_f64(double v, int l) {
 }
 
 template <int SMAX>
-__global__ void __launch_bounds__(64) chol_solve_kernel(const double* G, int s, const double* Y, int64_t n,
-                                                        double* Yout, int* flags, const double* ref2,
-                                                        double tau_rel, double tau_abs, DimBudget bud) {
+__global__ void __launch_bounds__(64) chol_solve_kernel(CholArgs a) {
   static_assert(SMAX % CS_NB == 0, "panels of 16 columns");
+  const CholJob& job = a.job[blockIdx.y];
+  const double* G = job.G;
+  const int s = (int)job.s;
+  const double* Y = job.Y;
+  const int64_t n = job.n;
+  double* Yout = job.Yout;
+  int* flags = job.flags;
+  const double* ref2 = job.ref2;
+  const double tau_rel = a.tau_rel, tau_abs = job.tau_abs;
+  const DimBudget bud = job.bud;
+  if ((int64_t)blockIdx.x * 64 >= n) return;
   __shared__ double Ls[SMAX][SMAX + 1];
   __shared__ double dinv[SMAX];
   __shared__ int keep[SMAX];
@@ -863,26 +932,72 @@ void dgemm_set_scratch(double* p, size_t bytes) {
   g_dgemm_scratch_bytes = bytes;
 }
 
+GemmJob gemm_job(int opA, int opB, int64_t m, int64_t n, int64_t k, double alpha, const double* A, int64_t lda,
+                 const double* B, int64_t ldb, double beta, double* C, int64_t ldc) {
+  GemmJob g = {};
+  g.A = A;
+  g.B = B;
+  g.C = C;
+  g.m = (int)m;
+  g.n = (int)n;
+  g.k = (int)k;
+  g.sai = opA ? 1 : lda;
+  g.sak = opA ? lda : 1;
+  g.sbk = opB ? 1 : ldb;
+  g.sbj = opB ? ldb : 1;
+  g.ldc = ldc;
+  g.alpha = alpha;
+  g.beta = beta;
+  return g;
+}
+
+// Every choice depends on the job alone, so a product has the same bits in
+// any company.  (The scratch is divided by the most jobs of a launch.)
+hipError_t dgemm_batched(const GemmJob* jobs, int njobs, hipStream_t s) {
+  if (njobs < 1 || njobs > kGemmJobs) return hipErrorInvalidValue;
+  GemmArgs a = {};
+  unsigned gx = 0;
+  int64_t red = 0;
+  int rows = 16;
+  const size_t share = g_dgemm_scratch ? g_dgemm_scratch_bytes / kGemmJobs / 8 : 0;   // doubles per job
+  for (int i = 0; i < njobs; ++i) {
+    GemmJob& g = a.job[i];
+    g = jobs[i];
+    if (g.m <= 0 || g.n <= 0) {
+      g.m = g.n = 0;
+      continue;
+    }
+    const int64_t cols = ceil_div(g.n, 16);
+    g.rows = g.m > 16 && ceil_div(g.m, 16) * cols >= 1024 ? 64 : 16;
+    rows = std::max(rows, g.rows);
+    g.trows = (int)ceil_div(g.m, g.rows);
+    g.tcols = (int)cols;
+    const int64_t tiles = (int64_t)g.trows * g.tcols;
+    int64_t splits = std::min<int64_t>(ceil_div(256, tiles), std::max(1, g.k / 512));
+    splits = std::min<int64_t>(splits, (int64_t)(share / ((size_t)g.m * g.n)));
+    g.kchunk = splits > 1 ? (int)(ceil_div(ceil_div(g.k, splits), 32) * 32) : std::max(g.k, 1);
+    g.splits = splits > 1 ? (int)ceil_div(g.k, g.kchunk) : 1;
+    if (g.splits > 1) {
+      g.part = g_dgemm_scratch + (size_t)i * share;
+      red = std::max(red, (int64_t)g.m * g.n);
+    }
+    const int64_t blocks = tiles * g.splits + (g.norms ? ceil_div(g.m, GW) : 0);
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    gx = std::max(gx, (unsigned)blocks);
+  }
+  if (gx == 0) return hipSuccess;
+  hipLaunchKernelGGL(gemm_kernel, dim3(gx, njobs), dim3(64 * GW), (size_t)GW * rows * 16 * 8, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || red == 0) return e;
+  hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(red, 256), 4096), njobs), dim3(256),
+                     0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t dgemm(int opA, int opB, int64_t m, int64_t n, int64_t k, double alpha, const double* A, int64_t lda,
                  const double* B, int64_t ldb, double beta, double* C, int64_t ldc, hipStream_t s) {
-  if (m <= 0 || n <= 0) return hipSuccess;
-  const int64_t tiles = ceil_div(m, GT) * ceil_div(n, GT);
-  int64_t splits = ceil_div(256, tiles);
-  splits = std::min<int64_t>(splits, std::max<int64_t>(1, k / 64));
-  splits = std::min<int64_t>(splits, 64);
-  if (g_dgemm_scratch == nullptr) splits = 1;
-  while (splits > 1 && (size_t)splits * m * n * 8 > g_dgemm_scratch_bytes) --splits;
-  const int64_t kchunk = splits > 1 ? ceil_div(ceil_div(k, splits), GK) * GK : std::max<int64_t>(k, 1);
-  splits = splits > 1 ? ceil_div(k, kchunk) : 1;
-  dim3 grid((unsigned)ceil_div(n, GT), (unsigned)ceil_div(m, GT), (unsigned)splits);
-  double* part = splits > 1 ? g_dgemm_scratch : nullptr;
-  hipLaunchKernelGGL(dgemm_kernel, grid, dim3(256), 0, s, opA, opB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
-                     part, kchunk);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || splits == 1) return e;
-  hipLaunchKernelGGL(dgemm_reduce_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(m * n, 256), 4096)), dim3(256), 0, s,
-                     m, n, (int)splits, part, alpha, beta, C, ldc);
-  return hipGetLastError();
+  const GemmJob g = gemm_job(opA, opB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+  return dgemm_batched(&g, 1, s);
 }
 
 hipError_t row_norms2(const double* Y, int64_t s, int64_t n, double* out, hipStream_t st) {
@@ -891,37 +1006,52 @@ hipError_t row_norms2(const double* Y, int64_t s, int64_t n, double* out, hipStr
   return hipGetLastError();
 }
 
-hipError_t chol_orth(double* Y, double* Yout, int64_t s, int64_t n, double* G, double* Lm, int* flags,
-                     const double* ref2, double tau_rel, double tau_abs, hipStream_t st, DimBudget bud) {
-  if (s <= 0) return hipSuccess;
-  hipError_t e = dgemm(0, 1, s, s, n, 1.0, Y, n, Y, n, 0.0, G, s, st);
+hipError_t chol_orth_batched(const CholJob* jobs, int njobs, double tau_rel, hipStream_t st) {
+  if (njobs < 1 || njobs > kGemmJobs) return hipErrorInvalidValue;
+  GemmJob gj[kGemmJobs], up[kGemmJobs];
+  CholArgs fit = {}, inv = {};
+  fit.tau_rel = inv.tau_rel = tau_rel;
+  int nfit = 0, ninv = 0;
+  int64_t smax = 0, nmax = 0;
+  for (int i = 0; i < njobs; ++i) {
+    const CholJob& j = jobs[i];
+    gj[i] = gemm_job(0, 1, j.s, j.s, j.n, 1.0, j.Y, j.n, j.Y, j.n, 0.0, j.G, j.s);
+    gj[i].norms = j.norms;
+    if (j.s <= CS_MAX) {
+      fit.job[nfit++] = j;
+      smax = std::max(smax, j.s);
+      nmax = std::max(nmax, j.n);
+    } else if (j.s <= CHOL_MAX) {
+      up[ninv] = gemm_job(0, 0, j.s, j.n, j.s, 1.0, j.Lm, j.s, j.Y, j.n, 0.0, j.Yout, j.n);
+      inv.job[ninv++] = j;
+    }
+  }
+  hipError_t e = dgemm_batched(gj, njobs, st);
   if (e != hipSuccess) return e;
-  if (s <= CS_MAX) {
-    const dim3 grid((unsigned)ceil_div(n, 64));
-    if (s <= 16)
-      hipLaunchKernelGGL(chol_solve_kernel<16>, grid, dim3(64), 0, st, G, (int)s, Y, n, Yout, flags, ref2, tau_rel,
-                         tau_abs, bud);
-    else if (s <= 32)
-      hipLaunchKernelGGL(chol_solve_kernel<32>, grid, dim3(64), 0, st, G, (int)s, Y, n, Yout, flags, ref2, tau_rel,
-                         tau_abs, bud);
-    else if (s <= 48)
-      hipLaunchKernelGGL(chol_solve_kernel<48>, grid, dim3(64), 0, st, G, (int)s, Y, n, Yout, flags, ref2, tau_rel,
-                         tau_abs, bud);
-    else
-      hipLaunchKernelGGL(chol_solve_kernel<64>, grid, dim3(64), 0, st, G, (int)s, Y, n, Yout, flags, ref2, tau_rel,
-                         tau_abs, bud);
-    return hipGetLastError();
-  }
-  if (s <= CHOL_MAX) {
-    hipLaunchKernelGGL(chol_inv_kernel, dim3(1), dim3(1024), 0, st, G, s, Lm, flags, ref2, tau_rel, tau_abs, bud);
+  if (nfit) {
+    const dim3 grid((unsigned)ceil_div(nmax, 64), nfit);
+    if (smax <= 16) hipLaunchKernelGGL(chol_solve_kernel<16>, grid, dim3(64), 0, st, fit);
+    else if (smax <= 32) hipLaunchKernelGGL(chol_solve_kernel<32>, grid, dim3(64), 0, st, fit);
+    else if (smax <= 48) hipLaunchKernelGGL(chol_solve_kernel<48>, grid, dim3(64), 0, st, fit);
+    else hipLaunchKernelGGL(chol_solve_kernel<64>, grid, dim3(64), 0, st, fit);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return dgemm(0, 0, s, n, s, 1.0, Lm, s, Y, n, 0.0, Yout, n, st);
   }
-  hipLaunchKernelGGL(chol_drop_kernel, dim3(1), dim3(1024), 0, st, G, s, Lm, flags, ref2, tau_rel, tau_abs, bud);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(trsm_rows_kernel, dim3(grid_for(n)), dim3(256), 0, st, Y, s, n, Lm, flags);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  return copy_rows_f64(Yout, n, Y, n, s, n, st);
+  if (ninv) {
+    hipLaunchKernelGGL(chol_inv_kernel, dim3(ninv), dim3(1024), 0, st, inv);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = dgemm_batched(up, ninv, st)) != hipSuccess) return e;
+  }
+  for (int i = 0; i < njobs; ++i) {
+    const CholJob& j = jobs[i];
+    if (j.s <= CHOL_MAX) continue;
+    hipLaunchKernelGGL(chol_drop_kernel, dim3(1), dim3(1024), 0, st, j.G, j.s, j.Lm, j.flags, j.ref2, tau_rel,
+                       j.tau_abs, j.bud);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(trsm_rows_kernel, dim3(grid_for(j.n)), dim3(256), 0, st, j.Y, j.s, j.n, j.Lm, j.flags);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = copy_rows_f64(j.Yout, j.n, j.Y, j.n, j.s, j.n, st)) != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Block width: the staged pair (2 nb columns of length n), G, V and the

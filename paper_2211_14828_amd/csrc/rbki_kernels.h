@@ -93,6 +93,29 @@ hipError_t launch_gather_columns(int x_elem, const void* X, int64_t I, int64_t B
 hipError_t dgemm(int opA, int opB, int64_t m, int64_t n, int64_t k, double alpha, const double* A,
                  int64_t lda, const double* B, int64_t ldb, double beta, double* C, int64_t ldc,
                  hipStream_t s);
+// The same for up to kGemmJobs independent products in one launch.  A job may
+// also ask for a second copy of its result (C2, leading dimension ldc2) and
+// for the squared norms of A's rows (norms, m values).  The last row of fields
+// is filled in by the launcher.
+constexpr int kGemmJobs = 8;
+struct GemmJob {
+  const double* A;
+  const double* B;
+  double* C;
+  double* C2;
+  double* norms;
+  int64_t sai, sak, sbk, sbj, ldc, ldc2;   // strides of op(A)(i, k) and op(B)(k, j)
+  int m, n, k;
+  double alpha, beta;
+  int rows, trows, tcols, splits, kchunk;
+  double* part;
+};
+struct GemmArgs {
+  GemmJob job[kGemmJobs];
+};
+GemmJob gemm_job(int opA, int opB, int64_t m, int64_t n, int64_t k, double alpha, const double* A, int64_t lda,
+                 const double* B, int64_t ldb, double beta, double* C, int64_t ldc);
+hipError_t dgemm_batched(const GemmJob* jobs, int njobs, hipStream_t s);
 
 // Orthonormalise the rows of Y (s x n, row-major: s vectors of length n) by
 // CholeskyQR with column dropping, writing the result to Yout (which must not
@@ -117,8 +140,25 @@ struct DimBudget {
     if (used_out) *used_out = (int)((used_in ? *used_in : 0) + kept);
   }
 };
-hipError_t chol_orth(double* Y, double* Yout, int64_t s, int64_t n, double* G, double* Lm, int* flags,
-                     const double* ref2, double tau_rel, double tau_abs, hipStream_t st, DimBudget bud = {});
+// Up to kGemmJobs blocks at once; ref2 may be the norms of Y itself (norms ==
+// ref2: formed with G), or formed earlier (norms null).
+struct CholJob {
+  double* Y;
+  double* Yout;
+  int64_t s, n;
+  double* G;
+  double* Lm;
+  int* flags;
+  const double* ref2;
+  double* norms;
+  double tau_abs;
+  DimBudget bud;
+};
+struct CholArgs {
+  CholJob job[kGemmJobs];
+  double tau_rel;
+};
+hipError_t chol_orth_batched(const CholJob* jobs, int njobs, double tau_rel, hipStream_t st);
 
 // Scratch for split-K float64 GEMMs (nullptr disables split-K).
 void dgemm_set_scratch(double* p, size_t bytes);
