@@ -250,33 +250,8 @@ __global__ void sum_pairs_kernel(const double* partial, int64_t n, double* out) 
 }
 
 // ------------------------------------------------------------------------
-// Streaming reconstruction-error pass for R <= 64.  Workgroup w owns columns
-// j0 .. j0+127 of X_(0) (I x J) and walks every 128-row tile of it: H(:,
-// j0..j0+127) is staged once in LDS as [j][k], the rows of U (I x 64,
-// zero-padded) are read straight from L2 into MFMA fragments, and the tile of
-// X is requested before the MFMAs so that its HBM reads are in flight while
-// Xhat = U H is formed.  (x - xhat)^2 and x^2 are accumulated in float64;
-// Xhat is never written.  PE is the product type: float32 (32x32x2 MFMA) or,
-// for the precision forms, split bfloat16: each operand is hi + lo with both
-// parts bfloat16, and U H = Uh Hh + Uh Hl + Ul Hh on 32x32x16 MFMA with
-// float32 accumulation (relative error about 2^-16; a fifth of the
-// matrix-core time of the float32 form).
-struct ResArgs {
-  const void* Up;       // I x 64 row-major, columns >= R zero: float32, or split
-                        // bfloat16 (hi parts, then the I x 64 lo parts)
-  const float* H;       // R x J row-major
-  const void* X;        // I x J row-major
-  int64_t I, J;
-  int R, nkt;           // nkt = ceil(R / 32) K tiles of 32 (float32 products)
-  double* partial;      // [gridDim.x] x 2
-};
-
-template <class XT>
-__device__ inline float x_to_f(XT v);
-template <> __device__ inline float x_to_f<float>(float v) { return v; }
-template <> __device__ inline float x_to_f<bf16_t>(bf16_t v) { return bf16_to_f32(v); }
-
-// The split-bfloat16 form: each workgroup owns 64 columns j0.. of X_(0),
+// Streaming reconstruction-error pass of the precision forms, R <= 64, in split
+// bfloat16: each workgroup owns 64 columns j0.. of X_(0),
 // their H block split into bfloat16 hi + lo parts in LDS; wave w walks the
 // 16-row tiles w, w + 4, ... and forms Xhat (16 x 64) of a tile as four
 // 16 x 16 blocks on 16x16x32 bfloat16 MFMA, K = 64 in two steps, three
@@ -457,153 +432,350 @@ __global__ void __launch_bounds__(256, 2) residual_split_kernel(ResSplitArgs a) 
   }
 }
 
-template <class XT, int PE>
-__global__ void __launch_bounds__(256, PE == E_F32 ? 2 : 1) residual_kernel(ResArgs a) {
-  __shared__ __attribute__((aligned(16))) char ldsB[2][TILE * LDS_ROW];
-  __shared__ double red[2][4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, lr = lane & 31;
-  const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;
-  const int64_t j0 = (int64_t)blockIdx.x * TILE;
+// ------------------------------------------------------------------------
+// Streaming mode products, float32 and float64: one operand is the tensor (or
+// an intermediate), read once, the other a factor of at most a few hundred
+// kilobytes.  The product is bound by the bytes of the tensor for factors of up
+// to about 48 columns and by the matrix cores beyond, so a wave works alone,
+// without LDS or barriers: it reads 16-byte pieces of the tensor straight into
+// the operand layout of the 16x16x4 MFMA, two stages ahead, and the factor from
+// L1 / L2.  With V = 16 / sizeof(T) values to a piece:
+//
+//  middle modes (LAST false): Y[a] (R x B) = Ut (R x K) X[a] (K x B).  The 16
+//    lanes of a group take V consecutive columns each, so that the V column
+//    blocks of a wave are the V values of its pieces; lane group g of a stage
+//    of 4 V inner values reads rows k0 + V g + t, t < V.
+//  last mode (LAST true): Y (A x R) = X (A x K) Ut^T.  A wave takes V blocks of
+//    16 rows; lane group g reads values k0 + V g + t of its row.
+//
+// The factor's lane (row r, group g) holds Ut[r][k0 + V g + t], one piece, in
+// both.  A wave forms 16 NR rows of the output (NR chosen so that R splits
+// evenly over the waves that share a piece of the tensor).  Column pieces past
+// the end of a slab (rows past the end) repeat the last ones and store the same
+// values again; no load needs more than the element's alignment.
+//
+// Against tiles of 128 x 128 through LDS: 200^3 float64, R = 10, the core's and
+// the reconstruction's six products 63 us (284); 64^5 float32, R = 16, the first
+// product 0.96 ms (3.6; 4.5 TB/s) and the last expansion, 1.07 GB written, 0.28
+// ms (1.3); 1000^3 float32, R = 50, the first product 2.0 ms beside a Gram pass
+// (16 ms), the last expansion, 200 MB written, 0.10 ms (0.13).
+struct StreamArgs {
+  const void* X;
+  const void* Ut;        // R x K row-major
+  void* Y;
+  int64_t A, B;          // LAST: B unused
+  int K, R;
+  int chunks;            // output row groups of 16 NR
+  int64_t groups;        // column pieces of V (LAST: blocks of 16 V rows)
+  int64_t nbg;           // column pieces per slab
+};
 
-  // H block -> LDS, transposed: chunk c holds 4 consecutive j at one k.
-  // float32: [k / 32][j][k % 32]; bfloat16: [j][k] (64 k in one row)
+template <int E> struct Vec;
+template <> struct Vec<E_F32> {
+  typedef float T;
+  static constexpr int V = 4;
+  typedef float vec __attribute__((ext_vector_type(4), aligned(4)));
+  typedef f32x4_t Acc;
+  __device__ static inline Acc mma(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  __device__ static inline int row(int g, int v) { return 4 * g + v; }      // of result value v, lane group g
+};
+template <> struct Vec<E_F64> {
+  typedef double T;
+  static constexpr int V = 2;
+  typedef double vec __attribute__((ext_vector_type(2), aligned(8)));
+  typedef f64x4_t Acc;
+  __device__ static inline Acc mma(double a, double b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  __device__ static inline int row(int g, int v) { return 4 * v + g; }
+};
+
+// KS > 1: the KS waves of a workgroup split the inner dimension of one block
+// of 16 rows (LAST only) and add their tiles through LDS.
+template <int E, int NR, bool LAST, int KS>
+__global__ void __launch_bounds__(64 * (KS > 1 ? KS : 4)) stream_kernel(StreamArgs p) {
+  typedef Vec<E> W;
+  typedef typename W::T T;
+  typedef typename W::vec vec;
+  constexpr int V = W::V, ST = 4 * V;
+  constexpr int NX = KS > 1 ? 1 : V;                 // tensor pieces of a stage
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t unit = KS > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
+  const int64_t blk = unit / p.chunks;
+  const int r0 = (int)(unit - blk * p.chunks) * 16 * NR;
+  const T* X = (const T*)p.X;
+  const T* px[NX];                                   // piece n at inner value 0 (LAST) / this lane's columns
+  int64_t col = 0;                                   // first column of this lane in its slab's output
+  T* py[LAST ? NX : 1];
+  if constexpr (LAST) {
+    if (blk >= p.groups) return;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int c = tid + 256 * q;
-    const int kk = c >> 5, jj = (c & 31) * 4;
-    const bool ok = kk < a.R && j0 + jj < a.J;
-    const int kc = kk < a.R ? kk : 0;
-    const int64_t jc = j0 + jj < a.J ? j0 + jj : 0;
-    float4 v = *(const float4*)(a.H + (int64_t)kc * a.J + jc);
-    if (!ok) v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (PE == E_F32) {
-      char* base = ldsB[kk >> 5] + (kk & 31) * 4;
-      *(float*)(base + (jj + 0) * LDS_ROW) = v.x;
-      *(float*)(base + (jj + 1) * LDS_ROW) = v.y;
-      *(float*)(base + (jj + 2) * LDS_ROW) = v.z;
-      *(float*)(base + (jj + 3) * LDS_ROW) = v.w;
-    } else {
-      // hi parts in ldsB[0], lo parts in ldsB[1], [j][k] with 64 k per row
-      const float vv[4] = {v.x, v.y, v.z, v.w};
+    for (int n = 0; n < NX; ++n) {
+      const int64_t a = (blk * NX + n) * 16 + li, ac = a < p.A ? a : p.A - 1;
+      px[n] = X + ac * p.K;
+      py[n] = (T*)p.Y + ac * p.R;
+    }
+  } else {
+    if (blk * 16 >= p.groups) return;
+    const int64_t q = blk * 16 + li, qc = q < p.groups ? q : p.groups - 1;
+    const int64_t a = qc / p.nbg;
+    const int64_t b = (qc - a * p.nbg) * V;
+    col = b < p.B - V ? b : p.B - V;
+    px[0] = X + a * p.K * p.B + col;
+    py[0] = (T*)p.Y + a * p.R * p.B + col;
+  }
+  const T* pu[NR];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bf16_t hi = f32_to_bf16(vv[e]);
-        *(bf16_t*)(ldsB[0] + kk * 2 + (jj + e) * LDS_ROW) = hi;
-        *(bf16_t*)(ldsB[1] + kk * 2 + (jj + e) * LDS_ROW) = f32_to_bf16(vv[e] - bf16_to_f32(hi));
+  for (int u = 0; u < NR; ++u) {
+    const int r = r0 + 16 * u + li;
+    pu[u] = (const T*)p.Ut + (int64_t)(r < p.R ? r : p.R - 1) * p.K;
+  }
+  typename W::Acc acc[NR][NX];
+#pragma unroll
+  for (int u = 0; u < NR; ++u)
+#pragma unroll
+    for (int n = 0; n < NX; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[u][n][v] = 0;
+
+  struct Stage {
+    vec x[LAST ? NX : V];
+    vec u[NR];
+  };
+  auto load = [&](Stage& s, int k0) {
+    const int k = k0 + V * g;
+#pragma unroll
+    for (int i = 0; i < (LAST ? NX : V); ++i)
+      s.x[i] = LAST ? *(const vec*)(px[LAST ? i : 0] + k) : *(const vec*)(px[0] + (int64_t)(k + i) * p.B);
+#pragma unroll
+    for (int u = 0; u < NR; ++u) s.u[u] = *(const vec*)(pu[u] + k);
+  };
+  // the last, partial stage: values from K on are zeros of both operands
+  auto load_tail = [&](Stage& s, int k0) {
+    const int k = k0 + V * g;
+#pragma unroll
+    for (int i = 0; i < (LAST ? NX : V); ++i)
+#pragma unroll
+      for (int t = 0; t < V; ++t) {
+        if (LAST) s.x[i][t] = k + t < p.K ? px[LAST ? i : 0][k + t] : (T)0;
+        else s.x[i][t] = k + i < p.K ? px[0][(int64_t)(k + i) * p.B + t] : (T)0;
+      }
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+#pragma unroll
+      for (int t = 0; t < V; ++t) s.u[u][t] = k + t < p.K ? pu[u][k + t] : (T)0;
+  };
+  auto mul = [&](const Stage& s) {
+#pragma unroll
+    for (int t = 0; t < V; ++t)
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+#pragma unroll
+        for (int n = 0; n < NX; ++n) acc[u][n] = W::mma(s.u[u][t], LAST ? s.x[LAST ? n : 0][t] : s.x[t][n], acc[u][n]);
+  };
+  // whole stages, this wave's share (KS > 1: every KS-th)
+  const int ns = p.K / ST, first = KS > 1 ? wave : 0;
+  constexpr int step = KS > 1 ? KS : 1;
+  Stage s0, s1, s2;
+  auto at = [&](int s) { return (s < ns ? s : ns - 1) * ST; };
+  if (first < ns) {
+    load(s0, first * ST);
+    load(s1, at(first + step));
+    for (int s = first; s < ns; s += 3 * step) {
+      load(s2, at(s + 2 * step));
+      mul(s0);
+      if (s + step >= ns) break;
+      load(s0, at(s + 3 * step));
+      mul(s1);
+      if (s + 2 * step >= ns) break;
+      load(s1, at(s + 4 * step));
+      mul(s2);
+    }
+  }
+  if (ns * ST < p.K && (KS == 1 || wave == ns % KS)) {
+    load_tail(s0, ns * ST);
+    mul(s0);
+  }
+
+  if constexpr (KS > 1) {
+    __shared__ T sums[KS][NR * 256];
+#pragma unroll
+    for (int u = 0; u < NR; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sums[wave][(16 * u + W::row(g, v)) * 16 + li] = acc[u][0][v];
+    __syncthreads();
+    for (int e = threadIdx.x; e < NR * 256; e += 64 * KS) {
+      // consecutive threads take consecutive output columns of a row
+      const int i = e / (16 * NR), rr = e % (16 * NR);
+      T v = sums[0][rr * 16 + i];
+#pragma unroll
+      for (int w = 1; w < KS; ++w) v += sums[w][rr * 16 + i];
+      const int64_t a = blk * 16 + i;
+      if (a < p.A && r0 + rr < p.R) ((T*)p.Y)[a * p.R + r0 + rr] = v;
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+      if constexpr (LAST && E == E_F32) {
+        // a lane's four result values are consecutive columns
+        const int r = r0 + 16 * u + 4 * g;
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+          if (r + 4 <= p.R) {
+            *(vec*)(py[LAST ? n : 0] + r) = vec{acc[u][n][0], acc[u][n][1], acc[u][n][2], acc[u][n][3]};
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (r + v < p.R) py[LAST ? n : 0][r + v] = acc[u][n][v];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = r0 + 16 * u + W::row(g, v);
+          if (r >= p.R) continue;
+          if constexpr (LAST) {
+#pragma unroll
+            for (int n = 0; n < NX; ++n) py[n][r] = acc[u][n][v];
+          } else {
+            vec o;
+#pragma unroll
+            for (int n = 0; n < V; ++n) o[n] = acc[u][n][v];
+            *(vec*)(py[0] + (int64_t)r * p.B) = o;
+          }
+        }
       }
     }
   }
-  __syncthreads();
+}
 
-  const XT* X = (const XT*)a.X;
+// ------------------------------------------------------------------------
+// Reconstruction error in the operand types' own precision: sum (x - xhat)^2
+// and sum x^2 over X_(0) (I x J), Xhat = U H with R <= 128, on the same MFMA.
+// A wave owns 16 column pieces of V values; H's R x 16 V block stays in its
+// registers and the wave walks its share of the 16-row tiles: U's tile from L1 /
+// L2 (one value a lane and inner step, from Ut as it is), X's tile as 16-byte
+// pieces in the layout of the result, two tiles ahead.  No LDS and no barrier
+// until the sums.  x - xhat and both sums are float64; each of a lane's V
+// columns has its own sums, and those that a shifted last piece repeats are left
+// out at the end.
+// Against 128-row tiles: 1000^3 float32, R = 50, 1.40 ms (1.82; the float32
+// matrix cores need 0.75 of it, the float64 sums most of the rest); 64^5, R = 16,
+// 1.08 ms (2.95; 4.0 TB/s); 200^3 float64, R = 10, 16 us (81).
+struct ResidualArgs {
+  const void* X;        // I x J
+  const void* Ut;       // R x I
+  const void* H;        // R x J
+  int64_t I, J;
+  int R;
+  int64_t blocks;       // column blocks of 16 V
+  int rchunks;          // row ranges
+  double* partial;      // [gridDim.x] x 2
+};
+
+template <class XT, int V> struct XPiece;
+template <> struct XPiece<float, 4> { typedef float vec __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct XPiece<double, 2> { typedef double vec __attribute__((ext_vector_type(2), aligned(8))); };
+template <> struct XPiece<bf16_t, 4> { typedef unsigned short vec __attribute__((ext_vector_type(4), aligned(2))); };
+template <class XT> __device__ inline double x_value(XT v) {
+  if constexpr (sizeof(XT) == 2) return (double)bf16_to_f32(v);
+  else return (double)v;
+}
+
+template <class XT, int E, int NK>
+__global__ void __launch_bounds__(256, NK > 4 ? 1 : 2) residual_stream_kernel(ResidualArgs p) {
+  typedef Vec<E> W;
+  typedef typename W::T T;
+  constexpr int V = W::V;
+  typedef typename W::vec vec;
+  typedef typename XPiece<XT, V>::vec xvec;
+  __shared__ double red[2][4];
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t ntile = ceil_div(p.I, 16);
   double res = 0.0, nrm = 0.0;
-  const int64_t nit = ceil_div(a.I, TILE);
-  // a tile of X in the accumulator layout (rows clamped into the matrix)
-  auto load_x = [&](int64_t it, XT (&xv)[64]) {
-    const int64_t i0 = it * TILE;
+  for (int64_t unit = (int64_t)blockIdx.x * 4 + wave; unit < p.blocks * p.rchunks; unit += (int64_t)gridDim.x * 4) {
+    const int64_t blk = unit / p.rchunks, rc = unit - blk * p.rchunks;
+    const int64_t t0 = rc * ntile / p.rchunks, t1 = (rc + 1) * ntile / p.rchunks;
+    const int64_t want = (blk * 16 + li) * V;                    // this lane's columns
+    const int64_t c = want < p.J - V ? want : p.J - V;
+    // H: inner step k, lane group g: row 4 k + g
+    T h[NK * 4][V];
 #pragma unroll
-    for (int j = 0; j < 64; ++j) {
-      int row, col;
-      Mma<E_F32>::coord(j, lane, row, col);
-      int64_t i = i0 + wr + row, jj = j0 + wc + col;
-      i = i < a.I ? i : a.I - 1;
-      jj = jj < a.J ? jj : a.J - 1;
-      xv[j] = X[i * a.J + jj];
+    for (int k = 0; k < NK * 4; ++k) {
+      const int r = 4 * k + g;
+      const vec v = *(const vec*)((const T*)p.H + (int64_t)(r < p.R ? r : p.R - 1) * p.J + c);
+#pragma unroll
+      for (int n = 0; n < V; ++n) h[k][n] = r < p.R ? v[n] : (T)0;
     }
-  };
-  // Xhat tile = U(i0.., :) H(:, j0..), then (x - xhat)^2 and x^2 into the
-  // sums; rows past I (a tile past the end included) add nothing
-  auto tile = [&](int64_t it, const XT (&xv)[64]) {
-    const int64_t i0 = it * TILE;
-    Mma<E_F32>::Frag f;
-    Mma<E_F32>::zero(f);
-    if (PE == E_F32) {
-      const float* Up = (const float*)a.Up;
-      for (int kt = 0; kt < a.nkt; ++kt) {
-        float av[2][16], bv[2][16];
+    double rs[V] = {}, ns[V] = {};
+    struct Tile { xvec x[4]; };
+    auto load = [&](Tile& t, int64_t it) {
+      it = it < t1 ? it : t1 - 1;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          int64_t i = i0 + wr + m * 32 + lr;
-          i = i < a.I ? i : a.I - 1;
-          const float4* pa = (const float4*)(Up + i * 64 + kt * 32 + half * 16);
-          const float4* pb = (const float4*)(ldsB[kt] + (wc + m * 32 + lr) * LDS_ROW + half * 64);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float4 va = pa[q], vb = pb[q];
-            av[m][4 * q] = va.x; av[m][4 * q + 1] = va.y; av[m][4 * q + 2] = va.z; av[m][4 * q + 3] = va.w;
-            bv[m][4 * q] = vb.x; bv[m][4 * q + 1] = vb.y; bv[m][4 * q + 2] = vb.z; bv[m][4 * q + 3] = vb.w;
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < 16; ++t)
-#pragma unroll
-          for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int n = 0; n < 2; ++n)
-              f.c[m * 2 + n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[m][t], bv[n][t], f.c[m * 2 + n], 0, 0, 0);
+      for (int v = 0; v < 4; ++v) {
+        int64_t i = it * 16 + W::row(g, v);
+        i = i < p.I ? i : p.I - 1;
+        t.x[v] = *(const xvec*)((const XT*)p.X + i * p.J + c);
       }
-    } else {
-      // lane half h takes k = 32 h .. 32 h + 31 of both operands, 8 per MFMA
-      const bf16_t* Uh = (const bf16_t*)a.Up;
-      const bf16_t* Ul = Uh + a.I * 64;
-      bf16x8_t ah[2][4], al[2][4];
+    };
+    auto tile = [&](const Tile& t, int64_t it) {
+      const int64_t i = it * 16 + li;
+      const T* pu = (const T*)p.Ut + (i < p.I ? i : p.I - 1);
+      typename W::Acc acc[V];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        int64_t i = i0 + wr + m * 32 + lr;
-        i = i < a.I ? i : a.I - 1;
-        const bf16x8_t* ph = (const bf16x8_t*)(Uh + i * 64 + half * 32);
-        const bf16x8_t* pl = (const bf16x8_t*)(Ul + i * 64 + half * 32);
+      for (int n = 0; n < V; ++n)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          ah[m][q] = ph[q];
-          al[m][q] = pl[q];
-        }
+        for (int v = 0; v < 4; ++v) acc[n][v] = 0;
+      T u[NK * 4];
+#pragma unroll
+      for (int k = 0; k < NK * 4; ++k) {
+        const int r = 4 * k + g;
+        u[k] = pu[(int64_t)(r < p.R ? r : p.R - 1) * p.I];
       }
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        bf16x8_t bh[2], bl[2];
+      for (int k = 0; k < NK * 4; ++k) {
+        if (NK > 2 && k > NK * 4 - 4 && 4 * k >= p.R) break;    // steps past R
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
-          bh[n] = ((const bf16x8_t*)(ldsB[0] + (wc + n * 32 + lr) * LDS_ROW + half * 64))[t];
-          bl[n] = ((const bf16x8_t*)(ldsB[1] + (wc + n * 32 + lr) * LDS_ROW + half * 64))[t];
-        }
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-          for (int n = 0; n < 2; ++n) {
-            f.c[m * 2 + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[m][t], bh[n], f.c[m * 2 + n], 0, 0, 0);
-            f.c[m * 2 + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[m][t], bl[n], f.c[m * 2 + n], 0, 0, 0);
-            f.c[m * 2 + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[m][t], bh[n], f.c[m * 2 + n], 0, 0, 0);
-          }
+        for (int n = 0; n < V; ++n) acc[n] = W::mma(u[k], h[k][n], acc[n]);
       }
+      auto add = [&](int n, double x, double xh) {
+        const double d = x - xh;
+        rs[n] = fma(d, d, rs[n]);
+        ns[n] = fma(x, x, ns[n]);
+      };
+      if (it * 16 + 16 <= p.I) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int n = 0; n < V; ++n) add(n, x_value<XT>(t.x[v][n]), (double)acc[n][v]);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (it * 16 + W::row(g, v) < p.I)
+#pragma unroll
+            for (int n = 0; n < V; ++n) add(n, x_value<XT>(t.x[v][n]), (double)acc[n][v]);
+      }
+    };
+    Tile a, b2, c2;
+    load(a, t0);
+    load(b2, t0 + 1);
+    for (int64_t it = t0; it < t1; it += 3) {
+      load(c2, it + 2);
+      tile(a, it);
+      if (it + 1 >= t1) break;
+      load(a, it + 3);
+      tile(b2, it + 1);
+      if (it + 2 >= t1) break;
+      load(b2, it + 4);
+      tile(c2, it + 2);
     }
 #pragma unroll
-    for (int j = 0; j < 64; ++j) {
-      int row, col;
-      Mma<E_F32>::coord(j, lane, row, col);
-      const bool ok = i0 + wr + row < a.I && j0 + wc + col < a.J;
-      const double x = ok ? (double)x_to_f<XT>(xv[j]) : 0.0;
-      const double d = ok ? x - (double)Mma<E_F32>::get(f, j) : 0.0;
-      res = fma(d, d, res);
-      nrm = fma(x, x, nrm);
-    }
-  };
-  if (PE == E_F32) {
-    for (int64_t it = 0; it < nit; ++it) {
-      XT xv[64];
-      load_x(it, xv);
-      tile(it, xv);
-    }
-  } else {
-    // two tiles per round, each tile's X requested a tile ahead of its use
-    XT xa[64], xb[64];
-    load_x(0, xa);
-    for (int64_t it = 0; it < nit; it += 2) {
-      load_x(it + 1 < nit ? it + 1 : nit - 1, xb);
-      tile(it, xa);
-      load_x(it + 2 < nit ? it + 2 : nit - 1, xa);
-      tile(it + 1, xb);
+    for (int n = 0; n < V; ++n) {
+      // a shifted piece counts only the columns from its place on
+      if (want < p.J && c + n >= want) {
+        res += rs[n];
+        nrm += ns[n];
+      }
     }
   }
   res = warp_sum(res);
@@ -613,28 +785,23 @@ __global__ void __launch_bounds__(256, PE == E_F32 ? 2 : 1) residual_kernel(ResA
     red[1][wave] = nrm;
   }
   __syncthreads();
-  if (tid == 0) {
-    a.partial[2 * blockIdx.x] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    a.partial[2 * blockIdx.x + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  if (threadIdx.x == 0) {
+    p.partial[2 * blockIdx.x] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+    p.partial[2 * blockIdx.x + 1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
   }
 }
 
-// U (given as Ut, R x I float32) -> Up (I x 64, zero-padded columns): float32,
-// or split bfloat16 (hi = rounded value, lo = rounded remainder, the lo block
-// after the hi block)
-template <class T>
-__global__ void pad_u_kernel(const float* Ut, int64_t R, int64_t I, T* Up) {
+// U (given as Ut, R x I float32) -> Up (I x 64, zero-padded columns) in split
+// bfloat16: hi = rounded value, lo = rounded remainder, the lo block after the
+// hi block
+__global__ void pad_u_kernel(const float* Ut, int64_t R, int64_t I, bf16_t* Up) {
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < I * 64;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = e >> 6, k = e & 63;
     const float v = k < R ? Ut[k * I + i] : 0.f;
-    if constexpr (sizeof(T) == 4) {
-      Up[e] = v;
-    } else {
-      const bf16_t hi = f32_to_bf16(v);
-      Up[e] = hi;
-      Up[I * 64 + e] = f32_to_bf16(v - bf16_to_f32(hi));
-    }
+    const bf16_t hi = f32_to_bf16(v);
+    Up[e] = hi;
+    Up[I * 64 + e] = f32_to_bf16(v - bf16_to_f32(hi));
   }
 }
 
@@ -909,179 +1076,6 @@ __global__ void u_first_kernel(const double* Ut, int64_t R, int64_t I, int64_t i
   }
 }
 
-// Last-mode product with a short output and a long contraction, float32:
-// Y (A x R) = X (A x I) U (I x R) for R <= 64, U given as Ut (R x I).  The
-// generic tile has one workgroup per 128 x 128 output block, so A = 2500,
-// R = 50, I = 1000 ran on 20 workgroups with a serial loop over I.  Here a
-// workgroup owns 32 rows of X, its four waves split the contraction into
-// four ranges, and each wave forms the 32 x 64 block of its range on
-// 32x32x2 float32 MFMA; the partial blocks are added through LDS in a fixed
-// order.  Within a run of 8 contraction indices kb.., lane half h supplies
-// the indices kb + 4 h + t at step t (t = 0..3), so each lane reads 4
-// consecutive values of its X row and of its Ut row (16 bytes when I is a
-// multiple of 4); both operands come straight from memory.
-constexpr int LM_ROWS = 32;
-struct LastArgs {
-  const float* X;       // A x I row-major
-  const float* Ut;      // R x I row-major
-  float* Y;             // A x R row-major
-  int64_t A, I;
-  int R;
-  int64_t krange;       // contraction indices per wave, a multiple of 8
-};
-
-template <bool VEC>
-__global__ void __launch_bounds__(256) lastmode_small_kernel(LastArgs a) {
-  __shared__ float part[4][LM_ROWS][65];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, lr = lane & 31;
-  const int64_t a0 = (int64_t)blockIdx.x * LM_ROWS;
-  const int64_t arow = a0 + lr < a.A ? a0 + lr : a.A - 1;       // clamped; rows past A are not stored
-  const float* xr = a.X + arow * a.I;
-  const float* ur[2];
-  bool uok[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int r = c * 32 + lr;
-    uok[c] = r < a.R;
-    ur[c] = a.Ut + (int64_t)(uok[c] ? r : 0) * a.I;
-  }
-  const int64_t k0 = (int64_t)wave * a.krange;
-  const int64_t k1 = std::min<int64_t>(k0 + a.krange, a.I);
-  f32x16_t acc[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
-  auto load4 = [&](const float* row, int64_t k, bool ok) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (VEC) {
-      if (ok && k < k1) v = *(const float4*)(row + k);
-    } else if (ok) {
-      if (k < k1) v.x = row[k];
-      if (k + 1 < k1) v.y = row[k + 1];
-      if (k + 2 < k1) v.z = row[k + 2];
-      if (k + 3 < k1) v.w = row[k + 3];
-    }
-    return v;
-  };
-  for (int64_t kb = k0; kb < k1; kb += 8) {
-    const int64_t k = kb + 4 * half;
-    const float4 xv = load4(xr, k, true);
-    const float4 u0 = load4(ur[0], k, uok[0]);
-    const float4 u1 = load4(ur[1], k, uok[1]);
-    const float xs[4] = {xv.x, xv.y, xv.z, xv.w};
-    const float us0[4] = {u0.x, u0.y, u0.z, u0.w}, us1[4] = {u1.x, u1.y, u1.z, u1.w};
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[t], us0[t], acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[t], us1[t], acc[1], 0, 0, 0);
-    }
-  }
-  // value v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of the tile
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) part[wave][8 * (v >> 2) + 4 * half + (v & 3)][c * 32 + lr] = acc[c][v];
-  __syncthreads();
-  const int col = tid & 63;
-  if (col < a.R) {
-#pragma unroll
-    for (int j = 0; j < LM_ROWS / 4; ++j) {
-      const int row = (tid >> 6) + 4 * j;
-      if (a0 + row < a.A)
-        a.Y[(a0 + row) * a.R + col] = (part[0][row][col] + part[1][row][col]) + (part[2][row][col] + part[3][row][col]);
-    }
-  }
-}
-
-// Last-mode product with a short contraction and a wide output, float32:
-// Y (A x R) = X (A x I) U (I x R) for I <= 64, U given as Ut (R x I) (the
-// expansion G x_N U^(N) of the reconstruction, 50000 x 50 times 50 x 1000 at
-// 1000^3, which the generic tile ran at a fifth of the write rate).  A
-// workgroup owns 64 rows of X and 128 columns of Y: its X rows and Ut rows
-// are each one contiguous run of memory, copied to LDS with coalesced loads;
-// wave w forms the 32 x 64 block at rows 32 (w / 2), columns 64 (w % 2) on
-// 32x32x2 float32 MFMA over the whole contraction (lane half h supplies the
-// indices kb + 4 h + t at step t, as in lastmode_small_kernel).
-constexpr int EX_ROWS = 64;
-constexpr int EX_COLS = 128;
-struct ExpArgs {
-  const float* X;       // A x I row-major
-  const float* Ut;      // R x I row-major
-  float* Y;             // A x R row-major
-  int64_t A, R;
-  int I;                // <= 64
-};
-
-__global__ void __launch_bounds__(256) expand_small_kernel(ExpArgs a) {
-  __shared__ __attribute__((aligned(16))) float xs[EX_ROWS * 64];
-  __shared__ __attribute__((aligned(16))) float us[EX_COLS * 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, lr = lane & 31;
-  // consecutive workgroups take the column blocks of the same rows, so they
-  // write whole output rows together
-  const int64_t c0 = (int64_t)blockIdx.x * EX_COLS, a0 = (int64_t)blockIdx.y * EX_ROWS;
-  const int I = a.I;
-  // the runs: rows a0.. of X and c0.. of Ut, I values each (packed in LDS
-  // with the same row length I)
-  auto copy = [&](const float* src, int64_t n, float* dst) {
-    if (((uintptr_t)src & 15) == 0) {
-      const int64_t n4 = n >> 2;
-      for (int64_t q = tid; q < n4; q += 256) *(float4*)(dst + 4 * q) = *(const float4*)(src + 4 * q);
-      for (int64_t q = 4 * n4 + tid; q < n; q += 256) dst[q] = src[q];
-    } else {
-      for (int64_t q = tid; q < n; q += 256) dst[q] = src[q];
-    }
-  };
-  copy(a.X + a0 * I, std::min<int64_t>(EX_ROWS, a.A - a0) * I, xs);
-  copy(a.Ut + c0 * I, std::min<int64_t>(EX_COLS, a.R - c0) * I, us);
-  __syncthreads();
-  // rows past A and columns past R read stale LDS values: their outputs are
-  // not stored, and the contraction past I is masked
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 64;
-  const float* xr = xs + (wr + lr) * I;
-  const float* u0r = us + (wc + lr) * I;
-  const float* u1r = us + (wc + 32 + lr) * I;
-  f32x16_t acc[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
-  const int nk = (I + 7) / 8;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    if (j < nk) {
-      float xv[4], u0[4], u1[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int k = 8 * j + 4 * half + t;
-        const bool ok = k < I;
-        const int kc = ok ? k : 0;
-        xv[t] = ok ? xr[kc] : 0.f;
-        u0[t] = ok ? u0r[kc] : 0.f;
-        u1[t] = ok ? u1r[kc] : 0.f;
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[t], u0[t], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[t], u1[t], acc[1], 0, 0, 0);
-      }
-    }
-  }
-  // value v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of the tile
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int64_t col = c0 + wc + c * 32 + lr;
-    if (col >= a.R) continue;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t row = a0 + wr + 8 * (v >> 2) + 4 * half + (v & 3);
-      if (row < a.A) a.Y[row * a.R + col] = acc[c][v];
-    }
-  }
-}
-
 template <int E, int EPI, class XT>
 hipError_t launch_prod(const ProdArgs& p, int64_t batches, hipStream_t s) {
   // the batch index runs on grid.y (at most 65535 per launch)
@@ -1108,8 +1102,57 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 size_t ttm_work_bytes(int, int64_t, int64_t, int64_t, int64_t) { return 0; }
 
+template <int E, int NR>
+static hipError_t launch_stream_nr(StreamArgs& p, bool last, hipStream_t s) {
+  constexpr int V = Vec<E>::V;
+  if (!last) {
+    const int64_t wgs = ceil_div(ceil_div(p.groups, 16) * p.chunks, 4);
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((stream_kernel<E, NR, false, 1>), dim3((unsigned)wgs), dim3(256), 0, s, p);
+    return hipGetLastError();
+  }
+  const int64_t wide = ceil_div(p.A, 16 * V) * p.chunks;
+  if (wide < 1024 && p.K >= 8 * 4 * V) {
+    // too few waves to fill the chip: eight waves share a block's inner range
+    const int64_t wgs = ceil_div(p.A, 16) * p.chunks;
+    p.groups = ceil_div(p.A, 16);
+    hipLaunchKernelGGL((stream_kernel<E, NR, true, 8>), dim3((unsigned)wgs), dim3(512), 0, s, p);
+    return hipGetLastError();
+  }
+  if (ceil_div(wide, 4) > 0x7fffffff) return hipErrorInvalidValue;
+  p.groups = ceil_div(p.A, 16 * V);
+  hipLaunchKernelGGL((stream_kernel<E, NR, true, 1>), dim3((unsigned)ceil_div(wide, 4)), dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+
+template <int E>
+static hipError_t launch_stream(const void* X, int64_t A, int64_t I, int64_t B, const void* Ut, int64_t R, void* Y,
+                                hipStream_t s) {
+  StreamArgs p = {};
+  p.X = X;
+  p.Ut = Ut;
+  p.Y = Y;
+  p.A = A;
+  p.B = B;
+  p.K = (int)I;
+  p.R = (int)R;
+  p.chunks = (int)ceil_div(R, 64);
+  p.nbg = ceil_div(B, (int64_t)Vec<E>::V);
+  p.groups = A * p.nbg;
+  switch ((int)ceil_div(ceil_div(R, p.chunks), 16)) {
+    case 1: return launch_stream_nr<E, 1>(p, B == 1, s);
+    case 2: return launch_stream_nr<E, 2>(p, B == 1, s);
+    case 3: return launch_stream_nr<E, 3>(p, B == 1, s);
+    default: return launch_stream_nr<E, 4>(p, B == 1, s);
+  }
+}
+
 hipError_t launch_ttm(int elem, const void* X, int64_t A, int64_t I, int64_t B, const void* Ut, int64_t R,
                       void* Y, void*, size_t, hipStream_t s) {
+  // float32 and float64 stream; slabs shorter than a 16-byte piece (a trailing
+  // dimension of 2 or 3 below the mode) and bfloat16 take the tiles
+  if (elem == E_F32 && (B == 1 || B >= Vec<E_F32>::V)) return launch_stream<E_F32>(X, A, I, B, Ut, R, Y, s);
+  if (elem == E_F64) return launch_stream<E_F64>(X, A, I, B, Ut, R, Y, s);
   const int es = elem_size(elem);
   ProdArgs p = {};
   p.K = I;
@@ -1128,37 +1171,6 @@ hipError_t launch_ttm(int elem, const void* X, int64_t A, int64_t I, int64_t B, 
     p.vec_b = (B * es) % 16 == 0 && aligned16(X);
     batches = A;
   } else {
-    if (elem == E_F32 && R <= 64 && I >= 256) {
-      // long contraction, short output: waves split the contraction
-      LastArgs la;
-      la.X = (const float*)X;
-      la.Ut = (const float*)Ut;
-      la.Y = (float*)Y;
-      la.A = A;
-      la.I = I;
-      la.R = (int)R;
-      la.krange = ceil_div(ceil_div(I, 4), 8) * 8;
-      const int64_t wgs = ceil_div(A, LM_ROWS);
-      if (wgs > 0x7fffffff) return hipErrorInvalidValue;
-      const bool vec = I % 4 == 0 && aligned16(X) && aligned16(Ut);
-      if (vec) hipLaunchKernelGGL(lastmode_small_kernel<true>, dim3((unsigned)wgs), dim3(256), 0, s, la);
-      else hipLaunchKernelGGL(lastmode_small_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, s, la);
-      return hipGetLastError();
-    }
-    if (elem == E_F32 && I <= 64 && R > 64) {
-      // short contraction, wide output
-      ExpArgs ea;
-      ea.X = (const float*)X;
-      ea.Ut = (const float*)Ut;
-      ea.Y = (float*)Y;
-      ea.A = A;
-      ea.R = R;
-      ea.I = (int)I;
-      const int64_t gx = ceil_div(R, EX_COLS), gy = ceil_div(A, EX_ROWS);
-      if (gx > 0x7fffffff || gy > 65535) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(expand_small_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, ea);
-      return hipGetLastError();
-    }
     // Y (A x R) = X (A x I) . U (I x R): rows a, cols r
     p.a = {X, I, 1, 0, A};
     p.b = {Ut, I, 1, 0, R};
@@ -1173,7 +1185,6 @@ hipError_t launch_ttm(int elem, const void* X, int64_t A, int64_t I, int64_t B, 
     batches = 1;
   }
   switch (elem) {
-    case E_F64: return launch_prod<E_F64, 0, double>(p, batches, s);
     case E_F32: return launch_prod<E_F32, 0, float>(p, batches, s);
     case E_BF16: return launch_prod<E_BF16, 0, float>(p, batches, s);
     default: return hipErrorInvalidValue;
@@ -1265,52 +1276,76 @@ size_t residual_work_bytes(int64_t I, int64_t J) {
   return (size_t)tiles * 16 + 256 + (size_t)I * 64 * 4 + 64;
 }
 
+template <class XT, int E>
+static hipError_t launch_residual_stream(const ResidualArgs& p, dim3 grid, hipStream_t s) {
+  const int nk = (int)ceil_div(p.R, 16);
+#define RS(NK)                                                                                          \
+  if (nk <= NK) {                                                                                       \
+    hipLaunchKernelGGL((residual_stream_kernel<XT, E, NK>), grid, dim3(256), 0, s, p);                  \
+    return hipGetLastError();                                                                           \
+  }
+  RS(1) RS(2) RS(3) RS(4) RS(6) RS(8)
+#undef RS
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_residual(int x_elem, const void* X, int op_elem, const void* Ut, const void* H, int64_t I,
                            int64_t J, int64_t R, double* out, void* work, size_t, hipStream_t s, bool bf16_products) {
   const int64_t tiles = std::max<int64_t>(ceil_div(I, TILE) * ceil_div(J, TILE), ceil_div(J, RS_COLS));
   double* partial = (double*)work;
-  if (op_elem == E_F32 && R <= 64 && (x_elem == E_F32 || x_elem == E_BF16) && J % 4 == 0 && aligned16(H) &&
-      ceil_div(J, TILE) <= 0x7fffffff) {
-    // streaming form
+  if (bf16_products && op_elem == E_F32 && R <= 64 && (x_elem == E_F32 || x_elem == E_BF16) && J % 4 == 0 &&
+      aligned16(H) && ceil_div(J, RS_COLS) <= 0x7fffffff) {
+    // the precision forms' streaming pass
     void* Up = (char*)work + ((tiles * 16 + 255) / 256) * 256;
     const dim3 pgrid((unsigned)std::min<int64_t>(ceil_div(I * 64, 256), 4096));
-    if (bf16_products) hipLaunchKernelGGL(pad_u_kernel<bf16_t>, pgrid, dim3(256), 0, s, (const float*)Ut, R, I, (bf16_t*)Up);
-    else hipLaunchKernelGGL(pad_u_kernel<float>, pgrid, dim3(256), 0, s, (const float*)Ut, R, I, (float*)Up);
-    ResArgs ra;
-    ra.Up = Up;
-    ra.H = (const float*)H;
-    ra.X = X;
-    ra.I = I;
-    ra.J = J;
-    ra.R = (int)R;
-    ra.nkt = (int)ceil_div(R, 32);
-    ra.partial = partial;
-    dim3 grid((unsigned)ceil_div(J, TILE));
-    if (bf16_products) {
-      ResSplitArgs rs;
-      rs.Uh = (const bf16_t*)Up;
-      rs.Ul = (const bf16_t*)Up + I * 64;
-      rs.H = (const float*)H;
-      rs.X = X;
-      rs.I = I;
-      rs.J = J;
-      rs.R = (int)R;
-      rs.partial = partial;
-      grid = dim3((unsigned)ceil_div(J, RS_COLS));
-      // VEC: every row starts on a 4-value boundary, so a lane's 4 values are one load
-      const bool vec = J % 4 == 0 && aligned16(X);
-      if (x_elem == E_F32) {
-        if (vec) hipLaunchKernelGGL((residual_split_kernel<float, true>), grid, dim3(256), 0, s, rs);
-        else hipLaunchKernelGGL((residual_split_kernel<float, false>), grid, dim3(256), 0, s, rs);
-      } else {
-        if (vec) hipLaunchKernelGGL((residual_split_kernel<bf16_t, true>), grid, dim3(256), 0, s, rs);
-        else hipLaunchKernelGGL((residual_split_kernel<bf16_t, false>), grid, dim3(256), 0, s, rs);
-      }
+    hipLaunchKernelGGL(pad_u_kernel, pgrid, dim3(256), 0, s, (const float*)Ut, R, I, (bf16_t*)Up);
+    ResSplitArgs rs;
+    rs.Uh = (const bf16_t*)Up;
+    rs.Ul = (const bf16_t*)Up + I * 64;
+    rs.H = (const float*)H;
+    rs.X = X;
+    rs.I = I;
+    rs.J = J;
+    rs.R = (int)R;
+    rs.partial = partial;
+    const dim3 grid((unsigned)ceil_div(J, RS_COLS));
+    // VEC: every row starts on a 4-value boundary, so a lane's 4 values are one load
+    const bool vec = J % 4 == 0 && aligned16(X);
+    if (x_elem == E_F32) {
+      if (vec) hipLaunchKernelGGL((residual_split_kernel<float, true>), grid, dim3(256), 0, s, rs);
+      else hipLaunchKernelGGL((residual_split_kernel<float, false>), grid, dim3(256), 0, s, rs);
     } else {
-      if (x_elem == E_F32) hipLaunchKernelGGL((residual_kernel<float, E_F32>), grid, dim3(256), 0, s, ra);
-      else hipLaunchKernelGGL((residual_kernel<bf16_t, E_F32>), grid, dim3(256), 0, s, ra);
+      if (vec) hipLaunchKernelGGL((residual_split_kernel<bf16_t, true>), grid, dim3(256), 0, s, rs);
+      else hipLaunchKernelGGL((residual_split_kernel<bf16_t, false>), grid, dim3(256), 0, s, rs);
     }
     hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(sum_pairs_kernel, dim3(1), dim3(1024), 0, s, (const double*)partial, (int64_t)grid.x, out);
+    return hipGetLastError();
+  }
+  // Factors of up to 128 columns (H's block in registers) on rows of at least
+  // one 16-byte piece, X in the product's type (or bfloat16 with float32
+  // products); the tiles otherwise.
+  const int V = op_elem == E_F64 ? Vec<E_F64>::V : Vec<E_F32>::V;
+  const bool pair = (op_elem == E_F64 && x_elem == E_F64) || (op_elem == E_F32 && x_elem != E_F64);
+  if (pair && R <= 128 && J >= V) {
+    ResidualArgs p = {};
+    p.X = X;
+    p.Ut = Ut;
+    p.H = H;
+    p.I = I;
+    p.J = J;
+    p.R = (int)R;
+    p.blocks = ceil_div(J, (int64_t)16 * V);
+    // row ranges so that some 4096 waves have work, of four tiles at least; up
+    // to 2048 workgroups then take the (column block, range) pairs in turn
+    p.rchunks = (int)std::min<int64_t>(ceil_div(4096, p.blocks), std::max<int64_t>(1, ceil_div(I, 16) / 4));
+    p.partial = partial;
+    const dim3 grid((unsigned)std::min<int64_t>({ceil_div(p.blocks * p.rchunks, 4), 2048, tiles}));
+    hipError_t e;
+    if (op_elem == E_F64) e = launch_residual_stream<double, E_F64>(p, grid, s);
+    else if (x_elem == E_F32) e = launch_residual_stream<float, E_F32>(p, grid, s);
+    else e = launch_residual_stream<bf16_t, E_F32>(p, grid, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sum_pairs_kernel, dim3(1), dim3(1024), 0, s, (const double*)partial, (int64_t)grid.x, out);
     return hipGetLastError();
