@@ -4,11 +4,11 @@
 // needed.  The method is the textbook dense one for a few eigenpairs:
 //
 //  1. Householder reduction Z = H T H^T to a symmetric tridiagonal T.  The
-//     upper triangle is held in LDS, its rows dealt round-robin to G
-//     workgroups (G = 1 up to n of about 165).  The rank-2 update of step k
-//     is fused with the matrix-vector product of step k+1; with G > 1 the
-//     workgroups exchange their partial products and the next reflector's row
-//     through a small global buffer once per step.
+//     matrix stays in the registers of G workgroups (G = 1 up to n = 165),
+//     its columns dealt round-robin to their waves.  The rank-2 update of
+//     step k is fused with the matrix-vector product of step k+1; with G > 1
+//     the workgroups exchange their partial products and the next reflector's
+//     row through a small global buffer once per step.
 //  2. The R largest eigenvalues of T by multisection on Sturm counts (the
 //     number of negative pivots of the LDL^T factorisation of T - x I equals
 //     the number of eigenvalues below x), one wave per eigenvalue testing
@@ -33,11 +33,9 @@ constexpr int EIG_NS_MAX = 8;                // n <= 64 * EIG_NS_MAX
 constexpr int SOLVE_THREADS = 512;          // eigenvalue / eigenvector workgroup (R <= 512)
 constexpr int SOLVE_WAVES = SOLVE_THREADS / 64;
 constexpr int EIG_ITERS = 3;                 // inverse-iteration solves
-constexpr int RED_THREADS = 1024;            // reduction workgroup
+constexpr int RED_THREADS = 512;             // reduction workgroup
 constexpr int RED_WAVES = RED_THREADS / 64;
-constexpr int RED_GMAX = 32;                 // workgroups per matrix at most
-constexpr size_t LDS_BYTES = 160 * 1024;
-constexpr unsigned SPIN_LIMIT = 1u << 20;    // barrier polls before giving up (default)
+constexpr unsigned SPIN_LIMIT = 1u << 20;    // polls of one value before giving up (default)
 constexpr double EPS = 0x1p-53;              // unit roundoff of float64
 
 struct EigArgs {
@@ -58,21 +56,9 @@ struct EigArgs {
   double* Vt[EIG_MAXB];
   int* info[EIG_MAXB];
   int G[EIG_MAXB];           // workgroups sharing the reduction
-  double* P[EIG_MAXB];       // exchange of partial products, [2][G][n]
-  double* RB[EIG_MAXB];      // exchange of the next reflector's row, [2][n]
-  unsigned* cnt[EIG_MAXB];   // barrier counter (zero at launch)
-  unsigned spin_limit;       // barrier polls before giving up; 0: give up at the first barrier
+  unsigned long long* P[EIG_MAXB];   // exchange ring, [RING][G + 1][64 NS] (zero at launch)
+  unsigned spin_limit;       // polls before giving up; 0: give up at the first exchange
 };
-
-// Value of element idx of a vector spread as x[t] = v[64 t + lane].
-template <int NS>
-__device__ inline double pick(const double (&x)[NS], int idx) {
-  double v = 0.0;
-#pragma unroll
-  for (int t = 0; t < NS; ++t)
-    if (t == (idx >> 6)) v = x[t];
-  return __shfl(v, idx & 63, 64);
-}
 
 // Lane permutation of a float64 by DPP (both 32-bit halves moved alike).
 template <int CTRL>
@@ -145,230 +131,307 @@ __device__ inline double away_from_zero(double u, double tol) {
   return fabs(u) < tol ? (u < 0.0 ? -tol : tol) : u;
 }
 
-// Barrier of the G workgroups of one matrix: arrive on a counter (release),
-// poll it (acquire) until all have arrived for this step.  The polling is
-// bounded: on time-out *failed (LDS, read by thread 0 only) is raised and
-// later barriers no longer wait, so a lost arrival ends the launch with an
-// error flag instead of a hang.
-__device__ inline void group_barrier(unsigned* cnt, unsigned target, int* failed, unsigned limit) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned spins = 0;
-    if (limit == 0) *failed = 1;
-    while (!*failed && __hip_atomic_load(cnt, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (++spins > limit) *failed = 1;
-      __builtin_amdgcn_s_sleep(2);
-    }
-  }
-  __syncthreads();
+// Step 1.  The whole symmetric matrix (both triangles) stays in the registers
+// of G workgroups of eight waves.  Lane l holds rows l, l + 64, ...; column j
+// belongs to the wave (workgroup j % 64 % 8G / 8, wave % 8), so a wave's columns
+// are the lanes wid, wid + 8G, ... of every 64, cyclic, and the waves stay level
+// as the matrix shrinks.  A product y = A v is NS multiplications per column,
+// with v's entry read from the lane that holds it (v_readlane) and no sum across
+// lanes: the eight waves' parts of y are added from LDS.  The rank-2 update of
+// step k - 1 is made on the way.
+//
+// G > 1 (n > 165, where one compute unit's registers end): the workgroups
+// exchange their sums of y, and the owner of column k + 1 that column, once a
+// step, with words that are their own flags: a cell of the exchange ring is zero
+// until its value arrives as bits ^ EXCH_KEY, which is zero for no value that is
+// sent (a NaN is sent as the canonical one).  So a step waits for one store and
+// one load at the point where the XCDs meet, with no counter and no L2
+// write-back in between.  The ring holds four steps; a workgroup clears its cells
+// of step k - 2 once it has all words of step k, which no one can have sent
+// without having read those of step k - 2, and the clearing is complete before
+// it sends its words of step k + 1, so a cell is zero when its turn comes again.
+// Polls are bounded: on time-out red_failed is raised, the call reports failure
+// and no later poll waits.
+//
+// The rest of a step is latency: in wave 0 p, w and the next reflector (two sums
+// over 64 lanes, a reciprocal square root and a reciprocal).  Against the upper
+// triangle packed in LDS with a counter barrier a step: n = 39 36 us (69), n =
+// 120 0.17 ms (0.37), n = 165 0.36 (0.70), n = 300 on four workgroups 1.05 ms
+// (1.9), of whose 3.6 us a step the exchange takes 1.6.
+constexpr int RING = 4;
+constexpr unsigned long long EXCH_KEY = 0x7FF8A5C35A3CA5C3ull;
+__shared__ int red_failed;
+
+__device__ inline void exch_send(unsigned long long* p, double v) {
+  const unsigned long long w = v == v ? (unsigned long long)__double_as_longlong(v) : 0x7FF8000000000000ull;
+  __hip_atomic_store(p, w ^ EXCH_KEY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Step 1.  Workgroup gi of matrix m holds rows i = gi, gi + G, ... of the
-// upper triangle, packed in LDS (row i from column i on).  Row i is walked by
-// wave (local row) % 16, column j by lane j % 64.
+// The workgroups that hold a matrix: registers for 8 NS^2 / G values of 8 bytes
+// a thread beside the vectors.
+__host__ __device__ inline int red_groups(int64_t n) {
+  const int ns = (int)((n + 63) / 64);
+  return n <= 165 ? 1 : ns <= 4 ? 2 : ns <= 6 ? 4 : 8;
+}
+
+// Element idx (the same in every lane) of a vector spread as x[t] = v[64 t + lane].
 template <int NS>
-__global__ void __launch_bounds__(RED_THREADS) eig_reduce_kernel(EigArgs g) {
-  constexpr int NM = 64 * NS;
-  extern __shared__ __attribute__((aligned(16))) double sm[];
-  double* Vb = sm;                 // [2][NM] reflectors of this and the previous step
-  double* Wb = Vb + 2 * NM;        // [2][NM] their rank-2 partners
-  double* cacc = Wb + 2 * NM;      // [16][NM] per-wave column sums of the product
-  double* rowsum = cacc + RED_WAVES * NM;   // row sums of the product (own rows)
-  double* rowbuf = rowsum + NM;    // the next reflector's row
+__device__ inline double element(const double (&x)[NS], int idx) {
+  // (every slot's lane is read and one kept: a chosen slot would be indexed in
+  // memory)
+  double v = lane_f64(x[0], idx & 63);
+#pragma unroll
+  for (int t = 1; t < NS; ++t) {
+    const double vt = lane_f64(x[t], idx & 63);
+    v = t == (idx >> 6) ? vt : v;
+  }
+  return v;
+}
+
+template <int NS, int G>
+__device__ inline void reduce_matrix(const EigArgs& g, int m, int gi, double* sm) {
+  constexpr int NM = 64 * NS, U = 8 / G, NC = NS * U;   // columns of a wave: U of every 64
+  double* Vs = sm;                 // [NM] the reflector
+  double* Ws = Vs + NM;            // [NM] its rank-2 partner
+  double* part = Ws + NM;          // [8][NM] the waves' parts of the product
+  double* ysum = part + RED_WAVES * NM;     // the product
+  double* rowbuf = ysum + NM;      // column k + 1
   double* dsh = rowbuf + NM;       // diagonal, off-diagonal and tau of T, written out at the end
   double* esh = dsh + NM;
   double* tsh = esh + NM;
-  double* red = tsh + NM;          // scalars
-  double* rows = red + 128;        // packed rows; reflector k replaces row k once used
+  double* last = tsh + NM;         // the last entry
 
-  const int m = blockIdx.y, gi = blockIdx.x;
-  const int n = g.n[m], G = g.G[m];
-  if (gi >= G) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = g.n[m];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wid = gi * RED_WAVES + wave;
   const double* Z = g.Z[m];
   double* H = g.A[m];              // reflector k is written to row k (columns k+2..)
-  const int nr = (n - gi + G - 1) / G;
-  auto roff = [&](int r) { return r * (n - gi) - G * (r * (r - 1) / 2); };   // start of local row r
 
-  for (int r = wave; r < nr; r += RED_WAVES) {
-    const int i = gi + r * G, base = roff(r) - i;
+  double A[NS][NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int j = 64 * (c / U) + wid + 8 * G * (c % U);
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
-      const int j = 64 * t + lane;
-      if (j >= i && j < n) rows[base + j] = Z[i * n + j];
+      const int i = 64 * t + lane;
+      A[t][c] = (i < n && j < n) ? (i >= j ? Z[(int64_t)j * n + i] : Z[(int64_t)i * n + j]) : 0.0;
     }
   }
-  for (int j = tid; j < 4 * NM; j += RED_THREADS) Vb[j] = 0.0;   // Vb and Wb
-  if (wave == 0) {
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      const int j = 64 * t + lane;
-      rowbuf[j] = j < n ? Z[j] : 0.0;
-    }
+  for (int j = tid; j < NM; j += RED_THREADS) {
+    Vs[j] = 0.0;
+    Ws[j] = 0.0;
+    rowbuf[j] = j < n ? Z[j] : 0.0;
   }
-  int* failed = (int*)(red + 63);
-  if (tid == 0) *failed = 0;
+  if (tid == 0) red_failed = 0;
   __syncthreads();
 
-  // Reflector k (wave 0, identical in every workgroup) from rowbuf = row k
-  // after the updates of steps up to k-2, minus the update of step k-1:
-  // v = x - beta e_{k+1} scaled so that v_{k+1} = 1, tau = (beta - alpha) / beta,
-  // beta = -sign(alpha) ||x||, x the part of the row beyond the diagonal.
-  auto reflector = [&](int k, const double* Vp, const double* Wp, double* Vn) {
-    const double vpk = Vp[k], wpk = Wp[k];
-    double x[NS];
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      const int j = 64 * t + lane;
-      x[t] = (j >= k && j < n) ? fma(-vpk, Wp[j], fma(-wpk, Vp[j], rowbuf[j])) : 0.0;
-    }
-    const double dk = pick(x, k), alpha = pick(x, k + 1);
+  // Reflector k (wave 0, identical in every workgroup) from x = row k from the
+  // diagonal on: v = x - beta e_{k+1} scaled so that v_{k+1} = 1,
+  // tau = (beta - alpha) / beta, beta = -sign(alpha) ||x||.
+  double tau = 0.0;                // wave 0: of the current reflector
+  auto reflector = [&](int k, const double (&x)[NS]) {
+    const double dk = element(x, k), alpha = element(x, k + 1);
     double s2 = 0.0;
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
-      const int j = 64 * t + lane;
-      if (j >= k + 2 && j < n) s2 = fma(x[t], x[t], s2);
+      const double xt = 64 * t + lane >= k + 2 ? x[t] : 0.0;
+      s2 = fma(xt, xt, s2);
     }
     s2 = wave_sum(s2);
-    double tk = 0.0, beta = alpha, scal = 0.0;
+    double beta = alpha, scal = 0.0;
+    tau = 0.0;
     if (s2 > 0.0) {
-      const double r = sqrt(fma(alpha, alpha, s2));
+      const double q = fma(alpha, alpha, s2), rs = rsq_nr(q), r = q * rs;
       beta = alpha >= 0.0 ? -r : r;
-      tk = (beta - alpha) / beta;
-      scal = 1.0 / (alpha - beta);
+      tau = fma(fabs(alpha), rs, 1.0);
+      scal = rcp_nr(alpha - beta);
     }
-    const bool own = k % G == gi;
-    const int kbase = roff((k - gi) / G) - k;
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
       const int j = 64 * t + lane;
-      const double v = j == k + 1 ? 1.0 : (j >= k + 2 && j < n ? x[t] * scal : 0.0);
-      Vn[j] = v;
-      if (own && j >= k + 2 && j < n) rows[kbase + j] = v;
+      Vs[j] = j == k + 1 ? 1.0 : (j >= k + 2 ? x[t] * scal : 0.0);
     }
     if (lane == 0) {
       dsh[k] = dk;
       esh[k] = beta;
-      tsh[k] = tk;
-      red[0] = tk;
+      tsh[k] = tau;
     }
   };
 
-  if (wave == 0 && n >= 3) reflector(0, Vb + NM, Wb + NM, Vb);   // the other buffers are still zero
-  __syncthreads();
-  for (int k = 0; k + 2 < n; ++k) {
-    const int cur = k & 1;
-    double* Vc = Vb + cur * NM;
-    double* Wc = Wb + cur * NM;
-    double* Vp = Vb + (cur ^ 1) * NM;
-    double* Wp = Wb + (cur ^ 1) * NM;
-    const double tk = red[0];
-
-    // own rows i >= k+1: apply the previous step's update A -= v w^T + w v^T
-    // and accumulate y = A v (row sums across lanes, column sums per lane)
-    double vcj[NS], vpj[NS], wpj[NS], csum[NS];
+  if (wave == 0 && n >= 3) {
+    double x[NS];
 #pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      vcj[t] = Vc[64 * t + lane];
-      vpj[t] = Vp[64 * t + lane];
-      wpj[t] = Wp[64 * t + lane];
-      csum[t] = 0.0;
-    }
-    const int r0 = k + 1 > gi ? (k + 1 - gi + G - 1) / G : 0;
-    for (int r = r0 + wave; r < nr; r += RED_WAVES) {
-      const int i = gi + r * G, base = roff(r) - i;
-      const double vci = Vc[i], vpi = Vp[i], wpi = Wp[i];
-      double rs = 0.0;
+    for (int t = 0; t < NS; ++t) x[t] = rowbuf[64 * t + lane];
+    reflector(0, x);
+  }
+  __syncthreads();
+  double v[NS], vp[NS];            // the reflectors of this and the previous step
+#pragma unroll
+  for (int t = 0; t < NS; ++t) v[t] = 0.0;
+  for (int k = 0; k + 2 < n; ++k) {
+    // columns j > k: the previous step's update A -= v w^T + w v^T, then this
+    // wave's part of y = A v
+    auto cell = [&](int q, int j) { return g.P[m] + ((int64_t)(k % RING) * (G + 1) + q) * NM + j; };
+    {
+      double wp[NS], y[NS];
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        const int j = 64 * t + lane;
-        if (j >= i && j < n) {
-          const double a = fma(-vpi, wpj[t], fma(-wpi, vpj[t], rows[base + j]));
-          rows[base + j] = a;
-          rs = fma(a, vcj[t], rs);
-          if (j > i) csum[t] = fma(a, vci, csum[t]);
-          if (i == k + 1) rowbuf[j] = a;
+        vp[t] = v[t];
+        v[t] = Vs[64 * t + lane];
+        wp[t] = Ws[64 * t + lane];
+        y[t] = 0.0;
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        if (64 * s + 63 <= k || 64 * s >= n) continue;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int c = s * U + u, l = wid + 8 * G * u;
+          if (64 * s + l <= k || 64 * s + l >= n) continue;
+          const double vj = lane_f64(v[s], l), vpj = lane_f64(vp[s], l), wpj = lane_f64(wp[s], l);
+#pragma unroll
+          for (int t = 0; t < NS; ++t) {
+            A[t][c] = fma(-vp[t], wpj, fma(-wp[t], vpj, A[t][c]));
+            y[t] = fma(A[t][c], vj, y[t]);
+          }
         }
       }
-      rs = wave_sum(rs);
-      if (lane == 0) rowsum[i] = rs;
-    }
 #pragma unroll
-    for (int t = 0; t < NS; ++t) cacc[wave * NM + 64 * t + lane] = csum[t];
+      for (int t = 0; t < NS; ++t) part[wave * NM + 64 * t + lane] = y[t];
+      // column k + 1, from the wave that holds it
+      if (((k + 1) & 63) % (8 * G) == wid) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          if (s != (k + 1) >> 6) continue;
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (u != ((k + 1) & 63) / (8 * G)) continue;
+#pragma unroll
+            for (int t = 0; t < NS; ++t) {
+              rowbuf[64 * t + lane] = A[t][s * U + u];
+              if (G > 1) exch_send(cell(G, 64 * t + lane), A[t][s * U + u]);
+            }
+          }
+        }
+      }
+      // the reflector goes out (to be applied to the eigenvectors of T)
+      if (gi == k % G && wave == RED_WAVES - 1) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+          const int j = 64 * t + lane;
+          if (j >= k + 2 && j < n) H[(int64_t)k * n + j] = v[t];
+        }
+      }
+    }
     __syncthreads();
 
-    // y = A v for j > k into rowsum: this workgroup's row and column sums,
-    // plus (G > 1) the other workgroups' parts and row k+1 from its owner,
-    // exchanged through global memory, added in a fixed order
-    const int par = k & 1;
-    double* Pp = g.P[m] + (size_t)par * G * n;
-    double* RBp = g.RB[m] + (size_t)par * n;
-    for (int j = tid; j < n; j += RED_THREADS) {
-      if (j > k) {
-        double y = (j - gi) % G == 0 ? rowsum[j] : 0.0;
+    auto parts = [&](int j) {
+      double p[RED_WAVES];
 #pragma unroll
-        for (int w = 0; w < RED_WAVES; ++w) y += cacc[w * NM + j];
-        if (G > 1) {
-          Pp[gi * n + j] = y;
-          if ((k + 1) % G == gi) RBp[j] = rowbuf[j];
-        } else {
-          rowsum[j] = y;
+      for (int w = 0; w < RED_WAVES; ++w) p[w] = part[w * NM + j];
+      return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    };
+    double y[NS];                  // wave 0: the product
+    if constexpr (G == 1) {
+      if (wave == 0) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t) y[t] = parts(64 * t + lane);
+      }
+    } else {
+      // wave t adds the parts of rows 64 t.., sends the sum and adds those of
+      // all workgroups in order
+      if (wave < NS) {
+        const int j = 64 * wave + lane;
+        const int owner = ((k + 1) & 63) % (8 * G) / 8;
+        const double own = parts(j);
+        exch_send(cell(gi, j), own);
+        unsigned long long w[G + 1];
+        unsigned spins = 0;
+        if (g.spin_limit == 0) red_failed = 1;
+        for (;;) {
+          bool all = true;
+#pragma unroll
+          for (int q = 0; q <= G; ++q) {
+            w[q] = __hip_atomic_load(cell(q, j), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+#pragma unroll
+          for (int q = 0; q <= G; ++q) all = all && (w[q] != 0);
+          if (__all(all)) break;
+          if (++spins > g.spin_limit) red_failed = 1;
+          if (__hip_atomic_load(&red_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
+        }
+        double sum = 0.0;
+#pragma unroll
+        for (int q = 0; q < G; ++q) sum += __longlong_as_double((long long)(w[q] ^ EXCH_KEY));
+        ysum[j] = sum;
+        if (owner != gi) rowbuf[j] = __longlong_as_double((long long)(w[G] ^ EXCH_KEY));
+        // everyone has read the cells of two steps ago
+        if (k >= 2) {
+          unsigned long long* old = g.P[m] + (int64_t)((k - 2) % RING) * (G + 1) * NM + j;
+          __hip_atomic_store(old + (int64_t)gi * NM, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (((k - 1) & 63) % (8 * G) / 8 == gi)
+            __hip_atomic_store(old + (int64_t)G * NM, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __builtin_amdgcn_s_waitcnt(0);
         }
       }
-    }
-    if (G > 1) {
-      group_barrier(g.cnt[m], (unsigned)(k + 1) * (unsigned)G, failed, g.spin_limit);
-      for (int j = tid; j < n; j += RED_THREADS) {
-        if (j > k) {
-          double y = 0.0;
-#pragma unroll 4
-          for (int q = 0; q < G; ++q) y += Pp[q * n + j];
-          rowsum[j] = y;
-          rowbuf[j] = RBp[j];
-        }
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t) y[t] = ysum[64 * t + lane];
       }
     }
-    __syncthreads();
 
     if (wave == 0) {
-      // p = tau y, K = tau p^T v / 2, w = p - K v; then the next reflector
-      // from row k+1
-      double pj[NS], pv = 0.0;
+      // p = tau y, K = tau p^T v / 2, w = p - K v (zero up to k); then the next
+      // reflector from row k+1, which this step's update changes by
+      // w + w_{k+1} v (v_{k+1} = 1)
+      double x[NS], w[NS], pv = 0.0;
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        const int j = 64 * t + lane;
-        pj[t] = (j > k && j < n) ? tk * rowsum[j] : 0.0;
-        pv = fma(pj[t], vcj[t], pv);
+        x[t] = rowbuf[64 * t + lane];
+        w[t] = 64 * t + lane > k ? tau * y[t] : 0.0;
+        pv = fma(w[t], v[t], pv);
       }
-      const double K = 0.5 * tk * wave_sum(pv);
+      const double K = 0.5 * tau * wave_sum(pv);
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        const int j = 64 * t + lane;
-        Wc[j] = (j > k && j < n) ? fma(-K, vcj[t], pj[t]) : 0.0;
+        w[t] = fma(-K, v[t], w[t]);
+        Ws[64 * t + lane] = w[t];
       }
-      __builtin_amdgcn_wave_barrier();
-      if (k + 3 < n) reflector(k + 1, Vc, Wc, Vp);
+      if (k + 3 < n) {
+        const double wk = element(w, k + 1);
+#pragma unroll
+        for (int t = 0; t < NS; ++t) x[t] = 64 * t + lane > k ? x[t] - fma(wk, v[t], w[t]) : 0.0;
+        reflector(k + 1, x);
+      }
     }
     __syncthreads();
   }
 
   // the last 2 x 2 block: row n-2 (rowbuf) and entry (n-1, n-1) (its owner)
-  // after the last update; then T and the reflectors go out
+  // after the last update; then T goes out
+  const bool owner = ((n - 1) & 63) % (8 * G) / 8 == gi;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (64 * (c / U) + wid + 8 * G * (c % U) == n - 1 && lane == ((n - 1) & 63)) {
+#pragma unroll
+      for (int t = 0; t < NS; ++t)
+        if (t == (n - 1) >> 6) last[0] = A[t][c];
+    }
+  __syncthreads();
   if (tid == 0) {
     if (n <= 2) {
       dsh[0] = Z[0];
       esh[0] = n == 2 ? Z[1] : 0.0;
       if (n == 2) dsh[1] = Z[3];
     } else {
-      const int c = (n - 3) & 1, p = n - 2, q = n - 1;
-      const double* Vc = Vb + c * NM;
-      const double* Wc = Wb + c * NM;
-      dsh[p] = fma(-Vc[p], Wc[p], fma(-Wc[p], Vc[p], rowbuf[p]));
-      esh[p] = fma(-Vc[p], Wc[q], fma(-Wc[p], Vc[q], rowbuf[q]));
-      if (q % G == gi) g.d[m][q] = fma(-Vc[q], Wc[q], fma(-Wc[q], Vc[q], rows[roff((q - gi) / G)]));
+      const int p = n - 2, q = n - 1;
+      dsh[p] = fma(-Vs[p], Ws[p], fma(-Ws[p], Vs[p], rowbuf[p]));
+      esh[p] = fma(-Vs[p], Ws[q], fma(-Ws[p], Vs[q], rowbuf[q]));
+      if (owner) g.d[m][q] = fma(-Vs[q], Ws[q], fma(-Ws[q], Vs[q], last[0]));
     }
-    if (*failed && g.info[m]) g.info[m][0] = 1;
+    if (red_failed && g.info[m]) g.info[m][0] = 1;
   }
   __syncthreads();
   if (gi == 0) {
@@ -378,14 +441,26 @@ __global__ void __launch_bounds__(RED_THREADS) eig_reduce_kernel(EigArgs g) {
       g.tau[m][i] = i + 2 < n ? tsh[i] : 0.0;
     }
   }
-  for (int r = wave; r < nr; r += RED_WAVES) {
-    const int k = gi + r * G, base = roff(r) - k;
-    if (k + 2 >= n) continue;
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      const int j = 64 * t + lane;
-      if (j >= k + 2 && j < n) H[k * n + j] = rows[base + j];
-    }
+}
+
+// Each matrix takes the form of its own size, whatever else is in the launch.
+// LARGE: matrices above 192 among them.
+template <bool LARGE>
+__global__ void __launch_bounds__(RED_THREADS) eig_reduce_kernel(EigArgs g) {
+  extern __shared__ __attribute__((aligned(16))) double sm[];
+  const int m = blockIdx.y, gi = blockIdx.x, n = g.n[m];
+  if (gi >= g.G[m]) return;
+  if (n <= 64) reduce_matrix<1, 1>(g, m, gi, sm);
+  else if (n <= 128) reduce_matrix<2, 1>(g, m, gi, sm);
+  else if (n <= 165) reduce_matrix<3, 1>(g, m, gi, sm);
+  else if (n <= 192) reduce_matrix<3, 2>(g, m, gi, sm);
+  if constexpr (LARGE) {
+    if (n <= 192) return;
+    if (n <= 256) reduce_matrix<4, 2>(g, m, gi, sm);
+    else if (n <= 320) reduce_matrix<5, 4>(g, m, gi, sm);
+    else if (n <= 384) reduce_matrix<6, 4>(g, m, gi, sm);
+    else if (n <= 448) reduce_matrix<7, 8>(g, m, gi, sm);
+    else reduce_matrix<8, 8>(g, m, gi, sm);
   }
 }
 
@@ -735,32 +810,19 @@ size_t solve_lds_bytes(int ns) {
   const int nm = 64 * ns;
   return (size_t)(5 * nm + 64) * 8 + (size_t)(nm + 1) * 4;
 }
-size_t reduce_fixed_bytes(int ns) { return (size_t)((9 + RED_WAVES) * 64 * ns + 128) * 8; }
-
-// Smallest G whose largest share of packed rows fits in LDS beside the rest
-// (0: none up to RED_GMAX); rows_cap receives that share in doubles.
-int reduce_groups(int64_t n, int64_t& rows_cap) {
-  const int ns = (int)ceil_div(n, 64);
-  for (int G = 1; G <= RED_GMAX && G <= n; ++G) {
-    int64_t rows = 0;
-    for (int64_t i = 0; i < n; i += G) rows += n - i;   // group 0 holds the most
-    if (reduce_fixed_bytes(ns) + (size_t)rows * 8 <= LDS_BYTES) {
-      rows_cap = rows;
-      return G;
-    }
-  }
-  return 0;
+size_t reduce_lds_bytes(int ns) { return (size_t)((7 + RED_WAVES) * 64 * ns + 8) * 8; }
+size_t ring_bytes(int64_t n) {
+  const int G = red_groups(n);
+  return G > 1 ? (size_t)RING * (G + 1) * (size_t)(ceil_div(n, 64) * 64) * 8 : 0;
 }
 
 struct Layout {
-  size_t A, d, e, tau, X, Y, ainv, bu, du, cm, piv, P, RB, cnt, total;
+  size_t A, d, e, tau, X, Y, ainv, bu, du, cm, piv, P, total;
 };
 inline size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 Layout layout(int64_t n, int64_t R) {
   Layout L;
   size_t o = 0;
-  int64_t cap = 0;
-  const int G = std::max(1, reduce_groups(n, cap));
   auto take = [&](size_t bytes) { const size_t at = o; o = al256(o + bytes); return at; };
   L.A = take((size_t)n * n * 8);
   L.d = take((size_t)n * 8);
@@ -773,39 +835,38 @@ Layout layout(int64_t n, int64_t R) {
   L.du = take((size_t)n * R * 8);
   L.cm = take((size_t)n * R * 8);
   L.piv = take((size_t)n * R);
-  L.P = take((size_t)2 * G * n * 8);
-  L.RB = take((size_t)2 * n * 8);
-  L.cnt = take(64);
+  L.P = take(ring_bytes(n));
   L.total = o;
   return L;
 }
 
 template <int NS>
-hipError_t launch_ns(EigArgs& a, int nmat, int gmax, int64_t rows_cap, int rmax, bool coop, hipStream_t st) {
+hipError_t launch_ns(EigArgs& a, int nmat, int gmax, int rmax, bool coop, hipStream_t st) {
   hipError_t e;
-  const size_t rshm = reduce_fixed_bytes(NS) + (size_t)rows_cap * 8;
-  if ((e = hipFuncSetAttribute((const void*)eig_reduce_kernel<NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)rshm)) != hipSuccess)
+  const size_t rshm = reduce_lds_bytes(NS);
+  constexpr bool LARGE = NS > 3;
+  const void* reduce = (const void*)eig_reduce_kernel<LARGE>;
+  if ((e = hipFuncSetAttribute(reduce, hipFuncAttributeMaxDynamicSharedMemorySize, (int)reduce_lds_bytes(LARGE ? 8 : 3))) !=
+      hipSuccess)
     return e;
   if (gmax > 1) {
     // the workgroups of a matrix wait for each other: a cooperative launch
     // guarantees that they are all resident.  An ordinary launch (coop false,
     // for a solve that runs beside other work) relies on the few workgroups
-    // becoming resident as the device frees room; the barrier's bounded spin
-    // reports a failure rather than waiting for ever.
+    // becoming resident as the device frees room; the bounded polls report a
+    // failure rather than waiting for ever.
     for (int k = 0; k < nmat; ++k)
-      if (a.G[k] > 1 && (e = fill_zero(a.cnt[k], 64, st)) != hipSuccess) return e;
+      if (a.G[k] > 1 && (e = fill_zero(a.P[k], ring_bytes(a.n[k]), st)) != hipSuccess) return e;
     if (coop) {
       void* args[] = {&a};
-      e = hipLaunchCooperativeKernel((const void*)eig_reduce_kernel<NS>, dim3(gmax, nmat), dim3(RED_THREADS), args,
-                                     rshm, st);
+      e = hipLaunchCooperativeKernel(reduce, dim3(gmax, nmat), dim3(RED_THREADS), args, rshm, st);
       if (e != hipSuccess) return e;
     } else {
-      hipLaunchKernelGGL(eig_reduce_kernel<NS>, dim3(gmax, nmat), dim3(RED_THREADS), rshm, st, a);
+      hipLaunchKernelGGL(eig_reduce_kernel<LARGE>, dim3(gmax, nmat), dim3(RED_THREADS), rshm, st, a);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   } else {
-    hipLaunchKernelGGL(eig_reduce_kernel<NS>, dim3(1, nmat), dim3(RED_THREADS), rshm, st, a);
+    hipLaunchKernelGGL(eig_reduce_kernel<LARGE>, dim3(1, nmat), dim3(RED_THREADS), rshm, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const size_t sshm = solve_lds_bytes(NS);
@@ -823,8 +884,7 @@ hipError_t launch_ns(EigArgs& a, int nmat, int gmax, int64_t rows_cap, int rmax,
 }  // namespace
 
 bool eig_top_ok(int64_t n, int64_t R) {
-  int64_t cap;
-  return n >= 1 && n <= 64 * EIG_NS_MAX && R >= 1 && R <= n && reduce_groups(n, cap) > 0;
+  return n >= 1 && n <= 64 * EIG_NS_MAX && R >= 1 && R <= n;
 }
 
 size_t eig_top_work_bytes(int64_t n, int64_t R) { return layout(n, R).total; }
@@ -835,11 +895,11 @@ hipError_t eig_top_batched(int nmat, const double* const* Z, const int64_t* ns, 
   if (nmat <= 0) return hipSuccess;
   if (nmat > EIG_MAXB) return hipErrorInvalidValue;
   EigArgs a = {};
-  // RBKI_EIG_SPIN_LIMIT: barrier polls of a multi-workgroup reduction before
+  // RBKI_EIG_SPIN_LIMIT: polls of a value of a multi-workgroup reduction before
   // it gives up and reports failure (0: at once), to test the error path
   a.spin_limit = SPIN_LIMIT;
   if (const char* lim = getenv("RBKI_EIG_SPIN_LIMIT")) a.spin_limit = (unsigned)strtoul(lim, nullptr, 10);
-  int64_t nmax = 0, rmax = 0, rows_cap = 0;
+  int64_t nmax = 0, rmax = 0;
   int gmax = 1;
   for (int k = 0; k < nmat; ++k) {
     if (!eig_top_ok(ns[k], Rs[k])) return hipErrorInvalidValue;
@@ -862,25 +922,21 @@ hipError_t eig_top_batched(int nmat, const double* const* Z, const int64_t* ns, 
     a.lam[k] = lam[k];
     a.Vt[k] = Vt[k];
     a.info[k] = info ? info[k] : nullptr;
-    int64_t cap = 0;
-    a.G[k] = reduce_groups(ns[k], cap);
-    a.P[k] = (double*)(w + L.P);
-    a.RB[k] = (double*)(w + L.RB);
-    a.cnt[k] = (unsigned*)(w + L.cnt);
+    a.G[k] = red_groups(ns[k]);
+    a.P[k] = (unsigned long long*)(w + L.P);
     gmax = std::max(gmax, a.G[k]);
-    rows_cap = std::max(rows_cap, cap);
     nmax = std::max(nmax, ns[k]);
     rmax = std::max(rmax, Rs[k]);
   }
   switch ((int)ceil_div(nmax, 64)) {
-    case 1: return launch_ns<1>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    case 2: return launch_ns<2>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    case 3: return launch_ns<3>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    case 4: return launch_ns<4>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    case 5: return launch_ns<5>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    case 6: return launch_ns<6>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    case 7: return launch_ns<7>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
-    default: return launch_ns<8>(a, nmat, gmax, rows_cap, (int)rmax, coop, st);
+    case 1: return launch_ns<1>(a, nmat, gmax, (int)rmax, coop, st);
+    case 2: return launch_ns<2>(a, nmat, gmax, (int)rmax, coop, st);
+    case 3: return launch_ns<3>(a, nmat, gmax, (int)rmax, coop, st);
+    case 4: return launch_ns<4>(a, nmat, gmax, (int)rmax, coop, st);
+    case 5: return launch_ns<5>(a, nmat, gmax, (int)rmax, coop, st);
+    case 6: return launch_ns<6>(a, nmat, gmax, (int)rmax, coop, st);
+    case 7: return launch_ns<7>(a, nmat, gmax, (int)rmax, coop, st);
+    default: return launch_ns<8>(a, nmat, gmax, (int)rmax, coop, st);
   }
 }
 
