@@ -489,7 +489,8 @@ template <> struct Vec<E_F64> {
 };
 
 // KS > 1: the KS waves of a workgroup split the inner dimension of one block
-// of 16 rows (LAST only) and add their tiles through LDS.
+// of 16 rows (LAST only) and add their tiles through LDS, in float64; a wave's
+// own sums move to float64 every 6 stages (inner dimensions of thousands).
 template <int E, int NR, bool LAST, int KS>
 __global__ void __launch_bounds__(64 * (KS > 1 ? KS : 4)) stream_kernel(StreamArgs p) {
   typedef Vec<E> W;
@@ -577,6 +578,16 @@ __global__ void __launch_bounds__(64 * (KS > 1 ? KS : 4)) stream_kernel(StreamAr
   constexpr int step = KS > 1 ? KS : 1;
   Stage s0, s1, s2;
   auto at = [&](int s) { return (s < ns ? s : ns - 1) * ST; };
+  double big[KS > 1 ? NR : 1][4] = {};
+  auto flush = [&]() {
+#pragma unroll
+    for (int u = 0; u < (KS > 1 ? NR : 0); ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        big[u][v] += (double)acc[u][0][v];
+        acc[u][0][v] = 0;
+      }
+  };
   if (first < ns) {
     load(s0, first * ST);
     load(s1, at(first + step));
@@ -589,6 +600,7 @@ __global__ void __launch_bounds__(64 * (KS > 1 ? KS : 4)) stream_kernel(StreamAr
       if (s + 2 * step >= ns) break;
       load(s1, at(s + 4 * step));
       mul(s2);
+      if (KS > 1 && (s - first) / step % 6 == 3) flush();
     }
   }
   if (ns * ST < p.K && (KS == 1 || wave == ns % KS)) {
@@ -597,20 +609,21 @@ __global__ void __launch_bounds__(64 * (KS > 1 ? KS : 4)) stream_kernel(StreamAr
   }
 
   if constexpr (KS > 1) {
-    __shared__ T sums[KS][NR * 256];
+    __shared__ double sums[KS][NR * 256];
+    flush();
 #pragma unroll
     for (int u = 0; u < NR; ++u)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sums[wave][(16 * u + W::row(g, v)) * 16 + li] = acc[u][0][v];
+      for (int v = 0; v < 4; ++v) sums[wave][(16 * u + W::row(g, v)) * 16 + li] = big[u][v];
     __syncthreads();
     for (int e = threadIdx.x; e < NR * 256; e += 64 * KS) {
       // consecutive threads take consecutive output columns of a row
       const int i = e / (16 * NR), rr = e % (16 * NR);
-      T v = sums[0][rr * 16 + i];
+      double v = sums[0][rr * 16 + i];
 #pragma unroll
       for (int w = 1; w < KS; ++w) v += sums[w][rr * 16 + i];
       const int64_t a = blk * 16 + i;
-      if (a < p.A && r0 + rr < p.R) ((T*)p.Y)[a * p.R + r0 + rr] = v;
+      if (a < p.A && r0 + rr < p.R) ((T*)p.Y)[a * p.R + r0 + rr] = (T)v;
     }
   } else {
 #pragma unroll
