@@ -46,10 +46,10 @@
 // of X, run on one XCD (or two) and the slab is fetched from HBM once into its
 // L2, for any number of splits.
 // Measured per mode, against 128 x 128 tiles on the MFMA of the operand's own
-// type: float32 1000^3, S = 60, 12.5 ms (20.2; bound by its loads and by the
-// staging between two barriers a K tile, the matrix cores a third busy), 400^3,
-// S = 30, 0.41 ms (1.12); float32 64^5, S = 22, 1.55 ms (2.75; 2.8 TB/s of X);
-// float64 200^3, S = 15, 0.11 ms (0.22).
+// type: float32 64^5, S = 22, 1.55 ms (2.75; 2.8 TB/s of X); float64 200^3,
+// S = 15, 0.11 ms (0.22).
+//
+// Large float32 modes take the wide form below (gram_wide_kernel).
 #include "rbki_kernels.h"
 #include "rbki_philox.h"
 
@@ -485,6 +485,279 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
     }
 }
 
+// The wide form of float32: tiles of 256 x 256 of C, eight waves of 2 x 4 blocks,
+// K tiles of 16 values.  A diagonal tile has work for six waves and its rows for
+// four staging waves, so it forms the first 64 sketch rows by its 256 columns
+// too; sketch rows from 64 on have tiles of 128 rows x 384 columns.  Wave w loads,
+// splits and stores the 64 rows of staged group w.  A block's six part products of
+// a K tile are accumulated from zero and then added to its sum, so one accumulator
+// serves, a sum is rounded once per 16 K values, and the part products are rounded
+// at their own magnitude.
+//
+// A 128 x 128 tile stages 256 rows for 16 blocks and its two barriers a K tile keep
+// loads, splitting and products apart; here it is 512 rows for 64 blocks, with one
+// barrier, three LDS buffers and the two waves of a SIMD in opposite phases.
+// Measured per mode: 1000^3, S = 60, 7.3 ms (12.9 with the 128-row tiles, 20.2 on
+// the float32 MFMA): 1.07 PFLOP/s of bfloat16 products, where an 8192^3 bfloat16
+// matrix product of the vendor's library reaches 1.19; the clock falls to 1.7 GHz
+// under it (power), so fewer cycles on the vector unit change nothing there.
+// 400^3, S = 30, 0.31 ms (0.41, 1.12).
+constexpr int WIDE_K = 16, WIDE_GROUPS = 8, WIDE_WROWS = 128, WIDE_WCOLS = 384;
+// LDS: [buffer][part][half of the K tile][row][16 bytes]; the pad puts the two
+// halves of a row on different banks (a wave writes both at once)
+constexpr int WIDE_HALF = WIDE_GROUPS * GROUP * 16 + 128;
+constexpr int WIDE_PLANE = 2 * WIDE_HALF, WIDE_BUF = 3 * WIDE_PLANE;
+
+template <bool GATHER>
+__global__ void __launch_bounds__(512, 2) gram_wide_kernel(GramArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[3 * WIDE_BUF];
+  const int per = (g.ntiles * g.splits) >> 3, spare = (g.ntiles * g.splits) & 7, xcd = blockIdx.x & 7;
+  const int id = xcd * per + (xcd < spare ? xcd : spare) + (int)(blockIdx.x >> 3);
+  const int split = id / g.ntiles, tile = id % g.ntiles;
+  int lane = threadIdx.x & 63;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int I = (int)g.I, S = g.S;
+
+  // this wave's staged group (first row, rows that exist, sketch or mode) and
+  // blocks (staged rows of the operands, first row and column of the output;
+  // live: whether any is wanted).  Waves w and w + 4 share a SIMD: of a diagonal
+  // tile (64-row, 128-column) (0, 0) and (1, 0); (2, 0) and the sketch's first 128
+  // columns; (3, 0) and its other 128; (2, 1) and (3, 1).
+  int grow, gn, ra, rb, row0, col0;
+  bool gom = false, is_w = tile >= g.ntri, live;
+  if (!is_w) {
+    int ti, tj;
+    tri_at(tile, ti, tj);
+    const bool diag = ti == tj;
+    const int r = (0x31012320 >> (4 * wave)) & 3, c = (0xE8 >> wave) & 1;
+    gom = diag && wave == 4;
+    grow = gom ? 0 : (wave < 4 ? ti : tj) * 256 + (wave & 3) * 64;
+    gn = gom ? S : wave < 4 || !diag ? I - grow : 0;
+    ra = r * 64;
+    rb = (diag ? 0 : 256) + c * 128;
+    row0 = ti * 256 + r * 64;
+    col0 = tj * 256 + c * 128;
+    live = row0 < I;
+    if (diag && (wave == 5 || wave == 6)) {
+      is_w = true;
+      ra = 256;
+      rb = (wave - 5) * 128;
+      row0 = 0;
+      col0 = tj * 256 + rb;
+      live = S > 0 && col0 < I;
+    }
+  } else {
+    const int w = tile - g.ntri, sg = w / g.nw, cg = w % g.nw;
+    gom = wave < 2;
+    grow = gom ? GROUP + sg * WIDE_WROWS + wave * 64 : cg * WIDE_WCOLS + (wave - 2) * 64;
+    gn = (gom ? S : I) - grow;
+    ra = (wave & 1) * 64;
+    rb = 128 + (wave >> 1) * 128;
+    row0 = GROUP + sg * WIDE_WROWS + ra;
+    col0 = cg * WIDE_WCOLS + (wave >> 1) * 128;
+    live = wave < 6 && row0 < S && col0 < I;
+  }
+
+  // staging: 16-byte pieces of rows lane / 4 + 16 j, or (GATHER, mode rows) 16
+  // values of row lane.  Rows past the end repeat the last one: their products
+  // are not wanted.  (A row, of more than 128 in a tensor that fits the card, is
+  // below 4 GB.)
+  const int last = gn < GROUP ? gn - 1 : GROUP - 1;
+  const uint32_t stride = (uint32_t)((gom ? g.J : g.B) * 4);
+  const char* base = (const char*)(gom ? g.omegaT : g.X) + (int64_t)grow * stride;
+  const int nk = GATHER ? (int)(g.nbt * g.B) : WIDE_K;
+  const bool gat = GATHER && !gom;
+  const int64_t kt0 = (int64_t)split * g.nkt / g.splits, kt1 = (int64_t)(split + 1) * g.nkt / g.splits;
+
+  uint32_t st[16];
+  int lo = 0;                      // values of st from which on they count
+  int64_t a, b0 = 0;
+  if (GATHER) {
+    a = kt0 * g.nbt;
+  } else {
+    a = kt0 / g.nbt;
+    b0 = (kt0 - a * g.nbt) * WIDE_K;
+  }
+  // load the K tile (a, b0) and step to the next
+  auto load = [&]() {
+    const int64_t at = GATHER ? a : b0, end = GATHER ? g.A - g.nbt : g.B - WIDE_K;
+    const int64_t from = at < end ? at : end;
+    lo = (int)(at - from) * (GATHER ? (int)g.B : 1);
+    const int64_t xoff = (GATHER ? from * g.I * g.B : a * g.I * g.B + from) * 4;
+    const int64_t ooff = (GATHER ? from * g.B : a * g.B + from) * 4;
+    asm volatile("" : "+v"(lane));   // addresses are formed anew each time: registers are short
+    if (gn > 0) {
+      if (gat) {
+        const char* p = base + xoff;
+        const uint32_t rbyte = (uint32_t)(lane < last ? lane : last) * stride;
+        int b = 0;
+#pragma unroll
+        for (int k = 0; k < WIDE_K; ++k) {
+          st[k] = k < nk ? *(const uint32_t*)(p + rbyte) : 0u;
+          // (the next K value: the next b, or the next a)
+          const bool wrap = ++b == (int)g.B;
+          p += wrap ? (g.I * g.B - g.B + 1) * 4 : 4;
+          b = wrap ? 0 : b;
+        }
+      } else {
+        const char* p = base + (gom ? ooff : xoff) + (lane & 3) * 16;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = (lane >> 2) + 16 * j;
+          const u32x4u_t v = *(const u32x4u_t*)(p + (uint64_t)(uint32_t)(r < last ? r : last) * stride);
+          st[4 * j] = v.x; st[4 * j + 1] = v.y; st[4 * j + 2] = v.z; st[4 * j + 3] = v.w;
+        }
+      }
+    }
+    if (GATHER) {
+      a += g.nbt;
+    } else {
+      b0 += WIDE_K;
+      if (b0 >= g.B) {
+        b0 = 0;
+        ++a;
+      }
+    }
+  };
+  auto store = [&](char* buf) {
+    if (gn <= 0) return;
+    if (lo > 0 || nk < WIDE_K) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int k = gat ? i : (lane & 3) * 4 + (i & 3);
+        if (k < lo || k >= nk) st[i] = 0;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      uint32_t h[4], m[4], l[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        split3(__uint_as_float(st[8 * j + 2 * i]), __uint_as_float(st[8 * j + 2 * i + 1]), h[i], m[i], l[i]);
+      if (gat) {
+        char* d = buf + j * WIDE_HALF + (wave * GROUP + lane) * 16;
+        *(uint4*)d = make_uint4(h[0], h[1], h[2], h[3]);
+        *(uint4*)(d + WIDE_PLANE) = make_uint4(m[0], m[1], m[2], m[3]);
+        *(uint4*)(d + 2 * WIDE_PLANE) = make_uint4(l[0], l[1], l[2], l[3]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          char* d = buf + ((lane >> 1) & 1) * WIDE_HALF + (wave * GROUP + (lane >> 2) + 16 * (2 * j + i)) * 16 + (lane & 1) * 8;
+          *(uint2*)d = make_uint2(h[2 * i], h[2 * i + 1]);
+          *(uint2*)(d + WIDE_PLANE) = make_uint2(m[2 * i], m[2 * i + 1]);
+          *(uint2*)(d + 2 * WIDE_PLANE) = make_uint2(l[2 * i], l[2 * i + 1]);
+        }
+      }
+    }
+  };
+
+  f32x16_t acc[2][4];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[m][n][v] = 0;
+  // operands: x of the wave's rows, y of 32 columns at a time (the next 32 read
+  // while these are used)
+  bf16x8_t x[2][3], y[2][3];
+  const int frag = (lane >> 5) * WIDE_HALF + (lane & 31) * 16;
+  const int fa = frag + ra * 16, fb = frag + rb * 16;
+  auto read_x = [&](const char* buf) {
+#pragma unroll
+    for (int q = 2; q >= 0; --q)
+#pragma unroll
+      for (int m = 0; m < 2; ++m) x[m][q] = *(const bf16x8_t*)(buf + fa + m * 512 + q * WIDE_PLANE);
+  };
+  auto read_y = [&](const char* buf, int n) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) y[n & 1][q] = *(const bf16x8_t*)(buf + fb + n * 512 + q * WIDE_PLANE);
+  };
+  auto products = [&](const char* buf, const char* ahead) {
+    f32x16_t t[2];
+    // the sum of the block before, a quarter between two products, so that it
+    // runs beside them (the order as written: the compiler would gather them)
+    auto add = [&](int blk, int quarter) {
+      if (blk < 0) return;
+#pragma unroll
+      for (int v = 4 * quarter; v < 4 * quarter + 4; ++v) acc[blk & 1][blk >> 1][v] += t[blk & 1][v];
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int blk = 0; blk < 8; ++blk) {
+      const int n = blk >> 1, m = blk & 1;
+      if (m == 0 && n < 3) read_y(buf, n + 1);
+      const bf16x8_t(&c)[3] = y[n & 1];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) t[m][v] = 0;
+      t[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][2], c[0], t[m], 0, 0, 0);
+      t[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][0], c[2], t[m], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      add(blk - 1, 0);
+      t[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][1], c[1], t[m], 0, 0, 0);
+      add(blk - 1, 1);
+      t[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][1], c[0], t[m], 0, 0, 0);
+      add(blk - 1, 2);
+      t[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][0], c[1], t[m], 0, 0, 0);
+      add(blk - 1, 3);
+      t[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[m][0], c[0], t[m], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    read_x(ahead);
+    read_y(ahead, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) add(7, q);
+  };
+
+  // K tile kt is formed from one buffer while kt + 2 is put into another and
+  // kt + 3 is on its way; kt + 1 is complete, so its first operands are read
+  // before the barrier.  Of the two waves of a SIMD one splits and stores before
+  // its products and one after them, so that the matrix core and the vector unit
+  // work at the same time.
+  const int64_t nt = kt1 - kt0;
+  if (nt > 0) {
+    load();
+    store(lds);
+    if (nt > 1) {
+      load();
+      store(lds + WIDE_BUF);
+    }
+    if (nt > 2) load();
+  }
+  __syncthreads();
+  read_x(lds);
+  read_y(lds, 0);
+  int cur = 0;
+  for (int64_t kt = 0; kt < nt; ++kt) {
+    const int ahead = cur == 2 * WIDE_BUF ? 0 : cur + WIDE_BUF;
+    const int next = ahead == 2 * WIDE_BUF ? 0 : ahead + WIDE_BUF;
+    auto stage = [&]() {
+      if (kt + 2 < nt) store(lds + next);
+      if (kt + 3 < nt) load();
+    };
+    if (wave < 4) stage();
+    if (live) products(lds + cur, lds + ahead);
+    if (wave >= 4) stage();
+    __syncthreads();
+    cur = ahead;
+  }
+
+  if (!live) return;
+  const int nb = (I + BLK - 1) / BLK;
+  float* part = (float*)g.partial + (int64_t)split * g.blocks * (BLK * BLK);
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int r = row0 + 32 * m, c = col0 + 32 * n;
+      if (r >= (is_w ? S : I) || c >= I || (!is_w && r < c)) continue;
+      const int bi = r / BLK, bj = c / BLK;
+      float* out = part + (int64_t)(is_w ? nb * (nb + 1) / 2 + bi * nb + bj : bi * (bi + 1) / 2 + bj) * (BLK * BLK);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) out[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * BLK + (lane & 31)] = acc[m][n][v];
+    }
+}
+
 // Sum the split-K partials in a fixed order: C (I x I, both triangles) and
 // W^T (S x I), float64.  64 consecutive values of a block per workgroup, the
 // splits dealt to 16 groups of lanes whose sums are added in order, so that a
@@ -587,7 +860,8 @@ static size_t partial_limit(int elem, int64_t A, int64_t I, int64_t B, int S, in
   int64_t splits = std::min(std::max<int64_t>(ceil_div(2 * (int64_t)cu_count, tiles), 1), std::max<int64_t>(nkt / 8, 1));
   if (splits >= 8) splits = (splits + 7) / 8 * 8;
   splits = std::min(splits, std::max<int64_t>(nkt, 1));
-  return (size_t)(splits * tiles) * 128 * 128 * (elem == E_F64 ? 8 : 4);
+  const size_t more = elem == E_F32 && A * I * B >= ((int64_t)1 << 26) ? (size_t)16 << 20 : 0;
+  return (size_t)(splits * tiles) * 128 * 128 * (elem == E_F64 ? 8 : 4) + more;
 }
 
 GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch) {
@@ -598,13 +872,32 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   g.J = A * B;
   g.S = S;
   g.thin = I <= GROUP && S <= GROUP;
-  g.nt = (int)ceil_div(I, 128);
-  g.ntri = g.thin ? 1 : g.nt * (g.nt + 1) / 2;
-  g.nw = (int)ceil_div(I, 256);
-  g.ntiles = g.thin ? 1 : g.ntri + (int)ceil_div(S, GROUP) * g.nw;
+  auto tiles = [&](bool wide) {
+    g.wide = wide;
+    g.nt = (int)ceil_div(I, wide ? 256 : 128);
+    g.ntri = g.nt * (g.nt + 1) / 2;
+    g.nw = (int)ceil_div(I, wide ? WIDE_WCOLS : 256);
+    const int wrows = wide ? (int)ceil_div(std::max(S - GROUP, 0), WIDE_WROWS) : (int)ceil_div(S, GROUP);
+    g.ntiles = g.ntri + wrows * g.nw;
+  };
+  tiles(true);
+  const double wide = g.ntri + 0.6 * (g.ntiles - g.ntri);
+  tiles(false);
+  if (g.thin) {
+    g.ntri = g.ntiles = 1;
+  } else if (elem == E_F32 && (B < WIDE_K ? 2.4 * wide + 0.8 : 3.1 * wide + 1.2) < g.ntiles) {
+    // The wide form where its tiles take less time than the others' count of
+    // their own.  A wide tile takes the time of 2.9 to 3.4 of 128 rows (2.4 where
+    // the rows run across the lanes, whose K values the narrow form stages by
+    // single words), one of the sketch alone 0.6 of that; over 1.2 (0.8) for the
+    // longer pipeline.  Measured (us, wide / 128 rows, S = 15, I^3): 192 36 / 33,
+    // 256 67 / 58, 384 252 / 228, 448 424 / 531, 512 580 / 658; last mode 224
+    // 52 / 66, 384 268 / 301, 512 643 / 939; 1000^3, S = 60, 7.3 ms / 12.9.
+    tiles(true);
+  }
   const int nb = (int)ceil_div(I, BLK);
   g.blocks = nb * (nb + 1) / 2 + (int)ceil_div(S, BLK) * nb;
-  const int kt = gram_kt(elem);
+  const int kt = g.wide ? WIDE_K : gram_kt(elem);
   g.gather = B < kt;
   g.nbt = g.gather ? std::min(kt / B, A) : ceil_div(B, kt);
   g.nkt = g.gather ? ceil_div(A, g.nbt) : A * g.nbt;
@@ -621,7 +914,7 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   for (int64_t s = 1; s <= std::min<int64_t>(g.nkt, 8 * (int64_t)cu_count); ++s) {
     if (s > 1 && (size_t)s * g.blocks * BLK * BLK * (elem == E_F64 ? 8 : 4) > limit) break;
     const int64_t n = ceil_div(g.ntiles * s, cu_count);
-    const double share = g.thin ? 4.0 * (double)ceil_div(n, 4) : (double)n + (n & 1 ? 0.6 : 0.0);
+    const double share = g.wide ? 1.2 * (double)n : g.thin ? 4.0 * (double)ceil_div(n, 4) : (double)n + (n & 1 ? 0.6 : 0.0);
     const double cost = share * ((double)ceil_div(g.nkt, s) + 6.0) + per * s / 7.5e6;
     if (best < 0 || cost < best) {
       best = cost;
@@ -642,8 +935,15 @@ static hipError_t launch_tiles(const GramArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <bool GATHER>
+static hipError_t launch_wide(const GramArgs& g, hipStream_t s) {
+  hipLaunchKernelGGL(gram_wide_kernel<GATHER>, dim3((unsigned)(g.ntiles * g.splits)), dim3(512), 0, s, g);
+  return hipGetLastError();
+}
+
 template <int E>
 static hipError_t launch_gram(const GramArgs& g, hipStream_t s) {
+  if (g.wide) return g.gather ? launch_wide<true>(g, s) : launch_wide<false>(g, s);
   if (g.thin) return g.gather ? launch_tiles<E, true, GROUPS_THIN>(g, s) : launch_tiles<E, false, GROUPS_THIN>(g, s);
   return g.gather ? launch_tiles<E, true, GROUPS_TILE>(g, s) : launch_tiles<E, false, GROUPS_TILE>(g, s);
 }
