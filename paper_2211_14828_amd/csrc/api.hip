@@ -388,6 +388,8 @@ struct Buffers {
   int* used = nullptr;       // per mode, q + 2 slots: directions kept by blocks 0..j-1
   double* Ut64[8] = {};
   void* Uop = nullptr;     // one factor in a product element type
+  void* Urow[8] = {};        // per mode, or null: U^T and U in the core chain's element type
+  void* Ucol[8] = {};        //   (see factor_copies), made with the factors
   void* chainA = nullptr;
   void* chainB = nullptr;
   void* gkeep = nullptr;   // the core, kept apart from the reconstruction chain
@@ -861,13 +863,47 @@ rbki_status factor_one(const Plan& P, const Buffers& b, int n, hipStream_t st) {
   return RBKI_OK;
 }
 
+FinishJob finish_job(double* Ut, int64_t R, int64_t I) {
+  FinishJob f = {};
+  f.Ut = Ut;
+  f.R = R;
+  f.I = I;
+  return f;
+}
+
+// Where the product operands of the factors are kept from run_factors on, for plans
+// with a chain set per mode: its Y, which no later step reads (U^T in float64 is the
+// operand itself).  In other plans each is made when it is used.
+void factor_copies(const Plan& P, Buffers& b) {
+  if (b.chain_lanes < P.N) return;
+  for (int n = 0; n < P.N; ++n) {
+    const int64_t ri = P.m[n].R * P.m[n].I;
+    if (ri > P.maxS * P.maxI) continue;
+    char* y = (char*)b.ln[n].Yt;
+    b.Urow[n] = P.celem == E_F64 ? (void*)b.Ut64[n] : (void*)y;
+    b.Ucol[n] = P.celem == E_F64 ? y : y + ri * 4;
+  }
+}
+
+// U^T (R x I) and U (I x R) of mode n as operands of element type elem.
+rbki_status operand_rows(const Plan& P, const Buffers& b, int n, int elem, const void** op, hipStream_t st) {
+  *op = b.Urow[n] && elem == P.celem ? b.Urow[n] : b.Uop;
+  if (*op == b.Uop) HIPCHK(convert_tensor(E_F64, b.Ut64[n], elem, b.Uop, P.m[n].R * P.m[n].I, st));
+  return RBKI_OK;
+}
+rbki_status operand_cols(const Plan& P, const Buffers& b, int n, const void** op, hipStream_t st) {
+  *op = b.Ucol[n] ? b.Ucol[n] : b.Uop;
+  if (*op == b.Uop) HIPCHK(store_factor(b.Ut64[n], P.m[n].R, P.m[n].I, b.Uop, P.celem, st));
+  return RBKI_OK;
+}
+
 // Alg. 2, steps 4-5 for mode n alone, on the caller's stream (the stages of
 // the sequential form): the R leading eigenpairs of Z (the Jacobi solver
 // beyond that solver's sizes), U^T = Vt(1:R, :) Q^T, sign rule.
-rbki_status factor_single(const Plan& P, const Buffers& b, int n, hipStream_t st, int64_t width = 0) {
+rbki_status factor_single(const Plan& P, const Buffers& b, int n, const FinishJob& fin, hipStream_t st) {
   const ModeGeom& g = P.m[n];
   const double* Z = b.Z[n];
-  int64_t sn = width > 0 ? width : g.Sp, rn = g.R;
+  int64_t sn = g.Sp, rn = g.R;
   double* lam = b.lam[n];
   double* Vt = b.Vt[n];
   void* w = b.jwork[n];
@@ -881,15 +917,17 @@ rbki_status factor_single(const Plan& P, const Buffers& b, int n, hipStream_t st
     }
   }
   HIPCHK(dgemm(0, 0, g.R, g.I, sn, 1.0, b.Vt[n], sn, b.Qt[n], g.I, 0.0, b.Ut64[n], g.I, st));
-  HIPCHK(canonical_sign_rows(b.Ut64[n], g.R, g.I, st));
+  HIPCHK(finish_factors(&fin, 1, st));
   return RBKI_OK;
 }
 
 // Alg. 2, steps 4-5 for all modes: the R leading eigenvectors of every Z in
 // one launch (tridiagonal reduction, bisection, inverse iteration; block
 // Jacobi for matrices beyond that solver's sizes), then U^T = Vt(1:R, :) Q^T
-// with the sign rule.
-rbki_status run_factors(const Plan& P, const Buffers& b, hipStream_t st) {
+// with the sign rule.  width: the order of each Z (null: S'), factors: where the
+// caller's go (null: nowhere yet).
+rbki_status run_factors(const Plan& P, const Buffers& b, const int64_t* width, void* const* factors, int out_type,
+                        hipStream_t st) {
   const double* Zs[8];
   int64_t ns[8], rs[8];
   double* ls[8];
@@ -899,7 +937,7 @@ rbki_status run_factors(const Plan& P, const Buffers& b, hipStream_t st) {
   bool top = true;
   for (int n = 0; n < P.N; ++n) {
     Zs[n] = b.Z[n];
-    ns[n] = P.m[n].Sp;
+    ns[n] = width ? width[n] : P.m[n].Sp;
     rs[n] = P.m[n].R;
     ls[n] = b.lam[n];
     vs[n] = b.Vt[n];
@@ -926,11 +964,20 @@ rbki_status run_factors(const Plan& P, const Buffers& b, hipStream_t st) {
   GemmJob job[8];
   for (int n = 0; n < P.N; ++n) {
     const ModeGeom& g = P.m[n];
-    job[n] = gemm_job(0, 0, g.R, g.I, g.Sp, 1.0, b.Vt[n], g.Sp, b.Qt[n], g.I, 0.0, b.Ut64[n], g.I);
+    job[n] = gemm_job(0, 0, g.R, g.I, ns[n], 1.0, b.Vt[n], ns[n], b.Qt[n], g.I, 0.0, b.Ut64[n], g.I);
   }
   HIPCHK(dgemm_batched(job, P.N, st));
   // sign rule: largest-magnitude entry of each factor column positive
-  for (int n = 0; n < P.N; ++n) HIPCHK(canonical_sign_rows(b.Ut64[n], P.m[n].R, P.m[n].I, st));
+  FinishJob fin[8];
+  for (int n = 0; n < P.N; ++n) {
+    fin[n] = finish_job(b.Ut64[n], P.m[n].R, P.m[n].I);
+    fin[n].rows = P.celem == E_F64 ? nullptr : b.Urow[n];
+    fin[n].cols = b.Ucol[n];
+    fin[n].rows_elem = fin[n].cols_elem = P.celem;
+    fin[n].out = factors ? factors[n] : nullptr;
+    fin[n].out_elem = dtype_elem(out_type);
+  }
+  HIPCHK(finish_factors(fin, P.N, st));
   return RBKI_OK;
 }
 
@@ -954,9 +1001,11 @@ rbki_status first_product(const Plan& P, const Buffers& b, const void* xsrc, hip
     ProfScope ps("ttm", st);
     HIPCHK(launch_ttm_padded(b.xpad, A, I, B, P.dims[P.N - 1], b.Uop, P.m[n].R, out, st));
   } else {
-    HIPCHK(convert_tensor(E_F64, b.Ut64[n], P.telem, b.Uop, P.m[n].R * I, st));
+    const void* U;
+    rbki_status s = operand_rows(P, b, n, P.telem, &U, st);
+    if (s != RBKI_OK) return s;
     ProfScope ps("ttm", st);
-    HIPCHK(launch_ttm(P.telem, xsrc, A, I, B, b.Uop, P.m[n].R, out, nullptr, 0, st));
+    HIPCHK(launch_ttm(P.telem, xsrc, A, I, B, U, P.m[n].R, out, nullptr, 0, st));
   }
   return RBKI_OK;
 }
@@ -980,9 +1029,11 @@ rbki_status reconstruct_error(const Plan& P, const Buffers& b, const void* X, in
     for (int k = 0; k < n; ++k) A *= cur[k];
     for (int k = n + 1; k < P.N; ++k) B *= cur[k];
     const int64_t R = P.m[n].R, I = P.m[n].I;
-    HIPCHK(store_factor(b.Ut64[n], R, I, b.Uop, P.celem == E_F64 ? E_F64 : E_F32, st));
+    const void* U;
+    rbki_status s = operand_cols(P, b, n, &U, st);
+    if (s != RBKI_OK) return s;
     void* dst = bufs[wsrc ^ 1];
-    HIPCHK(launch_ttm(P.celem, src, A, R, B, b.Uop, I, dst, nullptr, 0, st));
+    HIPCHK(launch_ttm(P.celem, src, A, R, B, U, I, dst, nullptr, 0, st));
     src = dst;
     wsrc ^= 1;
     cur[n] = I;
@@ -990,10 +1041,12 @@ rbki_status reconstruct_error(const Plan& P, const Buffers& b, const void* X, in
   // residual over X_(0) with U^(1)
   {
     const int64_t I0 = P.dims[0], J0 = P.T / P.dims[0], R0 = P.m[0].R;
-    HIPCHK(convert_tensor(E_F64, b.Ut64[0], P.celem, b.Uop, R0 * I0, st));
+    const void* U;
+    rbki_status s = operand_rows(P, b, 0, P.celem, &U, st);
+    if (s != RBKI_OK) return s;
     ProfScope ps("error", st);
     // precision forms: U H from split bfloat16 operands, x and the sums exact
-    HIPCHK(launch_residual(P.xelem, X, P.celem, b.Uop, src, I0, J0, R0, sums, b.rpartial, 0, st, P.need_pad));
+    HIPCHK(launch_residual(P.xelem, X, P.celem, U, src, I0, J0, R0, sums, b.rpartial, 0, st, P.need_pad));
   }
   HIPCHK(hipMemcpyAsync(sums_host, sums, 16, hipMemcpyDeviceToHost, st));
   return RBKI_OK;
@@ -1007,8 +1060,10 @@ rbki_status chain_product(const Plan& P, const Buffers& b, int n, int64_t* cur, 
   for (int k = n + 1; k < P.N; ++k) B *= cur[k];
   const int64_t I = cur[n];
   void* bufs[2] = {b.chainA, b.chainB};
-  HIPCHK(convert_tensor(E_F64, b.Ut64[n], P.celem, b.Uop, P.m[n].R * I, st));
-  HIPCHK(launch_ttm(P.celem, bufs[which], A, I, B, b.Uop, P.m[n].R, bufs[which ^ 1], nullptr, 0, st));
+  const void* U;
+  rbki_status s = operand_rows(P, b, n, P.celem, &U, st);
+  if (s != RBKI_OK) return s;
+  HIPCHK(launch_ttm(P.celem, bufs[which], A, I, B, U, P.m[n].R, bufs[which ^ 1], nullptr, 0, st));
   which ^= 1;
   cur[n] = P.m[n].R;
   return RBKI_OK;
@@ -1469,13 +1524,17 @@ rbki_status sequential_enqueue(const void* X, const rbki_params* prm, int xtype,
     HIPCHK(fill_zero(bn.info, counters_bytes(Pn), st));
     s = run_mode(Pn, bn, 0, src, n, true, st);
     if (s != RBKI_OK) return s;
-    s = factor_single(Pn, bn, n, st);
-    if (s != RBKI_OK) return s;
     const ModeGeom& g = Pn.m[n];
-    HIPCHK(copy_rows_f64(fac[n], g.I, bn.Ut64[n], g.I, g.R, g.I, st));
+    FinishJob fin = finish_job(bn.Ut64[n], g.R, g.I);
+    fin.copy = fac[n];
+    fin.rows = bn.Uop;
+    fin.rows_elem = src_elem;
+    fin.out = factors ? factors[n] : nullptr;
+    fin.out_elem = dtype_elem(out_type);
+    s = factor_single(Pn, bn, n, fin, st);
+    if (s != RBKI_OK) return s;
     HIPCHK(hipMemcpyAsync(info + 2 * n, bn.info + 2 * n, 2 * sizeof(int), hipMemcpyDeviceToDevice, st));
     // Y_n = Y_{n-1} x_n U^(n)T, in float32 (float64 for a float64 X)
-    HIPCHK(convert_tensor(E_F64, fac[n], src_elem, bn.Uop, g.R * g.I, st));
     void* dst = ybuf[n & 1];
     {
       ProfScope ps("ttm", st);
@@ -1488,9 +1547,6 @@ rbki_status sequential_enqueue(const void* X, const rbki_params* prm, int xtype,
   int64_t nc = 1;
   for (int n = 0; n < P0.N; ++n) nc *= P0.ranks[n];
   if (core) HIPCHK(convert_tensor(L.yelem, src, dtype_elem(out_type), core, nc, st));
-  for (int n = 0; n < P0.N; ++n)
-    if (factors && factors[n])
-      HIPCHK(store_factor(fac[n], P0.m[n].R, P0.m[n].I, factors[n], dtype_elem(out_type), st));
   void* gk = ws + L.gkeep;
   HIPCHK(convert_tensor(L.yelem, src, P0.celem, gk, nc, st));
   if (core_chain) *core_chain = gk;
@@ -1620,6 +1676,7 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
     s = krylov_block0(P, b, ms, st);
     if (s != RBKI_OK) return s;
   }
+  factor_copies(P, b);
   HostResult hr;
   double fit_prev = 0.0, err = 0.0;
   int t = 0;
@@ -1663,16 +1720,17 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
       s = step(ms, 0);
       if (s != RBKI_OK) return s;
     }
+    int64_t width[8];
     for (int n = 0; n < P.N; ++n) {
-      if (!P.fused && !P.together) {
-        ModeSet one;
-        one.add(n, 0);
-        s = step(one, n);
-        if (s != RBKI_OK) return s;
-      }
-      s = factor_single(P, b, n, st, P.m[n].S * (t + 1));
+      width[n] = P.m[n].S * (t + 1);
+      if (P.fused || P.together) continue;
+      ModeSet one;
+      one.add(n, 0);
+      s = step(one, n);
       if (s != RBKI_OK) return s;
     }
+    s = run_factors(P, b, width, nullptr, out_type, st);
+    if (s != RBKI_OK) return s;
     void* gk = nullptr;
     s = run_core_and_error(P, b, X, X, nullptr, dtype_elem(out_type), true, hr.sums, &gk, st);
     if (s != RBKI_OK) return s;
@@ -1739,10 +1797,11 @@ static rbki_status tucker_impl(const void* X, int xtype, const rbki_params* prm,
   s = run_modes(P, b, xsrc, st, inline_factors, &chain_done);
   if (s != RBKI_OK) return s;
   if (!inline_factors) {
-    s = run_factors(P, b, st);
+    factor_copies(P, b);
+    s = run_factors(P, b, nullptr, factors, out_type, st);
     if (s != RBKI_OK) return s;
   }
-  for (int n = 0; n < P.N; ++n)
+  for (int n = 0; inline_factors && n < P.N; ++n)
     if (factors && factors[n])
       HIPCHK(store_factor(b.Ut64[n], P.m[n].R, P.m[n].I, factors[n], dtype_elem(out_type), st));
   HostResult local;

@@ -206,6 +206,19 @@ hipError_t store_factor(const double* Ut /* R x I */, int64_t R, int64_t I, void
 hipError_t fill_zero(void* p, size_t bytes, hipStream_t st);
 // Flip each row of V (rows x n) so its largest-magnitude entry is positive.
 hipError_t canonical_sign_rows(double* V, int64_t rows, int64_t n, hipStream_t st);
+// The sign rule on the rows of U^T (R x I, float64, in place) and the copies of the
+// result that are not null: U^T in float64, U^T and U (I x R) as product operands,
+// U for the caller.
+struct FinishJob {
+  double* Ut;
+  int64_t R, I;
+  double* copy;
+  void* rows;
+  void* cols;
+  void* out;
+  int rows_elem, cols_elem, out_elem;
+};
+hipError_t finish_factors(const FinishJob* jobs, int njobs, hipStream_t st);
 
 // ------------------------------------------------------------ ttm.hip
 // Y[a, r, b] = sum_i U[i, r] X[a, i, b] for the view [A, I, B] of X;
