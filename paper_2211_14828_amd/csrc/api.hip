@@ -601,13 +601,15 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
   } else {
     // a sampled mode needs only C from the whole unfolding (for Z): no sketch
     const int Sf = g.sampled ? 0 : (int)S;
-    if (Sf) {
-      ProfScope ps("omega", st);
-      HIPCHK(launch_omega(P.gelem, P.seed, n, S * g.J, L.omegaT, st));
-    }
     GramArgs ga = gram_plan(P.gelem, g.A, g.I, g.B, Sf, cu_count(), (int)S);
     ga.X = xsrc;
     ga.omegaT = L.omegaT;
+    ga.seed = P.seed;
+    ga.om_mode = n;
+    if (Sf && !ga.gen) {
+      ProfScope ps("omega", st);
+      HIPCHK(launch_omega(P.gelem, P.seed, n, S * g.J, L.omegaT, st));
+    }
     ga.partial = L.partial;
     {
       ProfScope ps("gram", st);
@@ -622,13 +624,15 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
     // rows) from the gathered sample
     HIPCHK(launch_sample_columns(P.seed, n, g.J, g.m, L.cols, st));
     HIPCHK(launch_gather_columns(P.xelem, xsrc, I, g.B, L.cols, g.m, g.yelem, L.ysmp, st));
-    {
-      ProfScope ps("omega", st);
-      HIPCHK(launch_omega(g.yelem, P.seed, n, S * g.m, L.omegaT, st));
-    }
     GramArgs gy = gram_plan(g.yelem, 1, I, g.m, (int)S, cu_count());
     gy.X = L.ysmp;
     gy.omegaT = L.omegaT;
+    gy.seed = P.seed;
+    gy.om_mode = n;
+    if (!gy.gen) {
+      ProfScope ps("omega", st);
+      HIPCHK(launch_omega(g.yelem, P.seed, n, S * g.m, L.omegaT, st));
+    }
     gy.partial = L.partial;
     {
       ProfScope ps("gram_sample", st);

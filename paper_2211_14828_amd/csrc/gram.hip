@@ -46,8 +46,10 @@
 // of X, run on one XCD (or two) and the slab is fetched from HBM once into its
 // L2, for any number of splits.
 // Measured per mode, against 128 x 128 tiles on the MFMA of the operand's own
-// type: float32 64^5, S = 22, 1.55 ms (2.75; 2.8 TB/s of X); float64 200^3,
-// S = 15, 0.11 ms (0.22).
+// type: float32 64^5, S = 22, 1.55 ms (2.75), and 2.05 with the sketch made in place
+// (below; 2.1 apart, 0.55 of it the sketch's own kernel, and the read of the sketch:
+// the vector unit is busy for four fifths of it, two thirds of that on the sketch);
+// float64 200^3, S = 15, 0.11 ms (0.22).
 //
 // Large float32 modes take the wide form below (gram_wide_kernel), modes of at most
 // eight rows a form of their own (gram_tiny_kernel).
@@ -212,6 +214,40 @@ __device__ inline void store_piece(Piece r, char* lds, int plane, int grow, cons
   }
 }
 
+// Sketch values made in place (the thin float32 form, whose one tile reads each of
+// them once; the other forms' tiles would make them several times over, and the
+// float64 pair takes more registers than the thin form has): the tile's S rows of KT values, as the stream's pairs, thread by thread
+// from thread index tid on.  When a row starts at an odd index of the stream (J or
+// the tile's offset o odd) its pairs straddle the words of a row, and there is one
+// more of them.  (A loop: pairs side by side would take the products' registers.)
+__device__ inline void store_sketch(const GramArgs& g, char* lds, int plane, int64_t o, int tid) {
+  constexpr int E = E_F32, KT = Op<E>::KT;
+  const bool odd = (g.J | o) & 1;
+  const int per = KT / 2 + (odd ? 1 : 0), np = g.S * per;
+#pragma unroll 1
+  for (int p = tid; p < np; p += 256) {
+    const int row = odd ? p / (KT / 2 + 1) : p / (KT / 2);
+    const int64_t L = row * g.J + o;
+    const int64_t m = (L >> 1) + (p - row * per);
+    const int k = 2 * (p - row * per) - (int)(L & 1);     // K value of the pair's first
+    float z0, z1;
+    gauss_pair_f32((uint64_t)m, (uint32_t)g.om_mode, 0u, g.seed, z0, z1);
+    uint32_t part[3];
+    split3(z0, z1, part[0], part[1], part[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      char* d = lds + q * plane;
+      if (!odd) {
+        *(uint32_t*)(d + lds_at<E>(GROUP + row, k >> 3) + (k & 7) * 2) = part[q];
+      } else {
+        if (k >= 0 && k < KT) *(uint16_t*)(d + lds_at<E>(GROUP + row, k >> 3) + (k & 7) * 2) = (uint16_t)part[q];
+        if (k + 1 < KT)
+          *(uint16_t*)(d + lds_at<E>(GROUP + row, (k + 1) >> 3) + ((k + 1) & 7) * 2) = (uint16_t)(part[q] >> 16);
+      }
+    }
+  }
+}
+
 // One K tile of a wave's MB x 2 blocks: rows ra + .., columns rb + .. of the
 // staged rows; bit 2 m + n of mask: 32 x 32 block (m, n) is wanted.
 template <int E, int MB>
@@ -293,6 +329,7 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
   constexpr int plane = NG * GROUP * 64;           // float32: bytes of one part's rows
   constexpr int MB = NG == GROUPS_THIN ? 1 : 2;    // block rows of a wave
   constexpr int NACC = O::NACC * MB;
+  constexpr bool GEN = NG == GROUPS_THIN && E == E_F32;   // the sketch is made here
   const T* X = (const T*)g.X;
   const T* Om = (const T*)g.omegaT;
 
@@ -315,7 +352,7 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
   const int I = (int)g.I, S = g.S;
   if constexpr (NG == GROUPS_THIN) {
     grow[0] = 0; gn[0] = I; gom[0] = false;
-    grow[1] = 0; gn[1] = S; gom[1] = true;
+    grow[1] = 0; gn[1] = GEN ? 0 : S; gom[1] = true;
     is_w = wave >= 2;
     ra = 32 * wave;
     rb = 0;
@@ -438,6 +475,9 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
 #pragma unroll
     for (int v = 0; v < (E == E_F64 ? 4 : 16); ++v) acc[i][v] = 0;
 
+  // (the pairs start at another wave from split to split: there may be fewer than
+  // threads, and the waves of a SIMD would all have them)
+  const int stid = (int)(threadIdx.x + 64 * (split >> 3)) & 255;
   KTile now = {};
   if (kt0 < kt1) {
     now = tile_now();
@@ -450,6 +490,7 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
       if (GATHER && !gom[i]) store_piece<E, true>(st[i], lds, plane, i * GROUP, now);
       else store_piece<E, false>(st[i], lds, plane, i * GROUP, now);
     }
+    if constexpr (GEN) store_sketch(g, lds, plane, now.o, stid);
     __syncthreads();
     if (kt + 1 < kt1) {
       advance();
@@ -981,6 +1022,7 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   tiles(false);
   if (g.thin) {
     g.ntri = g.ntiles = 1;
+    g.gen = elem == E_F32 && S > 0;
   } else if (elem == E_F32 && (B < WIDE_K ? 2.4 * wide + 0.8 : 3.1 * wide + 1.2) < g.ntiles) {
     // The wide form where its tiles take less time than the others' count of
     // their own.  A wide tile takes the time of 2.9 to 3.4 of 128 rows (2.4 where
@@ -996,6 +1038,7 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   if (I <= TINY && S <= TINY) {
     // at least 4 chunks to a thread, at most 4 workgroups to a compute unit
     g.tiny = 1;
+    g.gen = 0;
     const int64_t v = B >= 16 / elem_size(elem) ? 16 / elem_size(elem) : 1;
     g.nbt = ceil_div(B, v);
     g.nkt = A * g.nbt;

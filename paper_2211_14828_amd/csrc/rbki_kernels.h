@@ -19,6 +19,8 @@ struct GramArgs {
   int blocks, gather;         // gram.hip: stored 32 x 32 blocks per split, K tiles of nbt values of a
   int xbase, xleft, grid;    // pipelined XCD map: whole splits per XCD, spare slots per XCD, workgroups
   int thin;                 // I <= 64, S <= 64: one tile of the mode's and the sketch's rows (gram.hip)
+  int gen, om_mode;         // gram.hip: the sketch is made by the kernel (set seed and om_mode, not omegaT)
+  uint64_t seed;
   int tiny;                 // I <= 8, S <= 8: products in registers (gram.hip)
   int wide;                 // float32: 256 x 256 tiles (gram.hip)
   void* partial;            // [splits][blocks][32*32] float (double for fp64), gram.hip

@@ -29,7 +29,7 @@ __host__ __device__ inline void mulhilo32(uint32_t a, uint32_t b, uint32_t& hi, 
   lo = (uint32_t)p;
 }
 
-__host__ __device__ inline PhiloxOut philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+__device__ inline PhiloxOut philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                    uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
@@ -40,8 +40,8 @@ __host__ __device__ inline PhiloxOut philox4x32_10(uint32_t c0, uint32_t c1, uin
     uint32_t hi0, lo0, hi1, lo1;
     mulhilo32(0xD2511F53u, c0, hi0, lo0);
     mulhilo32(0xCD9E8D57u, c2, hi1, lo1);
-    uint32_t n0 = hi1 ^ c1 ^ k0;
-    uint32_t n2 = hi0 ^ c3 ^ k1;
+    uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);   // a ^ b ^ c
+    uint32_t n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
     c0 = n0;
     c1 = lo1;
     c2 = n2;
