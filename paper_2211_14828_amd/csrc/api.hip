@@ -143,8 +143,7 @@ struct Plan {
   double rate = 1.0;         // column sampling rate omega (Sec. 3.1)
   bool sequential = false;   // sequential truncation (ST-HOSVD form)
   bool one_stream = false;   // every mode on the caller's stream (no helper streams)
-  bool fused = false;        // every mode's Krylov chain in one persistent launch (small modes)
-  bool together = false;     // larger modes: every mode's chain step in one launch
+  bool together = false;     // every mode's chain step in one launch
   bool any_sampled = false;
   int64_t maxM = 0;          // largest column sample
   size_t ybytes = 0;         // largest gathered sample
@@ -320,10 +319,6 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
     if (n != P.first_mode) { cur[n] = P.ranks[n]; mx = std::max(mx, prod(cur)); }
   for (int n = 1; n < P.N; ++n) { cur[n] = P.dims[n]; mx = std::max(mx, prod(cur)); }
   P.chain_elems = mx;
-  // small modes: the Krylov chains (Alg. 1 after the Gram pass, and Z) of
-  // all modes in one launch, one workgroup per mode
-  P.fused = !P.any_sampled;
-  for (int n = 0; n < P.N; ++n) P.fused = P.fused && krylov_chain_ok(P.m[n].I, P.m[n].S);
   P.together = plan_together(P);
   return RBKI_OK;
 }
@@ -378,7 +373,7 @@ struct Buffers {
   void* u16 = nullptr;     // the first product's factor as bf16 [64][block rows]
   Lane ln[8];
   int lanes = 1;             // scratch sets of concurrently running modes
-  int chain_lanes = 1;       // scratch sets of the Krylov chains (one per mode in a fused plan)
+  int chain_lanes = 1;       // scratch sets of the Krylov chains (one per mode when they run in step)
   double* Qt[8] = {};      // per mode: S'_n x I_n basis rows
   double* Z[8] = {};       // per mode: S'_n x S'_n
   double* lam[8] = {};
@@ -416,19 +411,28 @@ void carve_chain(const Plan& P, Arena& ar, Lane& L) {
   L.Ytmp = (double*)ar.take((size_t)P.maxS * P.maxI * 8);
   L.Pm = (double*)ar.take((size_t)P.maxS * P.maxSp * 8);
   L.G = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
-  if (P.fused) return;                        // the persistent chain needs no more
   L.L = (double*)ar.take((size_t)P.maxS * P.maxS * 8);
   L.flags = (int*)ar.take((size_t)P.maxSp * 4);
   L.ref2 = (double*)ar.take((size_t)P.maxS * 8);
   if (P.any_sampled) L.CY = (double*)ar.take((size_t)P.maxI * P.maxI * 8);
 }
 
-// Modes too large for the persistent chain whose chains can still run in step,
-// one launch for a step of all of them: those of a plan with one scratch set
-// (large tensors have a set and a stream per mode instead), as long as the
-// other modes' chain buffers stay within kChainSpare.
+// Modes whose Krylov chains run in step, one launch for a step of all of them:
+// those of a plan with one scratch set (large tensors have a set and a stream per
+// mode instead), as long as the other modes' chain buffers stay within kChainSpare;
+// and small modes always, whose chains, a few launches of 2 to 10 us a step, would
+// wait behind the next mode's Gram workgroups on a stream of their own (64^5, ring:
+// 17.7 ms against 16.0).  (A persistent kernel, one workgroup a mode, ran the small
+// modes' chains before: bound by one compute unit's matrix cores and its caches'
+// latency, 293 us against 130 at 200^3, S = 15, two steps; at 16 to 64 rows and S = 8
+// they were within 5% of each other, and from S = 15 on the launches are faster.)
+constexpr int64_t kSmallMode = 256, kSmallSketch = 64;
 bool plan_together(const Plan& P) {
-  if (P.fused || mode_lanes(P) > 1 || P.N < 2) return false;
+  bool small = !P.any_sampled;
+  for (int n = 0; n < P.N; ++n) small = small && P.m[n].I <= kSmallMode && P.m[n].S <= kSmallSketch;
+  if (P.N < 2) return false;
+  if (small) return true;
+  if (mode_lanes(P) > 1) return false;
   Arena ar(nullptr, 0);
   Lane L;
   for (int n = 1; n < P.N; ++n) carve_chain(P, ar, L);
@@ -450,13 +454,13 @@ void carve(const Plan& P, Arena& ar, Buffers& b) {
     }
   }
   b.lanes = mode_lanes(P);
-  b.chain_lanes = P.fused || P.together ? std::max(b.lanes, P.N) : b.lanes;
+  b.chain_lanes = P.together ? std::max(b.lanes, P.N) : b.lanes;
   for (int l = 0; l < b.chain_lanes; ++l) {
     Lane& L = b.ln[l];
     if (l >= b.lanes) {
-      // the extra sets of a fused plan or of modes that run together: chain
-      // buffers of their own; the sketch and Gram scratch of set 0 (those
-      // passes run one after the other)
+      // the extra sets of modes whose chains run in step: chain buffers of
+      // their own; the sketch and Gram scratch of set 0 (those passes run one
+      // after the other)
       L = b.ln[0];
       carve_chain(P, ar, L);
       continue;
@@ -740,6 +744,7 @@ rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int 
 // Alg. 2, steps 2-3 of the modes after run_mode_heavy: the Krylov bases from C
 // and W in the scratch sets, and Z.
 rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, bool with_factor, hipStream_t st) {
+  ProfScope ps("chain", st);
   dgemm_set_scratch(b.ln[ms.lane[0]].dscratch, kDgemmScratch);
   const double* Ck[8];
   double* CQ[8];
@@ -800,48 +805,10 @@ rbki_status run_mode_chain(const Plan& P, const Buffers& b, int lane, int n, boo
   return run_mode_chains(P, b, ms, with_factor, st);
 }
 
-// The persistent chain of mode n on scratch set `lane` (fused plans): blocks
-// j0..j1 of the basis, then Z over its first zr rows (zr = 0: no Z).
-ChainJob chain_job(const Plan& P, const Buffers& b, int lane, int n, int zr) {
-  const Lane& L = b.ln[lane];
-  const ModeGeom& g = P.m[n];
-  ChainJob j;
-  j.C = L.C;
-  j.Yt = L.Yt;
-  j.Ytmp = L.Ytmp;
-  j.Pm = L.Pm;
-  j.G = L.G;
-  j.CQ = L.CQt;
-  j.Qt = b.Qt[n];
-  j.Z = b.Z[n];
-  j.used = b.used + (size_t)n * (P.q + 2);
-  j.I = (int)g.I;
-  j.S = (int)g.S;
-  j.zr = zr;
-  return j;
-}
-
-rbki_status run_chains(const Plan& P, const ChainJob* jobs, int njobs, int j0, int j1, hipStream_t st) {
-  ChainArgs a = {};
-  a.power = P.power ? 1 : 0;
-  for (int i = 0; i < njobs; ++i) a.job[i] = jobs[i];
-  a.j0 = j0;
-  a.j1 = j1;
-  a.tau_rel = TAU_REL;
-  a.tau_abs = TAU_ABS;
-  ProfScope ps("chain", st);
-  HIPCHK(launch_krylov_chain(a, njobs, st));
-  return RBKI_OK;
-}
-
 rbki_status run_mode(const Plan& P, const Buffers& b, int lane, const void* xsrc, int n, bool with_factor,
                      hipStream_t st) {
   rbki_status s = run_mode_heavy(P, b, lane, xsrc, n, st);
   if (s != RBKI_OK) return s;
-  if (P.fused) {
-    const ChainJob j = chain_job(P, b, lane, n, with_factor ? (int)P.m[n].Sp : 0);
-    return run_chains(P, &j, 1, 0, P.q, st);
-  }
   return run_mode_chain(P, b, lane, n, with_factor, st);
 }
 
@@ -1347,19 +1314,9 @@ static hipStream_t lane_stream(int lane) {
 static rbki_status run_modes(const Plan& P, const Buffers& b, const void* xsrc, hipStream_t st,
                              bool inline_factors = false, int* chain_done = nullptr) {
   if (chain_done) *chain_done = 0;
-  if (P.fused) {
-    // the sketch and Gram passes one after the other, each into its mode's
-    // set, then every mode's Krylov chain in one launch
-    ChainJob jobs[8];
-    for (int n = 0; n < P.N; ++n) {
-      rbki_status s = run_mode_heavy(P, b, n, xsrc, n, st);
-      if (s != RBKI_OK) return s;
-      jobs[n] = chain_job(P, b, n, n, (int)P.m[n].Sp);
-    }
-    return run_chains(P, jobs, P.N, 0, P.q, st);
-  }
   if (P.together) {
-    // the same with the larger modes' chains in step
+    // the sketch and Gram passes one after the other, each into its mode's set,
+    // then the modes' chains in step
     ModeSet ms;
     for (int n = 0; n < P.N; ++n) {
       rbki_status s = run_mode_heavy(P, b, n, xsrc, n, st);
@@ -1651,7 +1608,7 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
   ModeSet ms;
   for (int n = 0; n < P.N; ++n) {
     const ModeGeom& g = P.m[n];
-    if (P.fused || P.together) {
+    if (P.together) {
       // each mode's Gram pass into its own chain set, which keeps C and the
       // products C Q for every step
       s = run_mode_heavy(P, b, n, X, n, st);
@@ -1713,21 +1670,14 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
     return RBKI_OK;
   };
   for (;; ++t) {
-    if (P.fused) {
-      // block t of every mode's basis and Z over the t + 1 blocks, in one
-      // launch: the same steps as the fixed-q launch, one block at a time
-      ChainJob jobs[8];
-      for (int n = 0; n < P.N; ++n) jobs[n] = chain_job(P, b, n, n, (int)(P.m[n].S * (t + 1)));
-      s = run_chains(P, jobs, P.N, t, t, st);
-      if (s != RBKI_OK) return s;
-    } else if (P.together) {
+    if (P.together) {
       s = step(ms, 0);
       if (s != RBKI_OK) return s;
     }
     int64_t width[8];
     for (int n = 0; n < P.N; ++n) {
       width[n] = P.m[n].S * (t + 1);
-      if (P.fused || P.together) continue;
+      if (P.together) continue;
       ModeSet one;
       one.add(n, 0);
       s = step(one, n);
@@ -1795,7 +1745,7 @@ static rbki_status tucker_impl(const void* X, int xtype, const rbki_params* prm,
   // with concurrent modes, each mode's eigenproblem and factor (and the first
   // product of the core chain) run on its stream as soon as its Krylov basis
   // is done
-  bool inline_factors = !P.concurrent && !P.one_stream && !P.fused && b.lanes > 1;
+  bool inline_factors = !P.concurrent && !P.one_stream && !P.together && b.lanes > 1;
   for (int n = 0; n < P.N; ++n) inline_factors = inline_factors && eig_top_ok(P.m[n].Sp, P.m[n].R);
   int chain_done = 0;
   s = run_modes(P, b, xsrc, st, inline_factors, &chain_done);
