@@ -157,259 +157,172 @@ __global__ void gemm_reduce_kernel(GemmArgs a) {
 }
 
 // ------------------------------------------------------------ Cholesky QR
-// Right-looking Cholesky of the s x s Gram matrix G in LDS with column
-// dropping, then the inverse of the (reduced) factor, one workgroup.  A pivot
-// d_k (the Schur-complement diagonal) is dropped, with its row and column of
-// the factor set to zero, when d_k <= tau_rel * G_kk (the vector lies within
-// the span of the earlier kept ones to working accuracy) or
-// d_k <= tau_abs^2 * max_k ref2[k] (it is at round-off level relative to the
-// block before projection).  Writes Linv (s x s, zero rows/columns for dropped
-// vectors) and flags[k] = 1 for kept vectors.
+// CholeskyQR step for s <= 96 in one launch: Yout = L^{-1} Y where G = L L^T, with
+// column dropping.  A pivot d_k (the Schur-complement diagonal) is dropped, with its
+// column of the factor set to zero and a zero row of Yout, when
+// d_k <= tau_rel * G_kk (the vector lies within the span of the earlier kept ones to
+// working accuracy), when d_k <= tau_abs^2 * max_k ref2[k] (it is at round-off level
+// relative to the block before projection) or when the direction budget is spent.
+// flags[k] = 1 for kept vectors.
+//
+// A workgroup of four waves takes 64 columns of Y and factors G itself, so no
+// workgroup waits for another.  G is zero-padded to 16 NB in LDS (a padded pivot is
+// dropped and changes nothing) and factored in panels of 16 columns by wave 0: a
+// lane holds a row of the panel in registers, and column k is read from the lanes
+// that hold it (v_readlane).  Sixteen more lanes start as the identity's rows: the
+// column operations that turn the diagonal block into D turn those into D^{-T}, at
+// no cost.  The waves then apply the panel to the trailing blocks and, once all are
+// factored, solve L y = Y by blocks, y_b = D_b^{-1} (Y_b - sum_a L_ba y_a), sixteen
+// columns a wave, on the float64 matrix cores: an item of a product is the next
+// product's operand as it stands.  The pivot is d * rsqrt(d) and its reciprocal the
+// Newton-refined rsqrt itself.
+//
+// The time is latency: launch, the read of G and Y, and 16 NB dependent columns of
+// about 0.2 us.  Against one wave that substituted in every column from LDS
+// broadcasts: s = 15 6.1 us (7.6), s = 30 9.9 (17.1), s = 60 25 (42); and for s = 90
+// against the unblocked factor and inverse of one workgroup and a product, 45 us (200
+// and 12), with other modes beside them.
 constexpr int CHOL_MAX = 96;
-
-__global__ void __launch_bounds__(1024) chol_inv_kernel(CholArgs a) {
-  const CholJob& job = a.job[blockIdx.x];
-  const double* G = job.G;
-  const int64_t s = job.s;
-  double* Linv = job.Lm;
-  int* flags = job.flags;
-  const double* ref2 = job.ref2;
-  const double tau_rel = a.tau_rel, tau_abs = job.tau_abs;
-  const DimBudget bud = job.bud;
-  __shared__ double Ls[CHOL_MAX][CHOL_MAX + 1];
-  __shared__ double Xs[CHOL_MAX][CHOL_MAX + 1];
-  __shared__ double d0[CHOL_MAX];
-  __shared__ int keep[CHOL_MAX];
-  __shared__ double red[16];
-  __shared__ double sh_ref;
-  const int tid = threadIdx.x;
-  double mx = 0.0;
-  if (ref2)
-    for (int64_t i = tid; i < s; i += blockDim.x) mx = fmax(mx, ref2[i]);
-  mx = warp_max(mx);
-  if ((tid & 63) == 0) red[tid >> 6] = mx;
-  for (int e = tid; e < (int)(s * s); e += blockDim.x) {
-    const int i = e / (int)s, j = e - i * (int)s;
-    Ls[i][j] = G[e];
-    if (i == j) d0[i] = G[e];
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double v = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) v = fmax(v, red[w]);
-    sh_ref = v;
-  }
-  __syncthreads();
-  const double abs_floor = tau_abs * tau_abs * sh_ref;
-  const int64_t allowed = bud.allowed();
-  int64_t nkept = 0;
-  for (int k = 0; k < s; ++k) {
-    const double d = Ls[k][k];
-    const int kp = (d0[k] > 0.0) && (d > tau_rel * d0[k]) && (d > abs_floor) && nkept < allowed;
-    nkept += kp;
-    const double piv = kp ? sqrt(d) : 0.0;
-    __syncthreads();
-    for (int i = k + tid; i < s; i += blockDim.x) Ls[i][k] = kp ? (i == k ? piv : Ls[i][k] / piv) : 0.0;
-    if (tid == 0) keep[k] = kp;
-    __syncthreads();
-    if (kp) {
-      const int t = s - k - 1;
-      for (int e = tid; e < t * t; e += blockDim.x) {
-        const int i = k + 1 + e / t, j = k + 1 + e % t;
-        if (j <= i) Ls[i][j] -= Ls[i][k] * Ls[j][k];
-      }
-    }
-    __syncthreads();
-  }
-  // X = L^{-1} restricted to kept rows/columns, right-looking: starting from
-  // the identity, row k is scaled by 1 / L_kk and then removed from the rows
-  // below it.  Only columns c <= k of a row are nonzero at step k.  A dropped
-  // k has a zero factor column, so its row and column of X stay zero.
-  const int sn = (int)s;
-  for (int e = tid; e < sn * sn; e += blockDim.x) {
-    const int i = e / sn, j = e - i * sn;
-    Xs[i][j] = (i == j && keep[i]) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  for (int k = 0; k < sn; ++k) {
-    if (keep[k]) {
-      const double inv = 1.0 / Ls[k][k];
-      for (int c = tid; c <= k; c += blockDim.x) Xs[k][c] *= inv;
-    }
-    __syncthreads();
-    if (keep[k]) {
-      const int w = k + 1, t = sn - k - 1;
-      for (int e = tid; e < t * w; e += blockDim.x) {
-        const int i = k + 1 + e / w, c = e - (e / w) * w;
-        Xs[i][c] -= Ls[i][k] * Xs[k][c];
-      }
-    }
-    __syncthreads();
-  }
-  // a dropped row k of L still holds its entries left of the diagonal, which
-  // reached row k of X above: dropped vectors get a zero row
-  for (int e = tid; e < sn * sn; e += blockDim.x) {
-    const int i = e / sn, j = e - i * sn;
-    Linv[e] = keep[i] ? Xs[i][j] : 0.0;
-  }
-  for (int64_t i = tid; i < s; i += blockDim.x) flags[i] = keep[i];
-  if (tid == 0) bud.record(nkept);
-}
-
-// CholeskyQR step for s <= 64 in one launch: Yout = L^{-1} Y where G = L L^T
-// (same drop rule as above: a dropped vector gets a zero row of Yout).
-// One wave per workgroup, 64 columns of Y each; every workgroup factors G
-// itself, so no workgroup waits for another.  G is zero-padded to SMAX in LDS
-// (a padded pivot is dropped and changes nothing), and the factor runs in
-// panels of 16 columns: lane i holds row i of the panel in registers and
-// reads the finished column k from the lane that holds it (v_readlane), then
-// the wave applies the panel to the trailing rows and columns in 4 x 4 tiles.
-// Every entry receives its updates in column order, one FMA each, as in the
-// unblocked right-looking form.  The pivot is d * rsqrt(d) and its reciprocal
-// the Newton-refined rsqrt itself.  Then each lane solves L y = Y(:, c) for
-// its column c by forward substitution, with y in registers and L read by LDS
-// broadcast, four rows per branch.  Loads of G and Y are clamped into range
-// so they are all issued before the first wait.  flags is written by
-// workgroup 0.
-constexpr int CS_MAX = 64;
-constexpr int CS_NB = 16;
 
 __device__ inline double lane_f64(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-template <int SMAX>
-__global__ void __launch_bounds__(64) chol_solve_kernel(CholArgs a) {
-  static_assert(SMAX % CS_NB == 0, "panels of 16 columns");
+template <int NB>
+__global__ void __launch_bounds__(256) chol_solve_kernel(CholArgs a) {
+  constexpr int SM = 16 * NB, LD = SM + 4;       // rows 4 banks (of 8 bytes) apart: no conflicts in a fragment
+  constexpr bool TWO = SM > 48;                  // rows of a panel beyond the first 48
   const CholJob& job = a.job[blockIdx.y];
-  const double* G = job.G;
   const int s = (int)job.s;
-  const double* Y = job.Y;
   const int64_t n = job.n;
-  double* Yout = job.Yout;
-  int* flags = job.flags;
-  const double* ref2 = job.ref2;
-  const double tau_rel = a.tau_rel, tau_abs = job.tau_abs;
-  const DimBudget bud = job.bud;
   if ((int64_t)blockIdx.x * 64 >= n) return;
-  __shared__ double Ls[SMAX][SMAX + 1];
-  __shared__ double dinv[SMAX];
-  __shared__ int keep[SMAX];
-  const int lane = threadIdx.x;
+  __shared__ double Ls[SM][LD];
+  __shared__ double Di[NB][16][20];              // inverses of the diagonal blocks
+  __shared__ double diag[SM];
+  __shared__ int keep[SM];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
   {
-    double gv[SMAX * SMAX / 64];
+    const double* G = job.G;
+    double gv[NB * NB];
 #pragma unroll
-    for (int q = 0; q < SMAX * SMAX / 64; ++q) {
-      const int e = lane + 64 * q, i = e / SMAX, j = e - i * SMAX;
+    for (int q = 0; q < NB * NB; ++q) {
+      const int e = tid + 256 * q, i = e / SM, j = e - i * SM;
       gv[q] = G[(i < s ? i : s - 1) * s + (j < s ? j : s - 1)];
     }
 #pragma unroll
-    for (int q = 0; q < SMAX * SMAX / 64; ++q) {
-      const int e = lane + 64 * q, i = e / SMAX, j = e - i * SMAX;
-      Ls[i][j] = (i < s && j < s) ? gv[q] : 0.0;
+    for (int q = 0; q < NB * NB; ++q) {
+      const int e = tid + 256 * q, i = e / SM, j = e - i * SM;
+      const double v = (i < s && j < s) ? gv[q] : 0.0;
+      Ls[i][j] = v;
+      if (i == j) diag[i] = v;
     }
   }
-  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  // this wave's columns of Y: item v of lane (li, lg) of block b is row 16 b + 4 v + lg
+  const int64_t c = (int64_t)blockIdx.x * 64 + wave * 16 + li;
   const int64_t cc = c < n ? c : n - 1;
-  double y[SMAX];
+  f64x4_t y[NB];
 #pragma unroll
-  for (int k = 0; k < SMAX; ++k) y[k] = Y[(int64_t)(k < s ? k : s - 1) * n + cc];
-  const double mx = warp_max((ref2 && lane < s) ? ref2[lane] : 0.0);
-  const double abs_floor = tau_abs * tau_abs * mx;
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int k = 16 * b + 4 * v + lg;
+      y[b][v] = job.Y[(int64_t)(k < s ? k : s - 1) * n + cc];
+    }
+  double mx = 0.0;
+  if (job.ref2)
+    for (int k = lane; k < s; k += 64) mx = fmax(mx, job.ref2[k]);
+  const double abs_floor = job.tau_abs * job.tau_abs * warp_max(mx);
+  const double tau_rel = a.tau_rel;
+  const DimBudget bud = job.bud;
   const int64_t allowed = bud.allowed();
-  __syncthreads();
-  const double d0 = lane < SMAX ? Ls[lane][lane] : 0.0;
   int64_t nkept = 0;
+  __syncthreads();
 #pragma unroll 1
-  for (int c0 = 0; c0 < SMAX; c0 += CS_NB) {
-    {
-      const int i = lane;
-      double r[CS_NB];
+  for (int b = 0; b < NB; ++b) {
+    const int c0 = 16 * b;
+    if (wave == 0) {
+      // lanes 0..47: rows c0 + lane; 48..63: the identity's; then rows c0 + 48 + lane
+      const int row0 = c0 + lane, row1 = c0 + 48 + lane;
+      const bool in0 = lane < 48 && row0 < SM, in1 = TWO && row1 < SM;
+      double r0[16], r1[TWO ? 16 : 1];
 #pragma unroll
-      for (int jj = 0; jj < CS_NB; ++jj) r[jj] = i < SMAX ? Ls[i][c0 + jj] : 0.0;
-#pragma unroll
-      for (int kk = 0; kk < CS_NB; ++kk) {
-        const int k = c0 + kk;
-        const double v = r[kk];           // G(i, k) minus the earlier columns' terms
-        const double d = lane_f64(v, k), dk0 = lane_f64(d0, k);
-        const bool kp = (dk0 > 0.0) && (d > tau_rel * dk0) && (d > abs_floor) && nkept < allowed;
-        nkept += kp;
-        const double rs = rsq_nr(kp ? d : 1.0);
-        const double inv = kp ? rs : 0.0;
-        const double lik = i > k ? v * inv : (i == k ? d * inv : 0.0);
-        r[kk] = lik;
-        if (i == k) {
-          keep[k] = kp;
-          dinv[k] = inv;
-        }
-#pragma unroll
-        for (int jj = kk + 1; jj < CS_NB; ++jj) r[jj] -= lik * lane_f64(lik, c0 + jj);
+      for (int j = 0; j < 16; ++j) {
+        r0[j] = in0 ? Ls[row0][c0 + j] : (lane == 48 + j ? 1.0 : 0.0);
+        if constexpr (TWO) r1[j] = in1 ? Ls[row1][c0 + j] : 0.0;
       }
-      if (i < SMAX) {
+      // the least pivot that is kept (none: infinity)
+      const double d0 = lane < 16 ? diag[c0 + lane] : 0.0;
+      const double least = d0 > 0.0 && abs_floor == abs_floor ? fmax(tau_rel * d0, abs_floor) : __builtin_inf();
+      unsigned kept = 0;
 #pragma unroll
-        for (int jj = 0; jj < CS_NB; ++jj) Ls[i][c0 + jj] = r[jj];
+      for (int k = 0; k < 16; ++k) {
+        const double v = r0[k];                   // G(i, k) minus the earlier columns' terms
+        const double d = lane_f64(v, k);
+        const bool kp = d > lane_f64(least, k) && nkept < allowed;
+        nkept += kp;
+        kept |= (unsigned)kp << k;
+        const double rs = rsq_nr(d);
+        const double inv = kp ? rs : 0.0;
+        const double l0 = v * inv;                // (above the diagonal: not used)
+        r0[k] = l0;
+        if constexpr (TWO) r1[k] *= inv;
+#pragma unroll
+        for (int j = k + 1; j < 16; ++j) {
+          const double lj = lane_f64(l0, j);
+          r0[j] -= l0 * lj;
+          if constexpr (TWO) r1[j] -= r1[k] * lj;
+        }
+      }
+      if (lane < 16) keep[c0 + lane] = (kept >> lane) & 1;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        if (in0) Ls[row0][c0 + j] = r0[j];
+        if (TWO && in1) Ls[row1][c0 + j] = r1[j];
+        if (lane >= 48) Di[b][j][lane - 48] = r0[j];
       }
     }
     __syncthreads();
-    // trailing rows and columns t0.. of the lower triangle's square, 4 x 4
-    // tiles (the upper part is updated too and never read)
-    const int t0 = c0 + CS_NB, mt = (SMAX - t0) / 4;
-    for (int t = lane; t < mt * mt; t += 64) {
-      const int ti = t / mt, tj = t - ti * mt;
-      const int i0 = t0 + 4 * ti, j0 = t0 + 4 * tj;
-      double acc[4][4];
+    // trailing blocks (ti, tj <= ti): A -= L_ti L_tj^T
+    const int m = NB - 1 - b;
+    for (int t = wave; t < m * (m + 1) / 2; t += 4) {
+      int ti = 0, tj = t;
+      while (tj > ti) tj -= ++ti;
+      const int i0 = c0 + 16 + 16 * ti, j0 = c0 + 16 + 16 * tj;
+      f64x4_t acc;
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int v = 0; v < 4; ++v) acc[v] = Ls[i0 + 4 * v + lg][j0 + li];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[a][q] = Ls[i0 + a][j0 + q];
+      for (int k = 0; k < 4; ++k)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Ls[i0 + li][c0 + 4 * k + lg], Ls[j0 + li][c0 + 4 * k + lg], acc, 0, 0, 0);
 #pragma unroll
-      for (int kk = 0; kk < CS_NB; ++kk) {
-        double li[4], lj[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          li[a] = Ls[i0 + a][c0 + kk];
-          lj[a] = Ls[j0 + a][c0 + kk];
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[a][q] -= li[a] * lj[q];
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) Ls[i0 + a][j0 + q] = acc[a][q];
+      for (int v = 0; v < 4; ++v) Ls[i0 + 4 * v + lg][j0 + li] = acc[v];
     }
     __syncthreads();
   }
   if (blockIdx.x == 0) {
-    if (lane < s) flags[lane] = keep[lane];
+    for (int k = tid; k < s; k += 256) job.flags[k] = keep[k];
     // every workgroup reads the count of earlier blocks; one writes the total
-    if (lane == 0) bud.record(nkept);
+    if (tid == 0) bud.record(nkept);
   }
 #pragma unroll
-  for (int k0 = 0; k0 < SMAX; k0 += 4) {
-    if (k0 < s) {
+  for (int b = 0; b < NB; ++b) {
+    f64x4_t t = y[b];
 #pragma unroll
-      for (int k = k0; k < k0 + 4; ++k) {
-        double a0 = y[k], a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    for (int p = 0; p < b; ++p)
 #pragma unroll
-        for (int j = 0; j + 3 < k; j += 4) {
-          a0 -= Ls[k][j] * y[j];
-          a1 -= Ls[k][j + 1] * y[j + 1];
-          a2 -= Ls[k][j + 2] * y[j + 2];
-          a3 -= Ls[k][j + 3] * y[j + 3];
-        }
+      for (int k = 0; k < 4; ++k)
+        t = __builtin_amdgcn_mfma_f64_16x16x4f64(-Ls[16 * b + li][16 * p + 4 * k + lg], y[p][k], t, 0, 0, 0);
+    f64x4_t z = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int j = k & ~3; j < k; ++j) a0 -= Ls[k][j] * y[j];
-        y[k] = ((a0 + a1) + (a2 + a3)) * dinv[k];   // zero for a dropped or padded vector
-      }
-      if (c < n) {
+    for (int k = 0; k < 4; ++k) z = __builtin_amdgcn_mfma_f64_16x16x4f64(Di[b][li][4 * k + lg], t[k], z, 0, 0, 0);
+    y[b] = z;
 #pragma unroll
-        for (int k = k0; k < k0 + 4; ++k)
-          if (k < s) Yout[(int64_t)k * n + c] = y[k];
-      }
+    for (int v = 0; v < 4; ++v) {
+      const int k = 16 * b + 4 * v + lg;
+      if (k < s && c < n) job.Yout[(int64_t)k * n + c] = z[v];
     }
   }
 }
@@ -911,7 +824,6 @@ __global__ void canonical_sign_rows_kernel(double* V, int64_t rows, int64_t n) {
 }
 
 template <class T> __device__ inline T factor_value(double v);
-template <> __device__ inline double factor_value<double>(double v) { return v; }
 template <> __device__ inline float factor_value<float>(double v) { return (float)v; }
 template <> __device__ inline bf16_t factor_value<bf16_t>(double v) { return f32_to_bf16((float)v); }
 
@@ -1055,38 +967,31 @@ hipError_t row_norms2(const double* Y, int64_t s, int64_t n, double* out, hipStr
 
 hipError_t chol_orth_batched(const CholJob* jobs, int njobs, double tau_rel, hipStream_t st) {
   if (njobs < 1 || njobs > kGemmJobs) return hipErrorInvalidValue;
-  GemmJob gj[kGemmJobs], up[kGemmJobs];
-  CholArgs fit = {}, inv = {};
-  fit.tau_rel = inv.tau_rel = tau_rel;
-  int nfit = 0, ninv = 0;
+  GemmJob gj[kGemmJobs];
+  CholArgs fit = {};
+  fit.tau_rel = tau_rel;
+  int nfit = 0;
   int64_t smax = 0, nmax = 0;
   for (int i = 0; i < njobs; ++i) {
     const CholJob& j = jobs[i];
     gj[i] = gemm_job(0, 1, j.s, j.s, j.n, 1.0, j.Y, j.n, j.Y, j.n, 0.0, j.G, j.s);
     gj[i].norms = j.norms;
-    if (j.s <= CS_MAX) {
+    if (j.s <= CHOL_MAX) {
       fit.job[nfit++] = j;
       smax = std::max(smax, j.s);
       nmax = std::max(nmax, j.n);
-    } else if (j.s <= CHOL_MAX) {
-      up[ninv] = gemm_job(0, 0, j.s, j.n, j.s, 1.0, j.Lm, j.s, j.Y, j.n, 0.0, j.Yout, j.n);
-      inv.job[ninv++] = j;
     }
   }
   hipError_t e = dgemm_batched(gj, njobs, st);
   if (e != hipSuccess) return e;
   if (nfit) {
-    const dim3 grid((unsigned)ceil_div(nmax, 64), nfit);
-    if (smax <= 16) hipLaunchKernelGGL(chol_solve_kernel<16>, grid, dim3(64), 0, st, fit);
-    else if (smax <= 32) hipLaunchKernelGGL(chol_solve_kernel<32>, grid, dim3(64), 0, st, fit);
-    else if (smax <= 48) hipLaunchKernelGGL(chol_solve_kernel<48>, grid, dim3(64), 0, st, fit);
-    else hipLaunchKernelGGL(chol_solve_kernel<64>, grid, dim3(64), 0, st, fit);
+    const dim3 grid((unsigned)ceil_div(nmax, 64), nfit), block(256);
+    if (smax <= 16) hipLaunchKernelGGL(chol_solve_kernel<1>, grid, block, 0, st, fit);
+    else if (smax <= 32) hipLaunchKernelGGL(chol_solve_kernel<2>, grid, block, 0, st, fit);
+    else if (smax <= 48) hipLaunchKernelGGL(chol_solve_kernel<3>, grid, block, 0, st, fit);
+    else if (smax <= 64) hipLaunchKernelGGL(chol_solve_kernel<4>, grid, block, 0, st, fit);
+    else hipLaunchKernelGGL(chol_solve_kernel<6>, grid, block, 0, st, fit);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (ninv) {
-    hipLaunchKernelGGL(chol_inv_kernel, dim3(ninv), dim3(1024), 0, st, inv);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = dgemm_batched(up, ninv, st)) != hipSuccess) return e;
   }
   for (int i = 0; i < njobs; ++i) {
     const CholJob& j = jobs[i];

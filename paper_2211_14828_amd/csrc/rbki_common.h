@@ -88,10 +88,11 @@ template <class T> __device__ inline T warp_max(T v) {
   return v;
 }
 
-// 1/x and 1/sqrt(x) in float64 from the hardware estimates refined by two
-// Newton-Raphson steps each (r <- r (2 - x r); r <- r (3 - x r^2) / 2), full
-// double precision from an estimate good to half of it, in a few dependent
-// FMAs instead of the correctly rounded divide / square-root sequences.
+// 1/x and 1/sqrt(x) in float64 from the hardware estimates, good to half of double
+// precision: the reciprocal by two Newton-Raphson steps r <- r (2 - x r), the root's
+// by one step of third order, r <- r (1 + e/2 + 3 e^2/8) with e = 1 - x r^2 (the next
+// term, 5 e^3/16, is below 2^-70).  Full double precision in a few dependent FMAs
+// instead of the correctly rounded divide / square-root sequences.
 __device__ inline double rcp_nr(double x) {
   double r = __builtin_amdgcn_rcp(x);
   r = fma(r, fma(-x, r, 1.0), r);
@@ -99,11 +100,9 @@ __device__ inline double rcp_nr(double x) {
   return r;
 }
 __device__ inline double rsq_nr(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double hx = 0.5 * x;
-  r = r * fma(-hx * r, r, 1.5);
-  r = r * fma(-hx * r, r, 1.5);
-  return r;
+  const double r = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * r, r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
 }
 
 }  // namespace rbki
