@@ -840,26 +840,33 @@ __device__ inline void put_factor(void* p, int elem, int64_t at, double v) {
 struct FactorArgs {
   FinishJob job[8];
 };
-__global__ void finish_factors_kernel(FactorArgs args) {
+__global__ void __launch_bounds__(256) finish_factors_kernel(FactorArgs args) {
   const FinishJob& f = args.job[blockIdx.y];
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int64_t row = blockIdx.x, n = f.I;
   if (row >= f.R) return;
-  const int64_t n = f.I;
+  const int tid = threadIdx.x;
   double* v = f.Ut + row * n;
   double best = -1.0;
   int64_t bi = n;
-  for (int64_t c = lane; c < n; c += 64) {
+  auto take = [&](double ob, int64_t oi) {
+    if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+  };
+  for (int64_t c = tid; c < n; c += 256) {
     const double a = fabs(v[c]);
     if (a > best) { best = a; bi = c; }
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    const double ob = __shfl_xor(best, o, 64);
-    const int64_t oi = __shfl_xor(bi, o, 64);
-    if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+  for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(best, o, 64), __shfl_xor(bi, o, 64));
+  __shared__ double sb[4];
+  __shared__ int64_t si[4];
+  if ((tid & 63) == 0) {
+    sb[tid >> 6] = best;
+    si[tid >> 6] = bi;
   }
+  __syncthreads();
+  for (int w = 0; w < 4; ++w) take(sb[w], si[w]);
   const bool flip = best > 0.0 && bi < n && v[bi < n ? bi : 0] < 0.0;
-  for (int64_t c = lane; c < n; c += 64) {
+  __syncthreads();                 // every thread has read the entry before one turns it
+  for (int64_t c = tid; c < n; c += 256) {
     const double x = flip ? -v[c] : v[c];
     if (flip) v[c] = x;
     if (f.copy) f.copy[row * n + c] = x;
@@ -1143,7 +1150,7 @@ hipError_t finish_factors(const FinishJob* jobs, int njobs, hipStream_t st) {
     args.job[i] = jobs[i];
     rows = std::max(rows, jobs[i].R);
   }
-  hipLaunchKernelGGL(finish_factors_kernel, dim3((unsigned)ceil_div(rows, 4), njobs), dim3(256), 0, st, args);
+  hipLaunchKernelGGL(finish_factors_kernel, dim3((unsigned)rows, njobs), dim3(256), 0, st, args);
   return hipGetLastError();
 }
 
