@@ -120,6 +120,7 @@ struct ModeGeom {
   bool pipe = false;              // mixed forms: the pipelined Gram kernel on a blocked copy
   int pelem = 0;                  // its element type (E_BF16 or E_FP8)
   int64_t nkt = 0;                // its K tiles
+  bool direct = false;            // products with X X^T are formed from X, which is kept in C's place
 };
 
 struct Plan {
@@ -157,6 +158,20 @@ struct Plan {
   size_t partial_bytes = 0;
   int64_t chain_elems = 0;   // largest intermediate of the core / reconstruction chains
 };
+
+// Modes with fewer than half as many columns as rows whose unfolding is a matrix in
+// memory as it stands (the first and the last): X X^T, I x I, is never formed.  A
+// float64 copy of X and a block T = Q^T X fit in its place, and a product (X X^T) Q
+// costs two of S I J operations, no more than the one of S I^2 with it.  Products and
+// sums are float64, so nothing is lost on X X^T in float32.  From 1024 rows on, where
+// forming and storing X X^T costs more than the extra launch a step.  Measured (us a
+// call, formed / direct, S = 15, one step): 512 x 256 361 / 333 but level with three
+// steps, 1024 x 512 458 / 409, 2048 x 1024 709 / 659, 4096 x 2048 1466 / 1011; the mode
+// of 7200 x 3072, S = 55: 2.1 of 5.6 ms a call.
+bool direct_mode(const Plan& P, const ModeGeom& g) {
+  return !P.need_pad && !g.sampled && (g.A == 1 || g.B == 1) && g.I >= 1024 && 2 * g.J <= g.I &&
+         (g.I + g.Sp) * g.J <= g.I * g.I;
+}
 
 int dtype_elem(int dt) { return dt == RBKI_F64 ? E_F64 : dt == RBKI_F32 ? E_F32 : E_BF16; }
 
@@ -257,6 +272,7 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
     g.S = std::min<int64_t>(std::min<int64_t>(g.R + P.p, g.I), g.m);   // Sec. 2.3, Sec. 4.1
     g.Sp = P.power ? g.S : g.S * (P.q + 1);
     if (g.Sp > 1200) return fail(RBKI_E_UNSUPPORTED, "Krylov width %lld > 1200 (mode %d)", (long long)g.Sp, n);
+    g.direct = direct_mode(P, g);
     const double ratio = (double)g.I / (double)g.R;
     if (ratio > best) { best = ratio; P.first_mode = n; }
     P.maxI = std::max(P.maxI, g.I);
@@ -546,6 +562,51 @@ rbki_status convert_input(const Plan& P, const Buffers& b, const void* X, hipStr
 constexpr double TAU_REL = 1e-12;   // pivot vs its own column: direction already spanned
 constexpr double TAU_ABS = 1e-10;   // pivot vs the block before projection (matches the oracle)
 
+// A direct mode's T = Q^T X_(n) (rows x J) and T X_(n)^T (rows x I); X64: its X.
+GemmJob direct_first(const ModeGeom& g, int64_t rows, const double* Q, const double* X64, double* T) {
+  if (g.A == 1) return gemm_job(0, 0, rows, g.J, g.I, 1.0, Q, g.I, X64, g.J, 0.0, T, g.J);
+  return gemm_job(0, 1, rows, g.J, g.I, 1.0, Q, g.I, X64, g.I, 0.0, T, g.J);
+}
+GemmJob direct_second(const ModeGeom& g, int64_t rows, const double* T, const double* X64, double* out) {
+  if (g.A == 1) return gemm_job(0, 1, rows, g.I, g.J, 1.0, T, g.J, X64, g.J, 0.0, out, g.I);
+  return gemm_job(0, 0, rows, g.I, g.J, 1.0, T, g.J, X64, g.I, 0.0, out, g.I);
+}
+
+// Products Q^T C (rows x I) of several modes at once; C is the mode's X X^T (or its
+// sample's), or in a direct mode X with room for T behind it.  out2: a second copy.
+struct GramProduct {
+  int mode;
+  int64_t rows;
+  const double* Q;
+  double* C;
+  double* out;
+  double* out2;
+};
+rbki_status gram_products(const Plan& P, const GramProduct* p, int count, hipStream_t st) {
+  GemmJob one[8], two[8];
+  int none = 0, ntwo = 0;
+  for (int i = 0; i < count; ++i) {
+    const ModeGeom& g = P.m[p[i].mode];
+    GemmJob j;
+    if (g.direct) {
+      double* T = p[i].C + g.I * g.J;
+      one[none++] = direct_first(g, p[i].rows, p[i].Q, p[i].C, T);
+      j = direct_second(g, p[i].rows, T, p[i].C, p[i].out);
+    } else {
+      j = gemm_job(0, 0, p[i].rows, g.I, g.I, 1.0, p[i].Q, g.I, p[i].C, g.I, 0.0, p[i].out, g.I);
+    }
+    if (p[i].out2) {
+      j.C2 = p[i].out2;
+      j.ldc2 = g.I;
+    }
+    if (g.direct) two[ntwo++] = j;
+    else one[none++] = j;
+  }
+  if (none) HIPCHK(dgemm_batched(one, none, st));
+  if (ntwo) HIPCHK(dgemm_batched(two, ntwo, st));
+  return RBKI_OK;
+}
+
 // heavy_wait / heavy_done (nullable): events that the sketch and Gram
 // kernels wait for and record, so that those throughput-bound kernels of
 // concurrently running modes follow each other.
@@ -602,6 +663,16 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
       }
       HIPCHK(launch_gram_reduce(E_BF16, ga, L.C, L.Yt, st));
     }
+  } else if (g.direct) {
+    double* T = L.C + I * g.J;
+    HIPCHK(convert_tensor(P.gelem, xsrc, E_F64, L.C, I * g.J, st));
+    {
+      ProfScope ps("omega", st);
+      HIPCHK(launch_omega(P.gelem, P.seed, n, S * g.J, P.gelem == E_F64 ? T : L.omegaT, st));
+      if (P.gelem != E_F64) HIPCHK(convert_tensor(P.gelem, L.omegaT, E_F64, T, S * g.J, st));
+    }
+    const GemmJob w = direct_second(g, S, T, L.C, L.Yt);
+    HIPCHK(dgemm_batched(&w, 1, st));
   } else {
     // a sampled mode needs only C from the whole unfolding (for Z): no sketch
     const int Sf = g.sampled ? 0 : (int)S;
@@ -698,9 +769,10 @@ rbki_status krylov_block0(const Plan& P, const Buffers& b, const ModeSet& ms, hi
 // twice and orthonormalised.  The product C Q_{j-1} is formed into the
 // set's Yt and, when CQ is given, kept as rows (j-1) S.. of CQ; with from_cq
 // it is taken from there instead (formed earlier with the same C).
-rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int j, const double* const* Ck,
+rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int j, double* const* Ck,
                         double* const* CQ, const bool* from_cq, hipStream_t st) {
-  GemmJob cq[8], proj[8], upd[8];
+  GramProduct cq[8];
+  GemmJob proj[8], upd[8];
   CholJob first[8], second[8];
   int ncq = 0;
   for (int i = 0; i < ms.count; ++i) {
@@ -714,12 +786,7 @@ rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int 
       HIPCHK(copy_rows_f64(L.Yt, I, CQ[i] + (m - S) * I, I, S, I, st));
     } else {
       // Y_j^T = Q_{j-1}^T C  (C symmetric)
-      cq[ncq] = gemm_job(0, 0, S, I, I, 1.0, Qt + (m - S) * I, I, Ck[i], I, 0.0, L.Yt, I);
-      if (CQ[i]) {
-        cq[ncq].C2 = CQ[i] + (m - S) * I;
-        cq[ncq].ldc2 = I;
-      }
-      ++ncq;
+      cq[ncq++] = GramProduct{n, S, Qt + (m - S) * I, Ck[i], L.Yt, CQ[i] ? CQ[i] + (m - S) * I : nullptr};
     }
     // remove earlier blocks, twice
     proj[i] = gemm_job(0, 1, S, m, I, 1.0, L.Yt, I, Qt, I, 0.0, L.Pm, m);
@@ -730,7 +797,8 @@ rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int 
     first[i].bud = DimBudget{used + j, used + j + 1, I};
     second[i] = orth_job(g, L, L.Ytmp, Qt + m * I);
   }
-  if (ncq) HIPCHK(dgemm_batched(cq, ncq, st));
+  rbki_status s = gram_products(P, cq, ncq, st);
+  if (s != RBKI_OK) return s;
   for (int pass = 0; pass < 2; ++pass) {
     for (int i = 0; i < ms.count; ++i) proj[i].norms = pass == 0 ? b.ln[ms.lane[i]].ref2 : nullptr;
     HIPCHK(dgemm_batched(proj, ms.count, st));
@@ -746,9 +814,9 @@ rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int 
 rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, bool with_factor, hipStream_t st) {
   ProfScope ps("chain", st);
   dgemm_set_scratch(b.ln[ms.lane[0]].dscratch, kDgemmScratch);
-  const double* Ck[8];
+  double* Ck[8];
   double* CQ[8];
-  GemmJob job[8];
+  GramProduct job[8];
   for (int i = 0; i < ms.count; ++i) {
     const Lane& L = b.ln[ms.lane[i]];
     Ck[i] = P.m[ms.mode[i]].sampled ? L.CY : L.C;   // a sampled mode's Krylov products: the sample's Y Y^T
@@ -765,14 +833,14 @@ rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, 
       const int n = ms.mode[i];
       const ModeGeom& g = P.m[n];
       const Lane& L = b.ln[ms.lane[i]];
-      job[i] = gemm_job(0, 0, g.S, g.I, g.I, 1.0, b.Qt[n], g.I, Ck[i], g.I, 0.0, L.Yt, g.I);
+      job[i] = GramProduct{n, g.S, b.Qt[n], Ck[i], L.Yt, nullptr};
       first[i] = orth_job(g, L, L.Yt, L.Ytmp);
       first[i].ref2 = first[i].norms = L.ref2;
       first[i].tau_abs = TAU_ABS;
       second[i] = orth_job(g, L, L.Ytmp, b.Qt[n]);
     }
     for (int j = 1; j <= P.q; ++j) {
-      HIPCHK(dgemm_batched(job, ms.count, st));
+      if ((s = gram_products(P, job, ms.count, st)) != RBKI_OK) return s;
       HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
       HIPCHK(chol_orth_batched(second, ms.count, TAU_REL, st));
     }
@@ -790,11 +858,10 @@ rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, 
     const int n = ms.mode[i];
     const ModeGeom& g = P.m[n];
     const int64_t from = P.power || g.sampled ? 0 : g.Sp - g.S;
-    job[i] = gemm_job(0, 0, g.Sp - from, g.I, g.I, 1.0, b.Qt[n] + from * g.I, g.I, b.ln[ms.lane[i]].C, g.I, 0.0,
-                      CQ[i] + from * g.I, g.I);
+    job[i] = GramProduct{n, g.Sp - from, b.Qt[n] + from * g.I, b.ln[ms.lane[i]].C, CQ[i] + from * g.I, nullptr};
     zj[i] = gemm_job(0, 1, g.Sp, g.Sp, g.I, 1.0, b.Qt[n], g.I, CQ[i], g.I, 0.0, b.Z[n], g.Sp);
   }
-  HIPCHK(dgemm_batched(job, ms.count, st));
+  if ((s = gram_products(P, job, ms.count, st)) != RBKI_OK) return s;
   HIPCHK(dgemm_batched(zj, ms.count, st));
   return RBKI_OK;
 }
@@ -1646,7 +1713,7 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
   // sampled takes C Q_{t-1} from the products kept for Z.
   auto step = [&](const ModeSet& set, int n0) -> rbki_status {
     if (t > 0) {
-      const double* Ck[8];
+      double* Ck[8];
       bool from_cq[8];
       double* kept[8];
       for (int i = 0; i < set.count; ++i) {
@@ -1658,14 +1725,16 @@ rbki_status adaptive_impl(const void* X, int xtype, const rbki_params* prm, doub
       rbki_status e = krylov_step(P, b, set, t, Ck, kept, from_cq, st);
       if (e != RBKI_OK) return e;
     }
-    GemmJob cq[8], zj[8];
+    GramProduct cq[8];
+    GemmJob zj[8];
     for (int i = 0; i < set.count; ++i) {
       const int n = n0 + i;
       const int64_t I = P.m[n].I, S = P.m[n].S, m = S * (t + 1);
-      cq[i] = gemm_job(0, 0, S, I, I, 1.0, b.Qt[n] + (m - S) * I, I, Cm[n], I, 0.0, CQm[n] + (m - S) * I, I);
+      cq[i] = GramProduct{n, S, b.Qt[n] + (m - S) * I, Cm[n], CQm[n] + (m - S) * I, nullptr};
       zj[i] = gemm_job(0, 1, m, m, I, 1.0, b.Qt[n], I, CQm[n], I, 0.0, b.Z[n], m);
     }
-    HIPCHK(dgemm_batched(cq, set.count, st));
+    rbki_status e = gram_products(P, cq, set.count, st);
+    if (e != RBKI_OK) return e;
     HIPCHK(dgemm_batched(zj, set.count, st));
     return RBKI_OK;
   };
