@@ -800,6 +800,180 @@ __global__ void __launch_bounds__(512, 2) gram_wide_kernel(GramArgs g) {
     }
 }
 
+// The flat form of float64, for modes of 65 to 256 rows: a workgroup of eight waves
+// stages every row of the mode and of the sketch (at most five groups of 64) and forms
+// a share of all the wanted blocks, up to four a wave, dealt out evenly, so that the
+// SIMDs stay level (in 128-row tiles a wave has 0 to 4 blocks) and each row is staged
+// once or twice instead of three times.  Two LDS buffers, one barrier a K tile.
+// Measured: 200^3, S = 15, 71 us (110 in 128-row tiles), 40 TFLOP/s of wanted blocks,
+// where an 8192^3 product of the vendor's library reaches 71: the rest is the first
+// loads, 37 MB of partial sums and the shares' unevenness (18 and 17 blocks).  Whole pass with
+// the reduction, us (128-row tiles): 72^3 17 (18), 128^3 25 (32), 160^3 41 (62), 256^3
+// 133 (172); S = 60: 128^3 33 (35), 256^3 158 (179).
+constexpr int FLAT_GROUPS = 5, FLAT_BLOCKS = 4;
+constexpr int FLAT_BUF = FLAT_GROUPS * Op<E_F64>::GROUP_BYTES;
+
+template <bool GATHER>
+__global__ void __launch_bounds__(512, 2) gram_flat_kernel(GramArgs g) {
+  constexpr int E = E_F64, KT = Op<E>::KT;
+  __shared__ __attribute__((aligned(16))) char lds[2 * FLAT_BUF];
+  const int per = (g.ntiles * g.splits) >> 3, spare = (g.ntiles * g.splits) & 7, xcd = blockIdx.x & 7;
+  const int id = xcd * per + (xcd < spare ? xcd : spare) + (int)(blockIdx.x >> 3);
+  const int split = id / g.ntiles, share = id % g.ntiles;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
+  const int I = (int)g.I, S = g.S;
+  const int xg = (I + GROUP - 1) / GROUP, ng = xg + (S > 0 ? 1 : 0);   // groups: the mode's, the sketch
+
+  // this wave's blocks: share + ntiles (wave + 8 i) of the wanted ones; their staged
+  // rows, and which of their 16 x 16 quarters have a wanted entry (bit 2 m + n)
+  const int nb = (I + BLK - 1) / BLK, ntri = nb * (nb + 1) / 2;
+  int blk[FLAT_BLOCKS], ra[FLAT_BLOCKS], rb[FLAT_BLOCKS], mask[FLAT_BLOCKS];
+#pragma unroll
+  for (int i = 0; i < FLAT_BLOCKS; ++i) {
+    blk[i] = share + g.ntiles * (wave + 8 * i);
+    int bi = 0, bj = 0;
+    const bool w = blk[i] >= ntri;
+    if (w) {
+      bi = (blk[i] - ntri) / nb;
+      bj = (blk[i] - ntri) % nb;
+    } else {
+      tri_at(blk[i], bi, bj);
+    }
+    ra[i] = (w ? xg * GROUP : 0) + 32 * bi;
+    rb[i] = 32 * bj;
+    mask[i] = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (blk[i] < g.blocks && 32 * bi + 16 * (q >> 1) < (w ? S : I) && 32 * bj + 16 * (q & 1) < I &&
+          (w || bi > bj || (q >> 1) >= (q & 1)))
+        mask[i] |= 1 << q;
+  }
+
+  // staging: 16-byte piece tid % 8 of row tid / 8 of every group, or (GATHER, mode
+  // rows) K values 2 wave, 2 wave + 1 of row lane; rows past the end repeat the last
+  const int nk = GATHER ? (int)(g.nbt * g.B) : KT;
+  const double* p[FLAT_GROUPS];
+  uint32_t rbyte[FLAT_GROUPS];
+  double2 st[FLAT_GROUPS];
+#pragma unroll
+  for (int i = 0; i < FLAT_GROUPS; ++i) {
+    const bool om = i == xg;
+    const int first = om ? 0 : i * GROUP, last = (om ? S : I) - 1;
+    const int r = first + (tid >> 3), rg = first + lane;
+    p[i] = (const double*)(om ? g.omegaT : g.X) + (r < last ? r : last) * (om ? g.J : g.B) + (tid & 7) * 2;
+    rbyte[i] = (uint32_t)(rg < last ? rg : last) * (uint32_t)g.B * 8u;
+  }
+  int64_t koff[2] = {0, 0};
+  if (GATHER) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) koff[k] = (int64_t)((2 * wave + k) / (int)g.B) * g.I * g.B + (2 * wave + k) % (int)g.B;
+  }
+  const int64_t kt0 = (int64_t)split * g.nkt / g.splits, kt1 = (int64_t)(split + 1) * g.nkt / g.splits;
+  int64_t a, b0 = 0;
+  if (GATHER) {
+    a = kt0 * g.nbt;
+  } else {
+    a = kt0 / g.nbt;
+    b0 = (kt0 - a * g.nbt) * KT;
+  }
+  int lo = 0;                      // K values of the loaded tile from which on they count
+  auto load = [&]() {
+    const int64_t at = GATHER ? a : b0, end = GATHER ? g.A - g.nbt : g.B - KT;
+    const int64_t from = at < end ? at : end;
+    lo = (int)(at - from) * (GATHER ? (int)g.B : 1);
+    const int64_t x = GATHER ? from * g.I * g.B : a * g.I * g.B + from, o = GATHER ? from * g.B : a * g.B + from;
+#pragma unroll
+    for (int i = 0; i < FLAT_GROUPS; ++i) {
+      if (i >= ng) continue;
+      if (GATHER && i < xg) {
+        const double* X = (const double*)g.X + x;
+        st[i].x = 2 * wave < nk ? *(const double*)((const char*)(X + koff[0]) + rbyte[i]) : 0.0;
+        st[i].y = 2 * wave + 1 < nk ? *(const double*)((const char*)(X + koff[1]) + rbyte[i]) : 0.0;
+      } else {
+        const u32x4u_t v = *(const u32x4u_t*)(p[i] + (i == xg ? o : x));
+        st[i] = __builtin_bit_cast(double2, v);
+      }
+    }
+    if (GATHER) {
+      a += g.nbt;
+    } else {
+      b0 += KT;
+      if (b0 >= g.B) {
+        b0 = 0;
+        ++a;
+      }
+    }
+  };
+  auto store = [&](char* buf) {
+#pragma unroll
+    for (int i = 0; i < FLAT_GROUPS; ++i) {
+      if (i >= ng) continue;
+      const bool gat = GATHER && i < xg;
+      const int row = i * GROUP + (gat ? lane : tid >> 3), q = gat ? wave : tid & 7;
+      double2 v = st[i];
+      if (lo > 0 || nk < KT) {
+        if (2 * q < lo || 2 * q >= nk) v.x = 0.0;
+        if (2 * q + 1 < lo || 2 * q + 1 >= nk) v.y = 0.0;
+      }
+      *(double2*)(buf + lds_at<E>(row, q)) = v;
+    }
+  };
+
+  f64x4_t acc[FLAT_BLOCKS][4];
+#pragma unroll
+  for (int i = 0; i < FLAT_BLOCKS; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[i][q][v] = 0.0;
+  const int lg = lane >> 4, li = lane & 15;
+  if (kt0 < kt1) {
+    load();
+    store(lds);
+    if (kt0 + 1 < kt1) load();
+  }
+  __syncthreads();
+  for (int64_t kt = kt0; kt < kt1; ++kt) {
+    const char* cur = lds + ((kt - kt0) & 1) * FLAT_BUF;
+    if (kt + 1 < kt1) store(lds + ((kt - kt0 + 1) & 1) * FLAT_BUF);
+    if (kt + 2 < kt1) load();
+#pragma unroll
+    for (int i = 0; i < FLAT_BLOCKS; ++i) {
+      if (!mask[i]) continue;
+      double2 x[2][2], y[2][2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          x[t][m] = *(const double2*)(cur + ra[i] * 128 + lds_at<E>(li, 2 * lg + t) + 16 * m * 128);
+          y[t][m] = *(const double2*)(cur + rb[i] * 128 + lds_at<E>(li, 2 * lg + t) + 16 * m * 128);
+        }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if ((mask[i] >> q) & 1) {
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            acc[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t][q >> 1].x, y[t][q & 1].x, acc[i][q], 0, 0, 0);
+            acc[i][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t][q >> 1].y, y[t][q & 1].y, acc[i][q], 0, 0, 0);
+          }
+        }
+    }
+    __syncthreads();
+  }
+
+  double* part = (double*)g.partial + (int64_t)split * g.blocks * (BLK * BLK);
+#pragma unroll
+  for (int i = 0; i < FLAT_BLOCKS; ++i) {
+    if (!mask[i]) continue;
+    double* out = part + (int64_t)blk[i] * (BLK * BLK);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(16 * (q >> 1) + 4 * v + lg) * BLK + 16 * (q & 1) + li] = acc[i][q][v];
+  }
+}
+
 // Modes of a few rows (I and S at most 8: the channels of images and video): bound
 // by the read of X and the sketch, which the tiles above, of 64 rows each, spend on
 // staging rows that do not exist.  A thread takes V consecutive K values of every
@@ -1047,6 +1221,11 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
     g.splits = (int)std::max<int64_t>(std::min({ceil_div(g.nkt, 4 * 256), 4 * (int64_t)cu_count, fit}), 1);
     return g;
   }
+  // (five staged groups; faster than the tiles over that whole range, see there)
+  if (elem == E_F64 && !g.thin && I <= 256 && S <= GROUP) {
+    g.flat = 1;
+    g.ntiles = (int)ceil_div(g.blocks, 8 * FLAT_BLOCKS);
+  }
   const int kt = g.wide ? WIDE_K : gram_kt(elem);
   g.gather = B < kt;
   g.nbt = g.gather ? std::min(kt / B, A) : ceil_div(B, kt);
@@ -1064,7 +1243,7 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   for (int64_t s = 1; s <= std::min<int64_t>(g.nkt, 8 * (int64_t)cu_count); ++s) {
     if (s > 1 && (size_t)s * g.blocks * BLK * BLK * (elem == E_F64 ? 8 : 4) > limit) break;
     const int64_t n = ceil_div(g.ntiles * s, cu_count);
-    const double share = g.wide ? 1.2 * (double)n : g.thin ? 4.0 * (double)ceil_div(n, 4) : (double)n + (n & 1 ? 0.6 : 0.0);
+    const double share = g.wide || g.flat ? 1.2 * (double)n : g.thin ? 4.0 * (double)ceil_div(n, 4) : (double)n + (n & 1 ? 0.6 : 0.0);
     const double cost = share * ((double)ceil_div(g.nkt, s) + 6.0) + per * s / 7.5e6;
     if (best < 0 || cost < best) {
       best = cost;
@@ -1106,6 +1285,12 @@ static hipError_t launch_tiny(const GramArgs& g, hipStream_t s) {
 template <int E>
 static hipError_t launch_gram(const GramArgs& g, hipStream_t s) {
   if (g.tiny) return launch_tiny<E>(g, s);
+  if constexpr (E == E_F64)
+    if (g.flat) {
+      if (g.gather) hipLaunchKernelGGL(gram_flat_kernel<true>, dim3((unsigned)(g.ntiles * g.splits)), dim3(512), 0, s, g);
+      else hipLaunchKernelGGL(gram_flat_kernel<false>, dim3((unsigned)(g.ntiles * g.splits)), dim3(512), 0, s, g);
+      return hipGetLastError();
+    }
   if (g.wide) return g.gather ? launch_wide<true>(g, s) : launch_wide<false>(g, s);
   if (g.thin) return g.gather ? launch_tiles<E, true, GROUPS_THIN>(g, s) : launch_tiles<E, false, GROUPS_THIN>(g, s);
   return g.gather ? launch_tiles<E, true, GROUPS_TILE>(g, s) : launch_tiles<E, false, GROUPS_TILE>(g, s);

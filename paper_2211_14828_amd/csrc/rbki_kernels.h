@@ -22,6 +22,7 @@ struct GramArgs {
   int gen, om_mode;         // gram.hip: the sketch is made by the kernel (set seed and om_mode, not omegaT)
   uint64_t seed;
   int tiny;                 // I <= 8, S <= 8: products in registers (gram.hip)
+  int flat;                 // float64, 65 to 256 rows (gram.hip)
   int wide;                 // float32: 256 x 256 tiles (gram.hip)
   void* partial;            // [splits][blocks][32*32] float (double for fp64), gram.hip
   int64_t part_stride;      // elements per split (pipelined bf16 form)
