@@ -110,6 +110,11 @@ def load_traffic(workload, precision):
 COPY_KERNEL = "AUnaryFunctor<float, float, float, at::native::binary_internal::MulFunctor<float> >"
 
 
+# the Gram kernels of the precision forms and of the plain ones (by element type and rows)
+PIPE_GRAM = ("gram_pipe_kernel",)
+PLAIN_GRAM = ("gram_tile_kernel", "gram_wide_kernel", "gram_flat_kernel", "gram_tiny_kernel")
+
+
 def _pmc_rows(path, counter):
     import csv
     out = {}
@@ -126,22 +131,22 @@ def traffic_from(fetch_csv, write_csv, workload, precision, copy_mib, command):
     """HBM bytes per Gram launch from two rocprofv3 --pmc runs (FETCH_SIZE, then
     WRITE_SIZE, KiB per dispatch), each scaled by what the same counter reads
     for the calibration copy of known size in the same program."""
-    kernel = "gram_pipe_kernel" if precision in ("mixed_bf16", "mixed_fp8") else "gram_sketch_kernel"
+    kernels = PIPE_GRAM if precision in ("mixed_bf16", "mixed_fp8") else PLAIN_GRAM
     known = copy_mib * 1024 * 1024
     res = {}
     for name, path, counter in (("fetch", fetch_csv, "FETCH_SIZE"), ("write", write_csv, "WRITE_SIZE")):
         rows = _pmc_rows(path, counter)
         copies = [v * 1024 for k, v in rows.values() if COPY_KERNEL in k]
-        grams = [v * 1024 for k, v in rows.values() if kernel in k]
+        grams = [v * 1024 for k, v in rows.values() if any(g in k for g in kernels)]
         if not copies or not grams:
-            raise SystemExit(f"{path}: no {COPY_KERNEL} or {kernel} dispatches with {counter}")
+            raise SystemExit(f"{path}: no {COPY_KERNEL} or {kernels} dispatches with {counter}")
         scale = known / (sum(copies) / len(copies))
         res[name] = {"raw_bytes_per_launch": sum(grams) / len(grams), "copy_scale": scale,
                      "bytes_per_launch": sum(grams) / len(grams) * scale, "launches": len(grams)}
     path = os.path.join(ROOT, "profiles", "traffic.json")
     db = json.load(open(path)) if os.path.exists(path) else {}
     db[f"gram/{workload}/{precision}"] = {
-        "kernel": kernel, "bytes_per_launch": res["fetch"]["bytes_per_launch"] + res["write"]["bytes_per_launch"],
+        "kernel": kernels[0], "bytes_per_launch": res["fetch"]["bytes_per_launch"] + res["write"]["bytes_per_launch"],
         "fetch": res["fetch"], "write": res["write"], "copy_bytes": known,
         "source_hash": source_hash(), "command": command}
     with open(path, "w") as fh:
@@ -470,7 +475,12 @@ def main():
     achieved = alg_gram / (avg_gram_ms * 1e-3) / 1e12
     in_dt = {"float32": "f32", "float64": "f64", "bfloat16": "bf16"}[w["dtype"]]
     gram_dtype = {"plain": in_dt, "mixed_bf16": "bf16", "mixed_fp8": "fp8"}[args.precision]
-    kernel = "gram_pipe_kernel" if gram_dtype in ("bf16", "fp8") else "gram_sketch_kernel"
+    if args.precision != "plain":
+        kernel = "gram_pipe_kernel"
+    elif gram_dtype == "f32":
+        kernel = "gram_wide_kernel" if max(dims) > 384 else "gram_tile_kernel"
+    else:
+        kernel = "gram_flat_kernel" if gram_dtype == "f64" and 64 < max(dims) <= 256 else "gram_tile_kernel"
     peak = PEAK_TFLOPS[gram_dtype]
     stages = {}
     for k in ("omega", "gram", "chain", "eig", "ttm", "error", "convert"):

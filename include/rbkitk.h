@@ -54,8 +54,10 @@ typedef enum { RBKI_F64 = 0, RBKI_F32 = 1, RBKI_BF16 = 2 } rbki_dtype;
 /* Arithmetic of the products that read the tensor (sketch, Gram/Krylov
  * products, mode products, error).  Orthonormalisation, the projected
  * eigenproblem and all norms are float64 in every form.
- *   PLAIN      : the tensor's own type (fp64 MFMA for F64, fp32 MFMA for F32,
- *                bf16 MFMA for BF16), fp32 or fp64 accumulation.
+ *   PLAIN      : the tensor's own type (fp64 MFMA for F64, bf16 MFMA for
+ *                BF16; for F32 fp32 MFMA, and in the sketch and Gram products
+ *                bf16 MFMA on three bf16 parts that hold each value exactly),
+ *                fp32 or fp64 accumulation.
  *   MIXED_BF16 : a bf16 copy of X feeds bf16 MFMA with fp32 accumulation.
  *   MIXED_FP8  : an e4m3 copy of X with power-of-two scales per 32^N block
  *                feeds the Gram and sketch products (block-scaled fp8 MFMA,
