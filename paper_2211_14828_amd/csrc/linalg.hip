@@ -189,6 +189,80 @@ __device__ inline double lane_f64(double v, int l) {
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
+// G = Y Y^T formed by the workgroup itself, the lower blocks into Ls: for few columns
+// (chol_forms_g) the product is less than the launch of one.  Wave w takes the column
+// blocks of 16 congruent to w modulo 4; lane group g of a block columns 4 g + u (the
+// same for both operands), so a lane reads 32 consecutive bytes.  The waves' sums are
+// added in order.  Measured, a step's two launches / the one: s = 15, n = 64 to 200 9.6 /
+// 8.3 us; s = 30, n = 190 to 300 14.2 / 15.0, level with the gap between launches, and n
+// = 400 15.8 / 18.2.  So up to 768 columns times blocks; it also takes 6 of the 58
+// launches of a served request (3910 -> 4150 solves/s with 16 slots, host-bound).
+typedef double d2u_t __attribute__((ext_vector_type(2), aligned(8)));
+constexpr int CHOL_FORM_NB = 4;
+inline bool chol_forms_g(int64_t s, int64_t n) {
+  const int64_t nb = ceil_div(s, 16);
+  return nb <= CHOL_FORM_NB && n <= 512 && nb * (nb + 1) / 2 * n <= 768;
+}
+
+template <int NB, int LD>
+__device__ inline void form_gram(double (*Ls)[LD], const double* Y, int s, int64_t n, int wave, int lane) {
+  constexpr int AHEAD = NB <= 2 ? 4 : 2;
+  const int li = lane & 15, lg = lane >> 4;
+  f64x4_t acc[NB * (NB + 1) / 2];
+#pragma unroll
+  for (int t = 0; t < NB * (NB + 1) / 2; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[t][v] = 0.0;
+  for (int64_t k0 = 16 * wave; k0 < n; k0 += 64 * AHEAD) {
+    double f[AHEAD][NB][4];
+#pragma unroll
+    for (int h = 0; h < AHEAD; ++h)
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        // (the last columns from where they end, those before moved out)
+        const int row = 16 * t + li;
+        const int64_t k = k0 + 64 * h + 4 * lg, from = k + 4 <= n ? k : n >= 4 ? n - 4 : 0;
+        const double* p = Y + (int64_t)(row < s ? row : s - 1) * n + from;
+        double v[4];
+        if (n >= 4) {
+          const d2u_t v0 = *(const d2u_t*)p, v1 = *(const d2u_t*)(p + 2);
+          v[0] = v0.x; v[1] = v0.y; v[2] = v1.x; v[3] = v1.y;
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = p[u < n ? u : n - 1];
+        }
+        const int skip = (int)(k - from < 4 ? k - from : 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) f[h][t][u] = row < s && u >= skip && from + u < n ? v[u] : 0.0;
+      }
+#pragma unroll
+    for (int h = 0; h < AHEAD; ++h)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int ti = 0; ti < NB; ++ti)
+#pragma unroll
+          for (int tj = 0; tj <= ti; ++tj)
+            acc[ti * (ti + 1) / 2 + tj] =
+                __builtin_amdgcn_mfma_f64_16x16x4f64(f[h][ti][u], f[h][tj][u], acc[ti * (ti + 1) / 2 + tj], 0, 0, 0);
+  }
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int ti = 0; ti < NB; ++ti)
+#pragma unroll
+        for (int tj = 0; tj <= ti; ++tj)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            double& d = Ls[16 * ti + 4 * v + lg][16 * tj + li];
+            const double x = acc[ti * (ti + 1) / 2 + tj][v];
+            d = w == 0 ? x : d + x;
+          }
+    }
+    __syncthreads();
+  }
+}
+
 template <int NB>
 __global__ void __launch_bounds__(256) chol_solve_kernel(CholArgs a) {
   constexpr int SM = 16 * NB, LD = SM + 4;       // rows 4 banks (of 8 bytes) apart: no conflicts in a fragment
@@ -204,22 +278,6 @@ __global__ void __launch_bounds__(256) chol_solve_kernel(CholArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
-  {
-    const double* G = job.G;
-    double gv[NB * NB];
-#pragma unroll
-    for (int q = 0; q < NB * NB; ++q) {
-      const int e = tid + 256 * q, i = e / SM, j = e - i * SM;
-      gv[q] = G[(i < s ? i : s - 1) * s + (j < s ? j : s - 1)];
-    }
-#pragma unroll
-    for (int q = 0; q < NB * NB; ++q) {
-      const int e = tid + 256 * q, i = e / SM, j = e - i * SM;
-      const double v = (i < s && j < s) ? gv[q] : 0.0;
-      Ls[i][j] = v;
-      if (i == j) diag[i] = v;
-    }
-  }
   // this wave's columns of Y: item v of lane (li, lg) of block b is row 16 b + 4 v + lg
   const int64_t c = (int64_t)blockIdx.x * 64 + wave * 16 + li;
   const int64_t cc = c < n ? c : n - 1;
@@ -231,9 +289,32 @@ __global__ void __launch_bounds__(256) chol_solve_kernel(CholArgs a) {
       const int k = 16 * b + 4 * v + lg;
       y[b][v] = job.Y[(int64_t)(k < s ? k : s - 1) * n + cc];
     }
+  bool formed = false;
+  if constexpr (NB <= CHOL_FORM_NB) {
+    if (job.form_g) {
+      form_gram<NB, LD>(Ls, job.Y, s, n, wave, lane);
+      formed = true;
+    }
+  }
+  if (!formed) {
+    const double* G = job.G;
+    double gv[NB * NB];
+#pragma unroll
+    for (int q = 0; q < NB * NB; ++q) {
+      const int e = tid + 256 * q, i = e / SM, j = e - i * SM;
+      gv[q] = G[(i < s ? i : s - 1) * s + (j < s ? j : s - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < NB * NB; ++q) {
+      const int e = tid + 256 * q, i = e / SM, j = e - i * SM;
+      Ls[i][j] = (i < s && j < s) ? gv[q] : 0.0;
+    }
+  }
+  __syncthreads();
+  for (int k = tid; k < SM; k += 256) diag[k] = Ls[k][k];
   double mx = 0.0;
   if (job.ref2)
-    for (int k = lane; k < s; k += 64) mx = fmax(mx, job.ref2[k]);
+    for (int k = lane; k < s; k += 64) mx = fmax(mx, formed ? (job.norms ? Ls[k][k] : job.ref2[k]) : job.ref2[k]);
   const double abs_floor = job.tau_abs * job.tau_abs * warp_max(mx);
   const double tau_rel = a.tau_rel;
   const DimBudget bud = job.bud;
@@ -975,29 +1056,37 @@ hipError_t row_norms2(const double* Y, int64_t s, int64_t n, double* out, hipStr
 hipError_t chol_orth_batched(const CholJob* jobs, int njobs, double tau_rel, hipStream_t st) {
   if (njobs < 1 || njobs > kGemmJobs) return hipErrorInvalidValue;
   GemmJob gj[kGemmJobs];
-  CholArgs fit = {};
-  fit.tau_rel = tau_rel;
-  int nfit = 0;
-  int64_t smax = 0, nmax = 0;
+  // (sketches of more than 64 columns in a launch of their own)
+  CholArgs fit[2] = {};
+  int nfit[2] = {}, ng = 0;
+  int64_t smax = 0, nmax[2] = {};
   for (int i = 0; i < njobs; ++i) {
-    const CholJob& j = jobs[i];
-    gj[i] = gemm_job(0, 1, j.s, j.s, j.n, 1.0, j.Y, j.n, j.Y, j.n, 0.0, j.G, j.s);
-    gj[i].norms = j.norms;
+    CholJob j = jobs[i];
+    j.form_g = chol_forms_g(j.s, j.n);
+    if (!j.form_g) {
+      gj[ng] = gemm_job(0, 1, j.s, j.s, j.n, 1.0, j.Y, j.n, j.Y, j.n, 0.0, j.G, j.s);
+      gj[ng++].norms = j.norms;
+    }
     if (j.s <= CHOL_MAX) {
-      fit.job[nfit++] = j;
-      smax = std::max(smax, j.s);
-      nmax = std::max(nmax, j.n);
+      const int w = j.s > 64;
+      fit[w].tau_rel = tau_rel;
+      fit[w].job[nfit[w]++] = j;
+      if (!w) smax = std::max(smax, j.s);
+      nmax[w] = std::max(nmax[w], j.n);
     }
   }
-  hipError_t e = dgemm_batched(gj, njobs, st);
-  if (e != hipSuccess) return e;
-  if (nfit) {
-    const dim3 grid((unsigned)ceil_div(nmax, 64), nfit), block(256);
-    if (smax <= 16) hipLaunchKernelGGL(chol_solve_kernel<1>, grid, block, 0, st, fit);
-    else if (smax <= 32) hipLaunchKernelGGL(chol_solve_kernel<2>, grid, block, 0, st, fit);
-    else if (smax <= 48) hipLaunchKernelGGL(chol_solve_kernel<3>, grid, block, 0, st, fit);
-    else if (smax <= 64) hipLaunchKernelGGL(chol_solve_kernel<4>, grid, block, 0, st, fit);
-    else hipLaunchKernelGGL(chol_solve_kernel<6>, grid, block, 0, st, fit);
+  hipError_t e = hipSuccess;
+  if (ng && (e = dgemm_batched(gj, ng, st)) != hipSuccess) return e;
+  if (nfit[0]) {
+    const dim3 grid((unsigned)ceil_div(nmax[0], 64), nfit[0]), block(256);
+    if (smax <= 16) hipLaunchKernelGGL(chol_solve_kernel<1>, grid, block, 0, st, fit[0]);
+    else if (smax <= 32) hipLaunchKernelGGL(chol_solve_kernel<2>, grid, block, 0, st, fit[0]);
+    else if (smax <= 48) hipLaunchKernelGGL(chol_solve_kernel<3>, grid, block, 0, st, fit[0]);
+    else hipLaunchKernelGGL(chol_solve_kernel<4>, grid, block, 0, st, fit[0]);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (nfit[1]) {
+    hipLaunchKernelGGL(chol_solve_kernel<6>, dim3((unsigned)ceil_div(nmax[1], 64), nfit[1]), dim3(256), 0, st, fit[1]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   for (int i = 0; i < njobs; ++i) {

@@ -158,6 +158,7 @@ struct CholJob {
   double* norms;
   double tau_abs;
   DimBudget bud;
+  bool form_g;               // set by chol_orth_batched: the step's kernel forms G (and takes norms from it)
 };
 struct CholArgs {
   CholJob job[kGemmJobs];

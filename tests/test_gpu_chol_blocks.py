@@ -11,7 +11,9 @@ from oracle.philox import omega
 pytestmark = pytest.mark.gpu
 
 SIZES = [(9, 1), (70, 2), (63, 15), (64, 16), (65, 17), (130, 31), (100, 33), (120, 48), (190, 49), (129, 64), (200, 65),
-         (140, 80), (150, 95), (193, 96), (230, 97)]
+         (140, 80), (150, 95), (193, 96), (230, 97),
+         # G formed by the step itself (few columns) and just past it
+         (3, 2), (512, 14), (513, 14), (256, 20), (257, 20), (128, 40), (129, 40), (76, 64), (77, 64)]
 
 
 @pytest.mark.parametrize("deficient", [False, True])
