@@ -1122,7 +1122,8 @@ __global__ void omega_kernel(uint64_t seed, uint32_t mode, int64_t total, void* 
       if (L + 1 < total) o[L + 1] = z1;
     } else {
       float z0, z1;
-      gauss_pair_f32((uint64_t)m, mode, 0u, seed, z0, z1);
+      if (E == E_F32) gauss_pair_f32((uint64_t)m, mode, 0u, seed, z0, z1);
+      else gauss_pair_bf16((uint64_t)m, mode, 0u, seed, z0, z1);
       if (E == E_F32) {
         float* o = (float*)out;
         o[L] = z0;

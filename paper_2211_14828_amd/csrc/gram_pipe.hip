@@ -612,7 +612,7 @@ __global__ void omega_block_kernel(uint64_t seed, uint32_t mode, int64_t S, int6
   for (int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; m < npairs;
        m += (int64_t)gridDim.x * blockDim.x) {
     float z[2];
-    gauss_pair_f32((uint64_t)m, mode, 0u, seed, z[0], z[1]);
+    gauss_pair_bf16((uint64_t)m, mode, 0u, seed, z[0], z[1]);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int64_t L = 2 * m + h;

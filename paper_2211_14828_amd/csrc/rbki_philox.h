@@ -92,7 +92,7 @@ __device__ inline float minus_ln(double u) {
   return -fmaf(k, LN2_HI, f - (h - fmaf(s, h + R, k * LN2_LO)));
 }
 
-// Same pair in single precision (for the float and bfloat16 forms).  The
+// Same pair in single precision, for the float sketch.  The
 // uniforms are exact in double, and so are the reductions of the logarithm's
 // argument (above) and of the angle, 2 pi u2 = pi/2 (q + y) with q = round(4 u2), so
 // the float arguments carry small absolute errors.  sin and cos of pi/2 y, |y| <=
@@ -123,6 +123,31 @@ __device__ inline void gauss_pair_f32(uint64_t m, uint32_t mode, uint32_t tag, u
   const float c = ((qi + 1) & 2) ? -a : a, d = (qi & 2) ? -b : b;
   z_even = r * c;
   z_odd = r * d;
+}
+
+// The same pair for the bfloat16 sketches, whose values are rounded to bfloat16: the
+// logarithm, root and sine and cosine of the library, with the same reductions in
+// double (ln u1 as log1p(-(1 - u1)) when u1 >= 1/2; the angle 2 pi u2 as pi (x - n)
+// with n = round(2 u2)).  It differs from the pair above in the last bits, and a value
+// near a rounding edge of bfloat16 then moves by a whole step of 2^-8: that changes a
+// basis of few steps by up to 1e-6, a factor's entries across their own edges in the
+// first bfloat16 product, and so the core by some 1e-5.  The bfloat16 sketch of a seed
+// is therefore fixed by this function.
+__device__ inline void gauss_pair_bf16(uint64_t m, uint32_t mode, uint32_t tag, uint64_t seed,
+                                       float& z_even, float& z_odd) {
+  PhiloxOut o = philox4x32_10((uint32_t)m, (uint32_t)(m >> 32), mode, tag, (uint32_t)seed,
+                              (uint32_t)(seed >> 32));
+  const double u1 = unit_open(o.w0, o.w1);
+  const double u2 = unit_open(o.w2, o.w3);
+  const float ln = u1 < 0.5 ? logf((float)u1) : log1pf(-(float)(1.0 - u1));
+  const float r = sqrtf(-2.0f * ln);
+  const double x = 2.0 * u2;                  // angle / pi in (0, 2)
+  const double nr = rint(x);                  // 0, 1 or 2
+  float s, c;
+  sincospif((float)(x - nr), &s, &c);
+  if (nr == 1.0) { s = -s; c = -c; }          // shift by pi
+  z_even = r * c;
+  z_odd = r * s;
 }
 
 // The same pair for the block-scaled e4m3 sketch, whose values are rounded to
