@@ -120,6 +120,7 @@ struct ModeGeom {
   bool pipe = false;              // mixed forms: the pipelined Gram kernel on a blocked copy
   int pelem = 0;                  // its element type (E_BF16 or E_FP8)
   int64_t nkt = 0;                // its K tiles
+  bool any_order = false;         // bfloat16: the factor is not rounded to bfloat16 for a product (gram_plan)
   bool direct = false;            // products with X X^T are formed from X, which is kept in C's place
 };
 
@@ -254,6 +255,10 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
   P.rows_pad = pad64(P.T / P.dims[P.N - 1]);
   double best = -1.0;
   for (int n = 0; n < P.N; ++n) {
+    const double ratio = (double)P.dims[n] / (double)P.ranks[n];
+    if (ratio > best) { best = ratio; P.first_mode = n; }
+  }
+  for (int n = 0; n < P.N; ++n) {
     ModeGeom& g = P.m[n];
     g.A = 1;
     for (int k = 0; k < n; ++k) g.A *= P.dims[k];
@@ -273,8 +278,8 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
     g.Sp = P.power ? g.S : g.S * (P.q + 1);
     if (g.Sp > 1200) return fail(RBKI_E_UNSUPPORTED, "Krylov width %lld > 1200 (mode %d)", (long long)g.Sp, n);
     g.direct = direct_mode(P, g);
-    const double ratio = (double)g.I / (double)g.R;
-    if (ratio > best) { best = ratio; P.first_mode = n; }
+    // (the sequential form's first product takes the factor of mode 0)
+    g.any_order = n != 0 && n != P.first_mode;
     P.maxI = std::max(P.maxI, g.I);
     P.maxS = std::max(P.maxS, g.S);
     P.maxSp = std::max(P.maxSp, g.Sp);
@@ -286,7 +291,7 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
       P.maxM = std::max(P.maxM, g.m);
       P.ybytes = std::max(P.ybytes, (size_t)g.I * g.m * elem_size(g.yelem));
       P.maxSJ = std::max(P.maxSJ, g.S * g.m);
-      GramArgs gy = gram_plan(g.yelem, 1, g.I, g.m, (int)g.S, cu_count());
+      GramArgs gy = gram_plan(g.yelem, 1, g.I, g.m, (int)g.S, cu_count(), -1, g.any_order);
       P.partial_bytes = std::max(P.partial_bytes, gram_partial_bytes(gy, g.yelem));
     }
     if (P.need_pad) {
@@ -303,7 +308,7 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
       } else {
         P.maxSJ = std::max(P.maxSJ, g.S * A * Bp);
         if (n == P.N - 1) P.need_xt16 = true;
-        GramArgs ga = gram_plan(E_BF16, A, g.I, Bp, (int)g.S, cu_count());
+        GramArgs ga = gram_plan(E_BF16, A, g.I, Bp, (int)g.S, cu_count(), -1, g.any_order);
         P.partial_bytes = std::max(P.partial_bytes, gram_partial_bytes(ga, E_BF16));
       }
     } else {
@@ -653,7 +658,7 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
         ProfScope ps("omega", st);
         HIPCHK(launch_omega_pad(P.seed, n, S, g.J, g.B, P.dims[P.N - 1], A * Bp, L.omegaT, st));
       }
-      GramArgs ga = gram_plan(E_BF16, A, I, Bp, (int)S, cu_count());
+      GramArgs ga = gram_plan(E_BF16, A, I, Bp, (int)S, cu_count(), -1, g.any_order);
       ga.X = last ? b.xt : b.xpad;
       ga.omegaT = L.omegaT;
       ga.partial = L.partial;
@@ -699,7 +704,7 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
     // rows) from the gathered sample
     HIPCHK(launch_sample_columns(P.seed, n, g.J, g.m, L.cols, st));
     HIPCHK(launch_gather_columns(P.xelem, xsrc, I, g.B, L.cols, g.m, g.yelem, L.ysmp, st));
-    GramArgs gy = gram_plan(g.yelem, 1, I, g.m, (int)S, cu_count());
+    GramArgs gy = gram_plan(g.yelem, 1, I, g.m, (int)S, cu_count(), -1, g.any_order);
     gy.X = L.ysmp;
     gy.omegaT = L.omegaT;
     gy.seed = P.seed;

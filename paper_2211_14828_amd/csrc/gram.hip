@@ -41,6 +41,13 @@
 // staged layout needs no transposition.  A slab's last tile overlaps the one
 // before it, with the values they share zeroed, so no load is masked.
 //
+// The bfloat16 tiles keep one order of their sums, whatever the launch: slices by the
+// count of 128-row tiles (slices), K tiles of 64 values from the slab's start with
+// zeros past its end, and in the MFMA of step t the values 8 t .. and 32 + 8 t ...
+// One factor of a decomposition is rounded to bfloat16 again in the first mode
+// product, and an entry that another order moves by 1e-7 across a rounding edge moves
+// the core by a few 1e-5 (7e-5 at 100 x 128 x 144).
+//
 // Workgroups are dispatched round-robin over the 8 XCDs.  Those of one XCD take
 // consecutive (split, tile) pairs, so the tiles of a split, which share a slab
 // of X, run on one XCD (or two) and the slab is fetched from HBM once into its
@@ -124,6 +131,21 @@ __device__ inline void load_rows(Piece& r, const typename Op<E>::T* const (&p)[2
     const u32x4u_t v = *(const u32x4u_t*)(p[j] + off);
     r.u[4 * j] = v.x; r.u[4 * j + 1] = v.y; r.u[4 * j + 2] = v.z; r.u[4 * j + 3] = v.w;
   }
+}
+
+// The same for a tile that ends with its slab after n < KT values (bfloat16): the
+// values past it are zeros.
+__device__ inline void load_rows_end(Piece& r, const bf16_t* const (&p)[2], int64_t off, int n) {
+  const int k0 = (threadIdx.x & 7) * 8;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t lo = 0, hi = 0;
+      if (k0 + 2 * i < n) lo = p[j][off + 2 * i];
+      if (k0 + 2 * i + 1 < n) hi = p[j][off + 2 * i + 1];
+      r.u[4 * j + i] = lo | hi << 16;
+    }
 }
 
 // Rows across the lanes: thread (row tid % 64, wave w) takes K values
@@ -282,7 +304,7 @@ __device__ inline void tile_step(typename Op<E>::Acc (&c)[Op<E>::NACC * MB], con
     const int half = lane >> 5, r = lane & 31;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int at = lds_at<E>(r, 2 * t + half);
+      const int at = lds_at<E>(r, E == E_BF16 ? t + 4 * half : 2 * t + half);
       bf16x8_t a[MB][NP], b[2][NP];
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
@@ -427,17 +449,23 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
   const int64_t kt0 = (int64_t)split * g.nkt / g.splits;
   const int64_t kt1 = (int64_t)(split + 1) * g.nkt / g.splits;
   Piece st[NG];
-  auto load = [&](int64_t x, int64_t o) {
+  auto load = [&](const KTile& t) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       if (gn[i] <= 0) continue;
-      if (GATHER && !gom[i]) load_gather<E>(st[i], X, rbyte[i], koff, x, nk);
-      else load_rows<E>(st[i], p[i], gom[i] ? o : x);
+      if constexpr (E == E_BF16 && !GATHER) {
+        if (t.hi < O::KT) {
+          load_rows_end(st[i], p[i], gom[i] ? t.o : t.x, t.hi);
+          continue;
+        }
+      }
+      if (GATHER && !gom[i]) load_gather<E>(st[i], X, rbyte[i], koff, t.x, nk);
+      else load_rows<E>(st[i], p[i], gom[i] ? t.o : t.x);
     }
   };
   // K tile kt: slab a from b0 on (GATHER: g.nbt values of a from a on).  The
   // last tile of a slab (of the mode) is moved back to end with it, its values
-  // that the tile before holds zeroed.  GATHER: the up to B - 1 sketch values
+  // that the tile before holds zeroed; in bfloat16 it stays, with zeros past the end.  GATHER: the up to B - 1 sketch values
   // past nk are read (at the very end of Omega^T from the workspace behind it)
   // and zeroed.
   int64_t a, b0 = 0;
@@ -450,9 +478,9 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
   auto tile_now = [&]() {
     KTile k;
     const int64_t at = GATHER ? a : b0, end = GATHER ? g.A - g.nbt : g.B - O::KT;
-    const int64_t from = at < end ? at : end;
+    const int64_t from = at < end || (E == E_BF16 && !GATHER) ? at : end;
     k.lo = (int)(at - from) * (GATHER ? (int)g.B : 1);
-    k.hi = nk;
+    k.hi = E == E_BF16 && !GATHER && at > end ? (int)(g.B - at) : nk;
     k.x = GATHER ? from * g.I * g.B : a * g.I * g.B + from;
     k.o = GATHER ? from * g.B : a * g.B + from;
     return k;
@@ -481,7 +509,7 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
   KTile now = {};
   if (kt0 < kt1) {
     now = tile_now();
-    load(now.x, now.o);
+    load(now);
   }
   for (int64_t kt = kt0; kt < kt1; ++kt) {
 #pragma unroll
@@ -495,7 +523,7 @@ __global__ void __launch_bounds__(256, NG == GROUPS_THIN ? 4 : 2) gram_tile_kern
     if (kt + 1 < kt1) {
       advance();
       now = tile_now();
-      load(now.x, now.o);
+      load(now);
     }
     if (mask) tile_step<E, MB>(acc, lds, plane, lane, ra, rb, mask);
     __syncthreads();
@@ -1161,22 +1189,29 @@ int elem_size(int elem) { return elem == E_F64 ? 8 : elem == E_F32 ? 4 : elem ==
 
 static int gram_kt(int elem) { return elem == E_F64 ? Op<E_F64>::KT : elem == E_F32 ? Op<E_F32>::KT : Op<E_BF16>::KT; }
 
-// The most bytes that the partials may take: two slices per compute unit of
-// 128 x 128 tiles of the rows and the sketch, each of at least 8 K tiles.
-static size_t partial_limit(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count) {
+// Two slices per compute unit of 128 x 128 tiles of the rows and the sketch, each of
+// at least 8 K tiles: the slices of the bfloat16 form, and what bounds the others'
+// partials.
+static int64_t slices(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int64_t& tiles) {
   const int64_t nt = ceil_div(I, 128);
   const bool thin = elem == E_F32 && I <= 64 && S >= 1 && S <= 64;
-  const int64_t tiles = thin ? 1 : nt * (nt + 1) / 2 + nt * ceil_div(S, 128);
+  tiles = thin ? 1 : nt * (nt + 1) / 2 + nt * ceil_div(S, 128);
   const int kt = gram_kt(elem);
   const int64_t nkt = B > 1 ? A * ceil_div(B, kt) : ceil_div(A, kt);
   int64_t splits = std::min(std::max<int64_t>(ceil_div(2 * (int64_t)cu_count, tiles), 1), std::max<int64_t>(nkt / 8, 1));
   if (splits >= 8) splits = (splits + 7) / 8 * 8;
-  splits = std::min(splits, std::max<int64_t>(nkt, 1));
+  return std::min(splits, std::max<int64_t>(nkt, 1));
+}
+
+// The most bytes that the partials may take.
+static size_t partial_limit(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count) {
+  int64_t tiles;
+  const int64_t splits = slices(elem, A, I, B, S, cu_count, tiles);
   const size_t more = elem == E_F32 && A * I * B >= ((int64_t)1 << 26) ? (size_t)16 << 20 : 0;
   return (size_t)(splits * tiles) * 128 * 128 * (elem == E_F64 ? 8 : 4) + more;
 }
 
-GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch) {
+GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch, bool any_order) {
   GramArgs g = {};
   g.A = A;
   g.I = I;
@@ -1210,7 +1245,7 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   }
   const int nb = (int)ceil_div(I, BLK);
   g.blocks = nb * (nb + 1) / 2 + (int)ceil_div(S, BLK) * nb;
-  if (I <= TINY && S <= TINY) {
+  if (I <= TINY && S <= TINY && (elem != E_BF16 || any_order)) {
     // at least 4 chunks to a thread, at most 4 workgroups to a compute unit
     g.tiny = 1;
     g.gen = 0;
@@ -1231,6 +1266,11 @@ GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_coun
   g.gather = B < kt;
   g.nbt = g.gather ? std::min(kt / B, A) : ceil_div(B, kt);
   g.nkt = g.gather ? ceil_div(A, g.nbt) : A * g.nbt;
+  if (elem == E_BF16) {
+    int64_t tiles128;
+    g.splits = (int)slices(elem, A, I, B, S, cu_count, tiles128);
+    return g;
+  }
   // Splits: a compute unit's share of the workgroups, two at a time (one alone
   // leaves the matrix cores idle between its loads and its products: taken as
   // 1.6 of the time of each of two), times a workgroup's K tiles plus about 6

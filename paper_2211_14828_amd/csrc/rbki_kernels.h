@@ -35,7 +35,10 @@ struct GramArgs {
 
 int elem_size(int elem);
 // S_scratch (default S): the sketch width whose partials bound this plan's.
-GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch = -1);
+// any_order: a bfloat16 mode of few rows may take the form in registers, whose sums
+// have another order than the tiles'.
+GramArgs gram_plan(int elem, int64_t A, int64_t I, int64_t B, int S, int cu_count, int S_scratch = -1,
+                   bool any_order = false);
 size_t gram_partial_bytes(const GramArgs& g, int elem);
 hipError_t launch_gram_main(int elem, const GramArgs& g, hipStream_t s);
 hipError_t launch_gram_reduce(int elem, const GramArgs& g, double* C, double* Wt, hipStream_t s);
