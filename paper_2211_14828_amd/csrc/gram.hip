@@ -1101,37 +1101,44 @@ __global__ void __launch_bounds__(256) gram_tiny_kernel(GramArgs g) {
 // W^T (S x I), float64.  64 consecutive values of a block per workgroup, the
 // splits dealt to 16 groups of lanes whose sums are added in order, so that a
 // few thousand outputs (a thin mode with hundreds of splits) still fill the
-// chip.
+// chip.  A launch has fewer than 2^32 threads, which modes of 23000 rows and more
+// would pass with a workgroup for every 64 values: at most RED_GRID workgroups, which
+// then take several.
 constexpr int RED_GROUPS = 16;
+constexpr int64_t RED_GRID = 1 << 20;
 template <class Out>
 __global__ void __launch_bounds__(64 * RED_GROUPS) gram_reduce_kernel(GramArgs g, double* C, double* Wt) {
   __shared__ double sums[RED_GROUPS][64];
   const int l = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int64_t e = (int64_t)blockIdx.x * 64 + l;
-  const Out* P = (const Out*)g.partial + e;
   const int64_t stride = (int64_t)g.blocks * (BLK * BLK);
-  double acc = 0.0;
-#pragma unroll 4
-  for (int sp = grp; sp < g.splits; sp += RED_GROUPS) acc += (double)P[sp * stride];
-  sums[grp][l] = acc;
-  __syncthreads();
-  if (grp) return;
-#pragma unroll
-  for (int i = 1; i < RED_GROUPS; ++i) acc += sums[i][l];
-  const int blk = (int)(e / (BLK * BLK)), at = (int)(e % (BLK * BLK));
   const int nb = (int)ceil_div(g.I, BLK), ntri = nb * (nb + 1) / 2;
-  int bi, bj;
-  if (blk < ntri) tri_at(blk, bi, bj);
-  else {
-    bi = (blk - ntri) / nb;
-    bj = (blk - ntri) % nb;
-  }
-  const int64_t i = bi * BLK + at / BLK, j = bj * BLK + at % BLK;
-  if (blk >= ntri) {
-    if (i < g.S && j < g.I) Wt[i * g.I + j] = acc;
-  } else if (i < g.I && j <= i) {
-    C[i * g.I + j] = acc;
-    C[j * g.I + i] = acc;
+  for (int64_t e0 = (int64_t)blockIdx.x * 64; e0 < stride; e0 += (int64_t)gridDim.x * 64) {
+    const int64_t e = e0 + l;
+    const Out* P = (const Out*)g.partial + e;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int sp = grp; sp < g.splits; sp += RED_GROUPS) acc += (double)P[sp * stride];
+    sums[grp][l] = acc;
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int i = 1; i < RED_GROUPS; ++i) acc += sums[i][l];
+      const int blk = (int)(e / (BLK * BLK)), at = (int)(e % (BLK * BLK));
+      int bi, bj;
+      if (blk < ntri) tri_at(blk, bi, bj);
+      else {
+        bi = (blk - ntri) / nb;
+        bj = (blk - ntri) % nb;
+      }
+      const int64_t i = bi * BLK + at / BLK, j = bj * BLK + at % BLK;
+      if (blk >= ntri) {
+        if (i < g.S && j < g.I) Wt[i * g.I + j] = acc;
+      } else if (i < g.I && j <= i) {
+        C[i * g.I + j] = acc;
+        C[j * g.I + i] = acc;
+      }
+    }
+    __syncthreads();               // sums is written again
   }
 }
 
@@ -1347,7 +1354,7 @@ hipError_t launch_gram_main(int elem, const GramArgs& g, hipStream_t s) {
 }
 
 hipError_t launch_gram_reduce(int elem, const GramArgs& g, double* C, double* Wt, hipStream_t s) {
-  const dim3 grid((unsigned)(g.blocks * (BLK * BLK / 64)));
+  const dim3 grid((unsigned)std::min<int64_t>((int64_t)g.blocks * (BLK * BLK / 64), RED_GRID));
   if (elem == E_F64 || g.tiny) hipLaunchKernelGGL(gram_reduce_kernel<double>, grid, dim3(64 * RED_GROUPS), 0, s, g, C, Wt);
   else hipLaunchKernelGGL(gram_reduce_kernel<float>, grid, dim3(64 * RED_GROUPS), 0, s, g, C, Wt);
   return hipGetLastError();

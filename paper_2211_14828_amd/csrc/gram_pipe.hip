@@ -553,45 +553,52 @@ __global__ void __launch_bounds__(256, 1) gram_pipe_kernel(GramArgs g) {
 // layout (part of one row of a tile), the splits dealt to groups of lanes whose sums
 // are added in order: one thread walked all of a value's splits before, with too few
 // reads in flight (400^3, S = 30, 85 splits: 25.7 us, now 14.3).  Each lower-triangle
-// value is written to C(i, j) and C(j, i).
+// value is written to C(i, j) and C(j, i).  At most PRED_GRID workgroups, which then
+// take several runs of 64: a launch has fewer than 2^32 threads.
+constexpr int64_t PRED_GRID = 1 << 20;
 template <int PRED_GROUPS>
 __global__ void __launch_bounds__(64 * PRED_GROUPS) gram_pipe_reduce_kernel(GramArgs g, double* C, double* Wt) {
   const int64_t nCp = (int64_t)g.ntri * PT * PT;
+  const int64_t total = nCp + (int64_t)g.nt * PT * PW;
   const int l = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int64_t e0 = (int64_t)blockIdx.x * 64;           // (tiles' rows are 256 and 64 wide)
-  int64_t i, j = 0, s = -1, off = e0 + l;
-  if (e0 < nCp) {
-    const int tile = (int)(e0 / (PT * PT));
-    const int w = (int)(e0 - (int64_t)tile * PT * PT);
-    int ti, tj;
-    decode_tri(tile, ti, tj);
-    i = (int64_t)ti * PT + (w >> 8);
-    const int64_t j0 = (int64_t)tj * PT + (w & (PT - 1));
-    if (i >= g.I || j0 > i) return;                      // padding rows, or the unused part of a diagonal tile
-    j = j0 + l;
-  } else {
-    const int64_t f = e0 - nCp;
-    i = f / PW;
-    if (i >= g.I) return;
-    s = l;
-    off = g.wpart_off + f + l;
-  }
-  static_assert(PW == 64 && PT == 256, "64 values are part of one row");
-  const float* P = (const float*)g.partial + off;
-  double acc = 0.0;
-#pragma unroll 4
-  for (int sp = grp; sp < g.splits; sp += PRED_GROUPS) acc += (double)P[sp * g.part_stride];
   __shared__ double sums[PRED_GROUPS][64];
-  sums[grp][l] = acc;
-  __syncthreads();
-  if (grp) return;
+  static_assert(PW == 64 && PT == 256, "64 values are part of one row");
+  // (e0 and what follows from it up to the barriers are the same for the workgroup)
+  for (int64_t e0 = (int64_t)blockIdx.x * 64; e0 < total; e0 += (int64_t)gridDim.x * 64) {
+    int64_t i, j = 0, s = -1, off = e0 + l;
+    if (e0 < nCp) {
+      const int tile = (int)(e0 / (PT * PT));
+      const int w = (int)(e0 - (int64_t)tile * PT * PT);
+      int ti, tj;
+      decode_tri(tile, ti, tj);
+      i = (int64_t)ti * PT + (w >> 8);
+      const int64_t j0 = (int64_t)tj * PT + (w & (PT - 1));
+      if (i >= g.I || j0 > i) continue;                  // padding rows, or the unused part of a diagonal tile
+      j = j0 + l;
+    } else {
+      const int64_t f = e0 - nCp;
+      i = f / PW;
+      if (i >= g.I) continue;
+      s = l;
+      off = g.wpart_off + f + l;
+    }
+    const float* P = (const float*)g.partial + off;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int sp = grp; sp < g.splits; sp += PRED_GROUPS) acc += (double)P[sp * g.part_stride];
+    sums[grp][l] = acc;
+    __syncthreads();
+    if (grp == 0) {
 #pragma unroll
-  for (int k = 1; k < PRED_GROUPS; ++k) acc += sums[k][l];
-  if (s >= 0) {
-    if (s < g.S) Wt[s * g.I + i] = acc;
-  } else if (j <= i) {
-    C[i * g.I + j] = acc;
-    C[j * g.I + i] = acc;
+      for (int k = 1; k < PRED_GROUPS; ++k) acc += sums[k][l];
+      if (s >= 0) {
+        if (s < g.S) Wt[s * g.I + i] = acc;
+      } else if (j <= i) {
+        C[i * g.I + j] = acc;
+        C[j * g.I + i] = acc;
+      }
+    }
+    __syncthreads();               // sums is written again
   }
 }
 
@@ -1255,7 +1262,7 @@ hipError_t launch_gram_pipe_reduce(const GramArgs& g, double* C, double* Wt, hip
   // groups: 16 where each still adds several splits; fewer, and so smaller workgroups,
   // where the launch has many of them and there is little to add (1000^3, 25 splits:
   // 19 us with 4, 47 with 16, 28 with one thread a value)
-  const dim3 grid((unsigned)(total / 64));
+  const dim3 grid((unsigned)std::min<int64_t>(total / 64, PRED_GRID));
   if (g.splits >= 48) hipLaunchKernelGGL(gram_pipe_reduce_kernel<16>, grid, dim3(64 * 16), 0, s, g, C, Wt);
   else hipLaunchKernelGGL(gram_pipe_reduce_kernel<4>, grid, dim3(64 * 4), 0, s, g, C, Wt);
   return hipGetLastError();
