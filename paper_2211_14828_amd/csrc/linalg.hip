@@ -1029,7 +1029,7 @@ hipError_t dgemm_batched(const GemmJob* jobs, int njobs, hipStream_t s) {
       red = std::max(red, (int64_t)g.m * g.n);
     }
     const int64_t blocks = tiles * g.splits + (g.norms ? ceil_div(g.m, GW) : 0);
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if (blocks * 64 * GW > 0xffffffff) return hipErrorInvalidValue;   // the threads of a launch
     gx = std::max(gx, (unsigned)blocks);
   }
   if (gx == 0) return hipSuccess;

@@ -468,6 +468,7 @@ struct StreamArgs {
   int chunks;            // output row groups of 16 NR
   int64_t groups;        // column pieces of V (LAST: blocks of 16 V rows)
   int64_t nbg;           // column pieces per slab
+  int64_t wg0;           // first workgroup of this launch
 };
 
 template <int E> struct Vec;
@@ -500,7 +501,7 @@ __global__ void __launch_bounds__(64 * (KS > 1 ? KS : 4)) stream_kernel(StreamAr
   constexpr int NX = KS > 1 ? 1 : V;                 // tensor pieces of a stage
   const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t unit = KS > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
+  const int64_t unit = KS > 1 ? (int64_t)blockIdx.x : (p.wg0 + blockIdx.x) * 4 + wave;
   const int64_t blk = unit / p.chunks;
   const int r0 = (int)(unit - blk * p.chunks) * 16 * NR;
   const T* X = (const T*)p.X;
@@ -1115,15 +1116,23 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 size_t ttm_work_bytes(int, int64_t, int64_t, int64_t, int64_t) { return 0; }
 
+// (a launch has fewer than 2^32 threads: products of more columns take several)
+constexpr int64_t STREAM_GRID = 1 << 22;
+template <int E, int NR, bool LAST>
+static hipError_t launch_stream_waves(StreamArgs& p, int64_t wgs, hipStream_t s) {
+  for (p.wg0 = 0; p.wg0 < wgs; p.wg0 += STREAM_GRID) {
+    hipLaunchKernelGGL((stream_kernel<E, NR, LAST, 1>), dim3((unsigned)std::min(STREAM_GRID, wgs - p.wg0)), dim3(256), 0,
+                       s, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <int E, int NR>
 static hipError_t launch_stream_nr(StreamArgs& p, bool last, hipStream_t s) {
   constexpr int V = Vec<E>::V;
-  if (!last) {
-    const int64_t wgs = ceil_div(ceil_div(p.groups, 16) * p.chunks, 4);
-    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((stream_kernel<E, NR, false, 1>), dim3((unsigned)wgs), dim3(256), 0, s, p);
-    return hipGetLastError();
-  }
+  if (!last) return launch_stream_waves<E, NR, false>(p, ceil_div(ceil_div(p.groups, 16) * p.chunks, 4), s);
   const int64_t wide = ceil_div(p.A, 16 * V) * p.chunks;
   if (wide < 1024 && p.K >= 8 * 4 * V) {
     // too few waves to fill the chip: eight waves share a block's inner range
@@ -1132,10 +1141,8 @@ static hipError_t launch_stream_nr(StreamArgs& p, bool last, hipStream_t s) {
     hipLaunchKernelGGL((stream_kernel<E, NR, true, 8>), dim3((unsigned)wgs), dim3(512), 0, s, p);
     return hipGetLastError();
   }
-  if (ceil_div(wide, 4) > 0x7fffffff) return hipErrorInvalidValue;
   p.groups = ceil_div(p.A, 16 * V);
-  hipLaunchKernelGGL((stream_kernel<E, NR, true, 1>), dim3((unsigned)ceil_div(wide, 4)), dim3(256), 0, s, p);
-  return hipGetLastError();
+  return launch_stream_waves<E, NR, true>(p, ceil_div(wide, 4), s);
 }
 
 template <int E>
@@ -1272,7 +1279,7 @@ hipError_t launch_ttm_first_blocked(int elem, const void* xb, const void* scales
   // the grid against kernels running beside it
   fa.bpw = FIRST_RUN;
   const int64_t wgs = ceil_div(blocks, (int64_t)FIRST_RUN);
-  if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+  if (wgs * 256 > 0xffffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)wgs), block(256);
   if (elem == E_FP8) {
     if (R > 32) hipLaunchKernelGGL((ttm_first_kernel<E_FP8, true>), grid, block, 0, s, fa);
@@ -1307,7 +1314,7 @@ hipError_t launch_residual(int x_elem, const void* X, int op_elem, const void* U
   const int64_t tiles = std::max<int64_t>(ceil_div(I, TILE) * ceil_div(J, TILE), ceil_div(J, RS_COLS));
   double* partial = (double*)work;
   if (bf16_products && op_elem == E_F32 && R <= 64 && (x_elem == E_F32 || x_elem == E_BF16) && J % 4 == 0 &&
-      aligned16(H) && ceil_div(J, RS_COLS) <= 0x7fffffff) {
+      aligned16(H) && ceil_div(J, RS_COLS) * 256 <= 0xffffffff) {
     // the precision forms' streaming pass
     void* Up = (char*)work + ((tiles * 16 + 255) / 256) * 256;
     const dim3 pgrid((unsigned)std::min<int64_t>(ceil_div(I * 64, 256), 4096));
