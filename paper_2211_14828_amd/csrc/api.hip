@@ -966,7 +966,8 @@ rbki_status factor_single(const Plan& P, const Buffers& b, int n, const FinishJo
 
 // Alg. 2, steps 4-5 for all modes: the R leading eigenvectors of every Z in
 // one launch (tridiagonal reduction, bisection, inverse iteration; block
-// Jacobi for matrices beyond that solver's sizes), then U^T = Vt(1:R, :) Q^T
+// Jacobi for matrices beyond that solver's sizes, in an adaptive step mode by
+// mode), then U^T = Vt(1:R, :) Q^T
 // with the sign rule.  width: the order of each Z (null: S'), factors: where the
 // caller's go (null: nowhere yet).
 rbki_status run_factors(const Plan& P, const Buffers& b, const int64_t* width, void* const* factors, int out_type,
@@ -995,6 +996,16 @@ rbki_status run_factors(const Plan& P, const Buffers& b, const int64_t* width, v
       // reduction takes the ordinary launch: a cooperative grid does not
       // share the device with work on other streams
       HIPCHK(eig_top_batched(P.N, Zs, ns, rs, ls, vs, ws, is, st, !P.concurrent));
+    } else if (width) {
+      // (an adaptive step's widths go on to 1200.  From 982 columns on the Jacobi grid
+      // has a workgroup for every eight: three such modes would ask for 369, of a
+      // compute unit each, in one cooperative launch)
+      for (int n = 0; n < P.N; ++n) {
+        if (eig_top_ok(ns[n], rs[n]))
+          HIPCHK(eig_top_batched(1, Zs + n, ns + n, rs + n, ls + n, vs + n, ws + n, is + n, st, !P.concurrent));
+        else
+          HIPCHK(jacobi_eig_batched(1, Zs + n, ns + n, ls + n, vs + n, ws + n, is + n, 40, st, false));
+      }
     } else {
       // beside other solves (the request server) small matrices take the
       // ordinary per-matrix launch: a cooperative grid does not share the
