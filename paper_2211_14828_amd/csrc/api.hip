@@ -160,18 +160,23 @@ struct Plan {
   int64_t chain_elems = 0;   // largest intermediate of the core / reconstruction chains
 };
 
-// Modes with fewer than half as many columns as rows whose unfolding is a matrix in
+// Modes with at most half as many columns as rows whose unfolding is a matrix in
 // memory as it stands (the first and the last): X X^T, I x I, is never formed.  A
 // float64 copy of X and a block T = Q^T X fit in its place, and a product (X X^T) Q
 // costs two of S I J operations, no more than the one of S I^2 with it.  Products and
-// sums are float64, so nothing is lost on X X^T in float32.  From 1024 rows on, where
-// forming and storing X X^T costs more than the extra launch a step.  Measured (us a
-// call, formed / direct, S = 15, one step): 512 x 256 361 / 333 but level with three
-// steps, 1024 x 512 458 / 409, 2048 x 1024 709 / 659, 4096 x 2048 1466 / 1011; the mode
-// of 7200 x 3072, S = 55: 2.1 of 5.6 ms a call.
-bool direct_mode(const Plan& P, const ModeGeom& g) {
+// sums are float64, so nothing is lost on X X^T in float32.
+// What is saved, forming and storing X X^T, is saved once and grows as I^2; what a step
+// pays for it, one more dependent launch, is paid q times.  So from 1024 rows on, with
+// q up to 2 I^2 / 1024^2.  Measured (us a call, formed / direct, S = 15), float32:
+// 1024 x 512 598 / 555 at q = 2, 1402 / 1407 at 8, 4302 / 4374 at 23; 2048 x 1024 757 /
+// 656 at 1, 2093 / 2036 at 8, 6137 / 6153 at 23; 4096 x 2048 1572 / 1048 at 1, 7555 /
+// 7328 at 23; float64: 1024 x 512 575 / 577 at 2, 1374 / 1482 at 8; 2048 x 1024 1388 /
+// 1392 at 4, 2235 / 2335 at 8; 4096 x 2048 8807 / 7583 at 23; power iteration, float32:
+// 1024 x 512 572 / 572 at 4, 2677 / 3302 at 50; the mode of 7200 x 3072, S = 55: 2.1 of
+// 5.6 ms a call.
+bool direct_mode(const Plan& P, const ModeGeom& g, int steps) {
   return !P.need_pad && !g.sampled && (g.A == 1 || g.B == 1) && g.I >= 1024 && 2 * g.J <= g.I &&
-         (g.I + g.Sp) * g.J <= g.I * g.I;
+         (g.I + g.Sp) * g.J <= g.I * g.I && g.I * g.I >= (int64_t)steps << 19;
 }
 
 int dtype_elem(int dt) { return dt == RBKI_F64 ? E_F64 : dt == RBKI_F32 ? E_F32 : E_BF16; }
@@ -277,7 +282,7 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
     g.S = std::min<int64_t>(std::min<int64_t>(g.R + P.p, g.I), g.m);   // Sec. 2.3, Sec. 4.1
     g.Sp = P.power ? g.S : g.S * (P.q + 1);
     if (g.Sp > 1200) return fail(RBKI_E_UNSUPPORTED, "Krylov width %lld > 1200 (mode %d)", (long long)g.Sp, n);
-    g.direct = direct_mode(P, g);
+    g.direct = direct_mode(P, g, P.q);
     // (the sequential form's first product takes the factor of mode 0)
     g.any_order = n != 0 && n != P.first_mode;
     P.maxI = std::max(P.maxI, g.I);
@@ -1651,6 +1656,8 @@ rbki_status adaptive_plan(const rbki_params* prm, int xtype, Plan& P, rbki_param
   pa.power = adaptive_q(prm, P0);
   s = make_plan(&pa, xtype, P);
   if (s != RBKI_OK) return s;
+  // (the rule rarely takes more than a few steps)
+  for (int n = 0; n < P.N; ++n) P.m[n].direct = direct_mode(P, P.m[n], std::min(P.q, 3));
   size_t off = plan_bytes(P);
   auto take = [&](size_t bytes) { off = (off + 255) & ~(size_t)255; size_t o = off; off += bytes; return o; };
   for (int n = 0; n < P.N; ++n) {
