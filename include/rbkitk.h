@@ -56,8 +56,9 @@ typedef enum { RBKI_F64 = 0, RBKI_F32 = 1, RBKI_BF16 = 2 } rbki_dtype;
  * eigenproblem and all norms are float64 in every form.
  *   PLAIN      : the tensor's own type (fp64 MFMA for F64, bf16 MFMA for
  *                BF16; for F32 fp32 MFMA, and in the sketch and Gram products
- *                bf16 MFMA on three bf16 parts that hold each value exactly),
- *                fp32 or fp64 accumulation.
+ *                bf16 MFMA on three bf16 parts that hold each value exactly
+ *                from 2^-110 up to the largest bf16 value), fp32 or fp64
+ *                accumulation.
  *   MIXED_BF16 : a bf16 copy of X feeds bf16 MFMA with fp32 accumulation.
  *   MIXED_FP8  : an e4m3 copy of X with power-of-two scales per 32^N block
  *                feeds the Gram and sketch products (block-scaled fp8 MFMA,

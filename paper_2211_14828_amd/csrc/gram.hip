@@ -21,7 +21,8 @@
 //
 // Float32 operands are split exactly into three bfloat16 parts while they are
 // staged, x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m (24
-// significand bits in three parts of 8; the parts of a finite x are exact),
+// significand bits in three parts of 8, exact where the last of them is a bfloat16
+// value, subnormal or not: |x| from 2^-110 up to the largest bfloat16 value),
 // and every product is formed from the six part products above 2^-24,
 // hh + hm + mh + mm + hl + lh, on 32x32x16 bfloat16 MFMA with float32
 // accumulation.  The terms left out (ml, lm, ll) are below 2^-25 of a product
