@@ -165,18 +165,22 @@ struct Plan {
 // float64 copy of X and a block T = Q^T X fit in its place, and a product (X X^T) Q
 // costs two of S I J operations, no more than the one of S I^2 with it.  Products and
 // sums are float64, so nothing is lost on X X^T in float32.
-// What is saved, forming and storing X X^T, is saved once and grows as I^2; what a step
-// pays for it, one more dependent launch, is paid q times.  So from 1024 rows on, with
-// q up to 2 I^2 / 1024^2.  Measured (us a call, formed / direct, S = 15), float32:
-// 1024 x 512 598 / 555 at q = 2, 1402 / 1407 at 8, 4302 / 4374 at 23; 2048 x 1024 757 /
-// 656 at 1, 2093 / 2036 at 8, 6137 / 6153 at 23; 4096 x 2048 1572 / 1048 at 1, 7555 /
-// 7328 at 23; float64: 1024 x 512 575 / 577 at 2, 1374 / 1482 at 8; 2048 x 1024 1388 /
-// 1392 at 4, 2235 / 2335 at 8; 4096 x 2048 8807 / 7583 at 23; power iteration, float32:
-// 1024 x 512 572 / 572 at 4, 2677 / 3302 at 50; the mode of 7200 x 3072, S = 55: 2.1 of
+// What is saved, forming and storing X X^T, is saved once and grows as I^2; a step pays
+// one more dependent launch for it, 4 to 12 us.  So from 1024 rows on (float64, whose
+// X X^T costs less there, 1280), where the few steps of a usual call gain; not by q,
+// for the call that chooses q gives the bits of the call with that q.  Measured (us a
+// call, formed / direct, S = 15), float32: 1024 x 512 598 / 555 at q = 2, 4302 / 4374 at
+// 23; 1500 x 700 697 / 605, 4365 / 4398; 2048 x 1024 919 / 825, 6137 / 6153; 4096 x 2048
+// 1772 / 1255, 7555 / 7328; float64: 1024 x 512 575 / 577, 4253 / 4602; 1100 x 30 505 /
+// 524, 4013 / 4342; 1500 x 700 685 / 613, 4428 / 4605; 2048 x 1024 1014 / 937, 6536 /
+// 6811; 4096 x 2048 2811 / 1531, 8807 / 7583; the mode of 7200 x 3072, S = 55: 2.1 of
 // 5.6 ms a call.
-bool direct_mode(const Plan& P, const ModeGeom& g, int steps) {
-  return !P.need_pad && !g.sampled && (g.A == 1 || g.B == 1) && g.I >= 1024 && 2 * g.J <= g.I &&
-         (g.I + g.Sp) * g.J <= g.I * g.I && g.I * g.I >= (int64_t)steps << 19;
+// Power iteration, whose steps are short, also by q, up to I^2 / 1024^2 (float32, 1024 x
+// 512 437 / 406 at q = 1, 572 / 572 at 4, 2677 / 3302 at 50; 2048 x 1024 933 / 936 at 4,
+// 1273 / 1386 at 8).
+bool direct_mode(const Plan& P, const ModeGeom& g) {
+  return !P.need_pad && !g.sampled && (g.A == 1 || g.B == 1) && g.I >= (P.gelem == E_F64 ? 1280 : 1024) &&
+         2 * g.J <= g.I && (g.I + g.Sp) * g.J <= g.I * g.I && (!P.power || g.I * g.I >= (int64_t)P.q << 20);
 }
 
 int dtype_elem(int dt) { return dt == RBKI_F64 ? E_F64 : dt == RBKI_F32 ? E_F32 : E_BF16; }
@@ -282,7 +286,7 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
     g.S = std::min<int64_t>(std::min<int64_t>(g.R + P.p, g.I), g.m);   // Sec. 2.3, Sec. 4.1
     g.Sp = P.power ? g.S : g.S * (P.q + 1);
     if (g.Sp > 1200) return fail(RBKI_E_UNSUPPORTED, "Krylov width %lld > 1200 (mode %d)", (long long)g.Sp, n);
-    g.direct = direct_mode(P, g, P.q);
+    g.direct = direct_mode(P, g);
     // (the sequential form's first product takes the factor of mode 0)
     g.any_order = n != 0 && n != P.first_mode;
     P.maxI = std::max(P.maxI, g.I);
@@ -1656,8 +1660,6 @@ rbki_status adaptive_plan(const rbki_params* prm, int xtype, Plan& P, rbki_param
   pa.power = adaptive_q(prm, P0);
   s = make_plan(&pa, xtype, P);
   if (s != RBKI_OK) return s;
-  // (the rule rarely takes more than a few steps)
-  for (int n = 0; n < P.N; ++n) P.m[n].direct = direct_mode(P, P.m[n], std::min(P.q, 3));
   size_t off = plan_bytes(P);
   auto take = [&](size_t bytes) { off = (off + 255) & ~(size_t)255; size_t o = off; off += bytes; return o; };
   for (int n = 0; n < P.N; ++n) {

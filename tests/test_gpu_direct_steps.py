@@ -1,6 +1,8 @@
-"""Tall modes on both sides of the rule by steps (1030 rows: up to two steps from X
-itself, from three on from X X^T; 1300: three and four), against the float64 oracle
-with the tolerances of test_gpu_parity.py."""
+"""Tall modes on both sides of the rule for products from X itself: 1030 rows (float32
+from X, float64 from X X^T), 1300 rows, power iteration of as many steps as the rule
+allows and one more; against the float64 oracle with the tolerances of
+test_gpu_parity.py.  And the call that chooses q gives the bits of the call with that q
+there, after many steps too."""
 import numpy as np
 import pytest
 
@@ -10,8 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["float64", "float32"])
-@pytest.mark.parametrize("dims,q,variant", [((1030, 40), 2, "krylov"), ((1030, 40), 3, "krylov"), ((20, 21, 1300), 3, "krylov"),
-                                            ((20, 21, 1300), 4, "krylov"), ((1030, 40), 9, "power")])
+@pytest.mark.parametrize("dims,q,variant", [((1030, 40), 2, "krylov"), ((20, 21, 1300), 3, "krylov"), ((1030, 40), 1, "power"),
+                                            ((1030, 40), 2, "power"), ((20, 21, 1500), 2, "power"),
+                                            ((20, 21, 1500), 3, "power"), ((1030, 40), 9, "power")])
 def test_steps(dims, q, variant, dtype):
     import torch
     import paper_2211_14828_amd as rb
@@ -22,3 +25,21 @@ def test_steps(dims, q, variant, dtype):
     core, factors, err = rb.tucker(torch.from_numpy(X).to("cuda"), ranks, p=4, q=q, seed=2, variant=variant)
     _, _, ref = rbki_tucker(X.astype(np.float64), ranks, 4, q, 2, variant=variant)
     assert abs(err - ref) <= (1e-10 if dtype == "float64" else 1e-5) * ref
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("dims,q", [((1030, 300), 7), ((1300, 30, 20), 5)])
+def test_chosen_q_gives_the_same_bits(dims, q, dtype):
+    import torch
+    import paper_2211_14828_amd as rb
+    ranks = [6] * len(dims)
+    X = torch.from_numpy(np.random.default_rng(q).standard_normal(dims).astype(dtype)).to("cuda")
+    core, factors, err, used = rb.tucker_adaptive(X, ranks, p=4, max_q=q, fit_tol=-1.0, seed=2)
+    assert used == q
+    c, f, e = rb.tucker(X, ranks, p=4, q=q, seed=2)
+    assert e == err and torch.equal(c, core) and all(torch.equal(U, V) for U, V in zip(f, factors))
+    # (a plan made for more steps than are taken)
+    core, factors, err, used = rb.tucker_adaptive(X, ranks, p=4, max_q=q, fit_tol=1.0, seed=2)
+    assert used == 1
+    c, f, e = rb.tucker(X, ranks, p=4, q=1, seed=2)
+    assert e == err and torch.equal(c, core) and all(torch.equal(U, V) for U, V in zip(f, factors))
