@@ -354,9 +354,11 @@ rbki_status make_plan(const rbki_params* prm, int xtype, Plan& P) {
 }
 
 constexpr size_t kDgemmScratch = (size_t)8 << 20;    // split-K partials of the float64 GEMMs
-// What one scratch set may spend, beyond its own buffers, on chain sets for
-// the other modes (plan_chain_sets).
-constexpr size_t kChainSpare = (size_t)24 << 20;
+// What one scratch set may spend, beyond its own buffers, on chain sets for the other
+// modes (plan_together): what the GEMM scratch, 32 MiB before the products took their
+// split sums through LDS, no longer takes, less the eigen-solver's exchange rings (up to
+// 66 KB a mode more than the partial products they replaced), so that no workspace grew.
+constexpr size_t kChainSpare = (size_t)23 << 20;
 
 struct Arena {
   char* base;
