@@ -577,6 +577,7 @@ rbki_status convert_input(const Plan& P, const Buffers& b, const void* X, hipStr
 // and Z).
 constexpr double TAU_REL = 1e-12;   // pivot vs its own column: direction already spanned
 constexpr double TAU_ABS = 1e-10;   // pivot vs the block before projection (matches the oracle)
+constexpr double TAU_KEPT = 0.1;    // second pass: what has to be left of a vector of the first
 
 // A direct mode's T = Q^T X_(n) (rows x J) and T X_(n)^T (rows x I); X64: its X.
 GemmJob direct_first(const ModeGeom& g, int64_t rows, const double* Q, const double* X64, double* T) {
@@ -746,10 +747,9 @@ struct ModeSet {
   }
 };
 
-// Alg. 1, block 0: Q_0 = orth(W) from W^T in each set's Yt.  The first pass
-// of every block's CholeskyQR2 also keeps the basis at most I_n wide: once
-// it spans the whole space the later blocks are rounding noise and are
-// dropped whatever their norm.
+// Alg. 1, block 0: Q_0 = orth(W) from W^T in each set's Yt.  Every block's
+// CholeskyQR2 also keeps the basis at most I_n wide: once it spans the whole
+// space the later blocks are rounding noise and are dropped whatever their norm.
 CholJob orth_job(const ModeGeom& g, const Lane& L, double* Y, double* Yout) {
   CholJob c = {};
   c.Y = Y;
@@ -759,6 +759,21 @@ CholJob orth_job(const ModeGeom& g, const Lane& L, double* Y, double* Yout) {
   c.G = L.G;
   c.Lm = L.L;
   c.flags = L.flags;
+  return c;
+}
+
+// The second pass, from the first's result in the set's Ytmp (unit vectors) to Yout.
+// A vector that the first pass kept is close to orthogonal, unless it was rounding
+// noise: a pivot after a small one that was kept carries the rounding error of that
+// one's column, divided by it, and can pass the tests with nothing but components
+// along the vectors before it (and, after a projection, along the earlier blocks).
+// Those have next to nothing left here and are dropped; what is kept is orthonormal to
+// rounding, since no kept pivot is small.  ref2: the squared norms of Ytmp (before its
+// projection, if there is one).
+CholJob again_job(const ModeGeom& g, const Lane& L, double* Yout) {
+  CholJob c = orth_job(g, L, L.Ytmp, Yout);
+  c.ref2 = L.ref2;
+  c.tau_abs = TAU_KEPT;
   return c;
 }
 
@@ -773,7 +788,9 @@ rbki_status krylov_block0(const Plan& P, const Buffers& b, const ModeSet& ms, hi
     first[i].ref2 = first[i].norms = L.ref2;
     first[i].tau_abs = TAU_ABS;
     first[i].bud = DimBudget{used, used + 1, g.I};
-    second[i] = orth_job(g, L, L.Ytmp, b.Qt[n]);
+    second[i] = again_job(g, L, b.Qt[n]);
+    second[i].norms = L.ref2;
+    second[i].bud = first[i].bud;
   }
   HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
   HIPCHK(chol_orth_batched(second, ms.count, TAU_REL, st));
@@ -781,14 +798,16 @@ rbki_status krylov_block0(const Plan& P, const Buffers& b, const ModeSet& ms, hi
 }
 
 // Alg. 1, Krylov step j >= 1: block j of the basis from (X X^T) Q_{j-1} (Ck
-// is X X^T, or Y Y^T of a sampled mode), projected off the earlier blocks
-// twice and orthonormalised.  The product C Q_{j-1} is formed into the
+// is X X^T, or Y Y^T of a sampled mode), projected off the earlier blocks and
+// orthonormalised, twice: the second projection takes unit vectors, so that
+// those of which little was left by the first (a mode of low rank) end up as
+// orthogonal to the earlier blocks as the others.  The product C Q_{j-1} is formed into the
 // set's Yt and, when CQ is given, kept as rows (j-1) S.. of CQ; with from_cq
 // it is taken from there instead (formed earlier with the same C).
 rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int j, double* const* Ck,
                         double* const* CQ, const bool* from_cq, hipStream_t st) {
   GramProduct cq[8];
-  GemmJob proj[8], upd[8];
+  GemmJob proj[2][8], upd[2][8];
   CholJob first[8], second[8];
   int ncq = 0;
   for (int i = 0; i < ms.count; ++i) {
@@ -804,24 +823,26 @@ rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int 
       // Y_j^T = Q_{j-1}^T C  (C symmetric)
       cq[ncq++] = GramProduct{n, S, Qt + (m - S) * I, Ck[i], L.Yt, CQ[i] ? CQ[i] + (m - S) * I : nullptr};
     }
-    // remove earlier blocks, twice
-    proj[i] = gemm_job(0, 1, S, m, I, 1.0, L.Yt, I, Qt, I, 0.0, L.Pm, m);
-    upd[i] = gemm_job(0, 0, S, I, m, -1.0, L.Pm, m, Qt, I, 1.0, L.Yt, I);
+    for (int pass = 0; pass < 2; ++pass) {       // remove earlier blocks
+      double* Y = pass ? L.Ytmp : L.Yt;
+      proj[pass][i] = gemm_job(0, 1, S, m, I, 1.0, Y, I, Qt, I, 0.0, L.Pm, m);
+      proj[pass][i].norms = L.ref2;
+      upd[pass][i] = gemm_job(0, 0, S, I, m, -1.0, L.Pm, m, Qt, I, 1.0, Y, I);
+    }
     first[i] = orth_job(g, L, L.Yt, L.Ytmp);
     first[i].ref2 = L.ref2;
     first[i].tau_abs = TAU_ABS;
     first[i].bud = DimBudget{used + j, used + j + 1, I};
-    second[i] = orth_job(g, L, L.Ytmp, Qt + m * I);
+    second[i] = again_job(g, L, Qt + m * I);
+    second[i].bud = first[i].bud;
   }
   rbki_status s = gram_products(P, cq, ncq, st);
   if (s != RBKI_OK) return s;
   for (int pass = 0; pass < 2; ++pass) {
-    for (int i = 0; i < ms.count; ++i) proj[i].norms = pass == 0 ? b.ln[ms.lane[i]].ref2 : nullptr;
-    HIPCHK(dgemm_batched(proj, ms.count, st));
-    HIPCHK(dgemm_batched(upd, ms.count, st));
+    HIPCHK(dgemm_batched(proj[pass], ms.count, st));
+    HIPCHK(dgemm_batched(upd[pass], ms.count, st));
+    HIPCHK(chol_orth_batched(pass ? second : first, ms.count, TAU_REL, st));
   }
-  HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
-  HIPCHK(chol_orth_batched(second, ms.count, TAU_REL, st));
   return RBKI_OK;
 }
 
@@ -853,7 +874,8 @@ rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, 
       first[i] = orth_job(g, L, L.Yt, L.Ytmp);
       first[i].ref2 = first[i].norms = L.ref2;
       first[i].tau_abs = TAU_ABS;
-      second[i] = orth_job(g, L, L.Ytmp, b.Qt[n]);
+      second[i] = again_job(g, L, b.Qt[n]);
+      second[i].norms = L.ref2;
     }
     for (int j = 1; j <= P.q; ++j) {
       if ((s = gram_products(P, job, ms.count, st)) != RBKI_OK) return s;
