@@ -668,7 +668,7 @@ rbki_status run_mode_heavy(const Plan& P, const Buffers& b, int lane, const void
       // small I or a sketch wider than 64: the bf16 kernel on the padded copies
       {
         ProfScope ps("omega", st);
-        HIPCHK(launch_omega_pad(P.seed, n, S, g.J, g.B, P.dims[P.N - 1], A * Bp, L.omegaT, st));
+        HIPCHK(launch_omega_pad(P.seed, n, S, g.J, g.B, last ? 0 : P.dims[P.N - 1], A * Bp, L.omegaT, st));
       }
       GramArgs ga = gram_plan(E_BF16, A, I, Bp, (int)S, cu_count(), -1, g.any_order);
       ga.X = last ? b.xt : b.xpad;
@@ -1086,7 +1086,7 @@ rbki_status first_product(const Plan& P, const Buffers& b, const void* xsrc, hip
     // precision form: the product reads the padded bf16 copy on bf16 MFMA
     HIPCHK(convert_tensor(E_F64, b.Ut64[n], E_BF16, b.Uop, P.m[n].R * I, st));
     ProfScope ps("ttm", st);
-    HIPCHK(launch_ttm_padded(b.xpad, A, I, B, P.dims[P.N - 1], b.Uop, P.m[n].R, out, st));
+    HIPCHK(launch_ttm_padded(b.xpad, A, I, B, P.dims[P.N - 1], n == P.N - 1, b.Uop, P.m[n].R, out, st));
   } else {
     const void* U;
     rbki_status s = operand_rows(P, b, n, P.telem, &U, st);

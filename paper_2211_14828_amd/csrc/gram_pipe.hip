@@ -605,8 +605,8 @@ __global__ void __launch_bounds__(64 * PRED_GROUPS) gram_pipe_reduce_kernel(Gram
 // Omega^T (S x J) of one mode, blocked: the value of stream index L = s J + j
 // goes to padded column jp(j), stored at [jp / KT][s][jp % KT] (KT values per
 // 64 sketch rows of a K tile); padded columns and rows s >= S must be zero
-// beforehand.  B = 1: jp = j.  B > 1: j = a B + b with b = bh I_N + bl,
-// jp = a Bp + bh I_Npad + bl.
+// beforehand.  j = a B + b with b = bh I_N + bl, jp = a Bp + bh I_Npad + bl (B and
+// I_N may be 1: every value then has a run of its own; I_Npad = 1: jp = j).
 // Index arithmetic in 32 bits when every index fits (the common case), else 64.
 template <class IT>
 __global__ void omega_block_kernel(uint64_t seed, uint32_t mode, int64_t S, int64_t J_, int64_t B_, int64_t IN_,
@@ -614,7 +614,7 @@ __global__ void omega_block_kernel(uint64_t seed, uint32_t mode, int64_t S, int6
   const IT J = (IT)J_, B = (IT)B_, IN = (IT)IN_, INp = (IT)INp_;
   const int64_t total = S * J_;
   const int64_t npairs = (total + 1) / 2;
-  const IT Bp = B > 1 ? (B / IN) * INp : 1;
+  const IT Bp = (B / IN) * INp;
   const IT kt_sz = (IT)KT;
   for (int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; m < npairs;
        m += (int64_t)gridDim.x * blockDim.x) {
@@ -626,12 +626,9 @@ __global__ void omega_block_kernel(uint64_t seed, uint32_t mode, int64_t S, int6
       if (L >= total) break;
       const IT Lt = (IT)L;
       const IT sv = Lt / J, j = Lt - sv * J;
-      IT jp = j;
-      if (B > 1) {
-        const IT a = j / B, b = j - a * B;
-        const IT bh = b / IN, bl = b - bh * IN;
-        jp = a * Bp + bh * INp + bl;
-      }
+      const IT a = j / B, b = j - a * B;
+      const IT bh = b / IN, bl = b - bh * IN;
+      const IT jp = a * Bp + bh * INp + bl;
       const IT kt = jp / kt_sz, kk = jp - kt * kt_sz;
       out[((int64_t)kt * PW + sv) * KT + kk] = f32_to_bf16(z[h]);
     }
@@ -1030,22 +1027,19 @@ __global__ void zero_pad_rows_kernel(char* out, unsigned char* scales, int64_t n
 template <class IT>
 __global__ void omega_fp8_kernel(uint64_t seed, uint32_t mode, int64_t S_, int64_t J_, int64_t B_, int64_t IN_,
                                  int64_t INp_, int64_t nrows, fp8_t* q, unsigned char* scales) {
-  const IT S = (IT)S_, J = (IT)J_, B = (IT)B_, IN = (IT)IN_, INp = (IT)INp_;
-  const IT Bp = B > 1 ? (B / IN) * INp : 1;
+  const IT S = (IT)S_, B = (IT)B_, IN = (IT)IN_, INp = (IT)INp_;
+  const IT Bp = (B / IN) * INp;
   const int lane = threadIdx.x & 63, pl = lane & 31;
   for (int64_t r2 = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); 2 * r2 < nrows;
        r2 += (int64_t)gridDim.x * (blockDim.x >> 6)) {
     const int64_t r = 2 * r2 + (lane >> 5);
     const IT kt = (IT)(r >> 6), sv = (IT)(r & 63);
     const IT jp = kt * 64 + (IT)(2 * pl);             // even: jp and jp + 1 share a and bh
-    IT j = jp, cols_left = J > jp ? J - jp : 0;
-    bool rowok = sv < S;
-    if (B > 1) {
-      const IT a = jp / Bp, bp = jp - a * Bp;
-      const IT bh = bp / INp, bl = bp - bh * INp;
-      j = a * B + bh * IN + bl;
-      cols_left = bl < IN ? IN - bl : 0;               // valid columns from jp on within this run of I_N
-    }
+    const bool rowok = sv < S;
+    const IT a = jp / Bp, bp = jp - a * Bp;
+    const IT bh = bp / INp, bl = bp - bh * INp;
+    const IT j = a * B + bh * IN + bl;
+    const IT cols_left = bl < IN ? IN - bl : 0;         // valid columns from jp on within this run of I_N
     float v[2] = {0.f, 0.f};
     if (rowok && cols_left > 0) {
       const int64_t L = (int64_t)sv * J_ + (int64_t)j;
@@ -1273,6 +1267,8 @@ hipError_t launch_omega_pad(uint64_t seed, int mode, int64_t S, int64_t J, int64
   // the row-major S x Jp layout is the blocked one with a single K tile of Jp
   // columns: [0][s][jp]
   if (Jp >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  const int64_t INp = IN > 0 ? pad64(IN) : 1;
+  if (IN < 1) IN = 1;
   hipError_t e = fill_zero(out, (size_t)S * Jp * 2, s);
   if (e != hipSuccess) return e;
   const int64_t npairs = (S * J + 1) / 2;
@@ -1280,10 +1276,10 @@ hipError_t launch_omega_pad(uint64_t seed, int mode, int64_t S, int64_t J, int64
   if (grid == 0) return hipSuccess;
   if (S * J < ((int64_t)1 << 31) && S * Jp < ((int64_t)1 << 31))
     hipLaunchKernelGGL(omega_block_kernel<uint32_t>, dim3(grid), dim3(256), 0, s, seed, (uint32_t)mode, S, J, B, IN,
-                       pad64(IN), (int)Jp, (bf16_t*)out);
+                       INp, (int)Jp, (bf16_t*)out);
   else
     hipLaunchKernelGGL(omega_block_kernel<uint64_t>, dim3(grid), dim3(256), 0, s, seed, (uint32_t)mode, S, J, B, IN,
-                       pad64(IN), (int)Jp, (bf16_t*)out);
+                       INp, (int)Jp, (bf16_t*)out);
   return hipGetLastError();
 }
 

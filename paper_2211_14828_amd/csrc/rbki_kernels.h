@@ -73,12 +73,13 @@ hipError_t launch_block_copies(int src_elem, int elem, const void* X, int order,
 hipError_t launch_omega_fp8(uint64_t seed, int mode, int64_t S, int64_t J, int64_t B, int64_t IN, int64_t nkt,
                             void* q, void* scales, hipStream_t s);
 // Omega^T (S x J) of one mode as bf16 in the padded column layout S x Jp
-// (row-major; the Gram fallback of the mixed forms).
+// (row-major; the Gram fallback of the mixed forms).  IN = 0 (with B = 1): the columns
+// follow each other, unpadded but at the end (the last mode).
 hipError_t launch_omega_pad(uint64_t seed, int mode, int64_t S, int64_t J, int64_t B, int64_t IN, int64_t Jp,
                             void* out, hipStream_t s);
 // Omega^T (S x J, S <= 64) of one mode as bf16, blocked [nkt][64][KT] in the
-// padded column order (B: the mode's trailing size, IN: the last dimension;
-// B = 1 for the last mode); zero in padded columns and rows past S.
+// padded column order (B: the mode's trailing size, IN: the last dimension; for the
+// last mode B = J and IN the dimension before it); zero in padded columns and rows past S.
 hipError_t launch_omega_block(uint64_t seed, int mode, int64_t S, int64_t J, int64_t B, int64_t IN, int64_t nkt,
                               int KT, void* out, hipStream_t s);
 hipError_t launch_philox(const uint32_t* ctr, int64_t count, uint64_t seed, uint32_t* out, hipStream_t s);
@@ -235,9 +236,10 @@ hipError_t launch_ttm(int elem, const void* X, int64_t A, int64_t I, int64_t B, 
                       int64_t R, void* Y, void* work, size_t work_bytes, hipStream_t s);
 size_t ttm_work_bytes(int elem, int64_t A, int64_t I, int64_t B, int64_t R);
 // The same product in bf16 on the zero-padded copy Xpad (rows of the last
-// dimension IN padded to pad64(IN)); Y is written in the unpadded layout.
-hipError_t launch_ttm_padded(const void* Xpad, int64_t A, int64_t I, int64_t B, int64_t IN, const void* Ut,
-                             int64_t R, void* Y, hipStream_t s);
+// dimension IN padded to pad64(IN)); Y is written in the unpadded layout.  last: the
+// last mode (others have B = 1, and rows apart by a padded run, where IN is 1).
+hipError_t launch_ttm_padded(const void* Xpad, int64_t A, int64_t I, int64_t B, int64_t IN, bool last,
+                             const void* Ut, int64_t R, void* Y, hipStream_t s);
 
 // First mode product of the precision forms from a leading mode's blocked
 // copy xb (E_FP8 with its scales, or E_BF16), view [A, I, B] of X with last

@@ -1211,13 +1211,13 @@ hipError_t launch_ttm(int elem, const void* X, int64_t A, int64_t I, int64_t B, 
   }
 }
 
-hipError_t launch_ttm_padded(const void* Xpad, int64_t A, int64_t I, int64_t B, int64_t IN, const void* Ut,
-                             int64_t R, void* Y, hipStream_t s) {
+hipError_t launch_ttm_padded(const void* Xpad, int64_t A, int64_t I, int64_t B, int64_t IN, bool last,
+                             const void* Ut, int64_t R, void* Y, hipStream_t s) {
   const int64_t INp = pad64(IN);
   ProdArgs p = {};
   p.K = I;
   int64_t batches;
-  if (B > 1) {
+  if (!last) {
     // Y[a] (R x B) = Ut (R x I) . Xpad[a] (I x Bp): rows r, padded columns mapped back
     const int64_t Bp = (B / IN) * INp;
     p.a = {Ut, I, 1, 0, R};
