@@ -768,11 +768,9 @@ CholJob orth_job(const ModeGeom& g, const Lane& L, double* Y, double* Yout) {
 // one's column, divided by it, and can pass the tests with nothing but components
 // along the vectors before it (and, after a projection, along the earlier blocks).
 // Those have next to nothing left here and are dropped; what is kept is orthonormal to
-// rounding, since no kept pivot is small.  ref2: the squared norms of Ytmp (before its
-// projection, if there is one).
+// rounding, since no kept pivot is small.
 CholJob again_job(const ModeGeom& g, const Lane& L, double* Yout) {
   CholJob c = orth_job(g, L, L.Ytmp, Yout);
-  c.ref2 = L.ref2;
   c.tau_abs = TAU_KEPT;
   return c;
 }
@@ -789,7 +787,6 @@ rbki_status krylov_block0(const Plan& P, const Buffers& b, const ModeSet& ms, hi
     first[i].tau_abs = TAU_ABS;
     first[i].bud = DimBudget{used, used + 1, g.I};
     second[i] = again_job(g, L, b.Qt[n]);
-    second[i].norms = L.ref2;
     second[i].bud = first[i].bud;
   }
   HIPCHK(chol_orth_batched(first, ms.count, TAU_REL, st));
@@ -826,7 +823,7 @@ rbki_status krylov_step(const Plan& P, const Buffers& b, const ModeSet& ms, int 
     for (int pass = 0; pass < 2; ++pass) {       // remove earlier blocks
       double* Y = pass ? L.Ytmp : L.Yt;
       proj[pass][i] = gemm_job(0, 1, S, m, I, 1.0, Y, I, Qt, I, 0.0, L.Pm, m);
-      proj[pass][i].norms = L.ref2;
+      if (pass == 0) proj[pass][i].norms = L.ref2;
       upd[pass][i] = gemm_job(0, 0, S, I, m, -1.0, L.Pm, m, Qt, I, 1.0, Y, I);
     }
     first[i] = orth_job(g, L, L.Yt, L.Ytmp);
@@ -875,7 +872,6 @@ rbki_status run_mode_chains(const Plan& P, const Buffers& b, const ModeSet& ms, 
       first[i].ref2 = first[i].norms = L.ref2;
       first[i].tau_abs = TAU_ABS;
       second[i] = again_job(g, L, b.Qt[n]);
-      second[i].norms = L.ref2;
     }
     for (int j = 1; j <= P.q; ++j) {
       if ((s = gram_products(P, job, ms.count, st)) != RBKI_OK) return s;

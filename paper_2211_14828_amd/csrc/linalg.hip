@@ -162,7 +162,7 @@ __global__ void gemm_reduce_kernel(GemmArgs a) {
 // column of the factor set to zero and a zero row of Yout, when
 // d_k <= tau_rel * G_kk (the vector lies within the span of the earlier kept ones to
 // working accuracy), when d_k <= tau_abs^2 * max_k ref2[k] (it is at round-off level
-// relative to the block before projection) or when the direction budget is spent.
+// relative to the block before projection; without ref2, to vectors of length 1) or when the direction budget is spent.
 // flags[k] = 1 for kept vectors.
 //
 // A workgroup of four waves takes 64 columns of Y and factors G itself, so no
@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(256) chol_solve_kernel(CholArgs a) {
   }
   __syncthreads();
   for (int k = tid; k < SM; k += 256) diag[k] = Ls[k][k];
-  double mx = 0.0;
+  double mx = job.ref2 ? 0.0 : 1.0;
   if (job.ref2)
     for (int k = lane; k < s; k += 64) mx = fmax(mx, formed ? (job.norms ? Ls[k][k] : job.ref2[k]) : job.ref2[k]);
   const double abs_floor = job.tau_abs * job.tau_abs * warp_max(mx);
@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(1024) chol_drop_kernel(const double* G, int64_
   __shared__ int sh_keep;
   __shared__ double sh_piv;
   const int tid = threadIdx.x;
-  double mx = 0.0;
+  double mx = ref2 ? 0.0 : 1.0;
   if (ref2)
     for (int64_t i = tid; i < s; i += blockDim.x) mx = fmax(mx, ref2[i]);
   mx = warp_max(mx);

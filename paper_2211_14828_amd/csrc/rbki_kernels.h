@@ -132,7 +132,7 @@ hipError_t dgemm_batched(const GemmJob* jobs, int njobs, hipStream_t s);
 // dropped (its vector set to zero) when it falls below tau_rel times its own
 // Gram diagonal or below tau_abs^2 times the largest ref2 entry.  G and Lm
 // are s x s scratch; flags (int[s]) receives 1 for kept vectors; ref2
-// (device, s doubles, nullable) holds squared reference norms.
+// (device, s doubles, nullable: 1) holds squared reference norms.
 //
 // DimBudget caps the kept directions of a basis built block by block at the
 // dimension of the space: `used_in` (device int) holds the count kept by
